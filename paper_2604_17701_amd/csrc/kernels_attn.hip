@@ -54,7 +54,8 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, bj = lane & 15, bg = lane >> 4;
     const int m0 = b * a.K;
     const int L = a.row_pos[m0], slot = a.row_slot[m0];
-    const int n_keys = min(L + a.K, a.max_ctx), R = a.rep * a.K;
+    const int K = min(a.K, a.rows - m0);   // a prompt's last block of rows may be short; a round's blocks never are
+    const int n_keys = min(L + K, a.max_ctx), R = a.rep * K;
     const bf16_t *kc = a.kv_layer + (size_t)slot * a.slot_stride + (size_t)g * a.ctx_pad * HD;
     const bf16_t *vc = kc + (size_t)a.G * a.ctx_pad * HD;
     const int n_steps = (n_keys + STEP - 1) / STEP, sps = (n_steps + a.n_splits - 1) / a.n_splits;
@@ -110,18 +111,18 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
         bf16_t *kw = a.kv_write + (size_t)slot * a.slot_stride + (size_t)g * a.ctx_pad * HD;
         bf16_t *vw = kw + (size_t)a.G * a.ctx_pad * HD;
         bf16_t *q16 = reinterpret_cast<bf16_t *>(qs);
-        for (int it = tid; it < (16 * NQ + (appends ? 2 * a.K : 0)) * 16; it += 64 * NW) {
+        for (int it = tid; it < (16 * NQ + (appends ? 2 * K : 0)) * 16; it += 64 * NW) {
             const int row = it >> 4, i = (it & 15) * 4;   // features i .. i + 3 and their partners i + 64 .. i + 67
             int j, col;                      // token of the block, first column of the head in a qkv row
             if (row < 16 * NQ) {
                 const int rho = min(row, R - 1);
                 j = rho / a.rep;
                 col = (g * a.rep + rho % a.rep) * HD;
-            } else if (row < 16 * NQ + a.K) {
+            } else if (row < 16 * NQ + K) {
                 j = row - 16 * NQ;
                 col = d_q + g * HD;
             } else {
-                j = row - 16 * NQ - a.K;
+                j = row - 16 * NQ - K;
                 col = d_q + d_kv + g * HD;
             }
             const float *src = a.qkv + (size_t)(m0 + j) * d_all + col + i;
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
                 *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0) * 2 + 1) * 64 + ln) << 3) + e) = pack(l0);
                 *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0 + 2) * 2 + 0) * 64 + ln) << 3) + e) = pack(h1);
                 *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0 + 2) * 2 + 1) * 64 + ln) << 3) + e) = pack(l1);
-            } else if (row < 16 * NQ + a.K) {
+            } else if (row < 16 * NQ + K) {
                 bf16_t k0[4], k1[4];
 #pragma unroll
                 for (int c = 0; c < 4; ++c) { k0[c] = f32_to_bf16(r0[c]); k1[c] = f32_to_bf16(r1[c]); }
@@ -493,14 +494,26 @@ template <int NQ, int NW, bool FUSE> static bool launch_nq(Ctx *c, const AttnArg
 // workgroups 44.7 us, 2 splits 29.1 us; 24 streams over 4096: 2 splits 112.8 us, 1 split 98.7 us) and 16 in all
 // (one stream over 512: the round takes 3.51 ms with 3 splits and their combine kernel, 3.55 ms with one).
 // 0: the shape is not served.
+//
+// A prompt's chunk has more rows than the 64 query rows one workgroup meets: it is cut into blocks of 64 / rep rows,
+// each treated as a stream of its own whose cached length is its first row's position (k_rope_append has written the
+// whole chunk's k, v rows before, and a block's causal limit is its own last position).
+static int attn_block(const Ctx *c, const Fwd &f) {
+    const wisv_config &g = c->cfg;
+    const int rep = g.n_heads / g.n_kv_heads;
+    if (!c->bf16 || g.head_dim != HD || rep > 64 || f.rows != f.batch * f.k) return 0;
+    if (rep * f.k <= 64) return f.k;
+    return f.batch == 1 ? 64 / rep : 0;
+}
 static int attn_splits(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
-    const int rep = g.n_heads / g.n_kv_heads, R = rep * f.k;
-    if (!c->bf16 || g.head_dim != HD || R > 64 || f.rows != f.batch * f.k) return 0;
-    const int nw = R <= 32 ? 8 : 4;
-    const int n_steps = (f.max_len_ub + STEP - 1) / STEP, wgs = f.batch * g.n_kv_heads;
+    const int block = attn_block(c, f);
+    if (!block) return 0;
+    const int nw = g.n_heads / g.n_kv_heads * block <= 32 ? 8 : 4;
+    const int n_steps = (f.max_len_ub + STEP - 1) / STEP, wgs = (f.rows + block - 1) / block * g.n_kv_heads;
     const int want = std::max(1, std::min(256 / wgs, (n_steps + nw - 1) / nw));
-    return std::max(1, std::min(std::min(want, 16), c->att_max_splits));   // 16: one batch of the combine kernel
+    // 16: one batch of the combine kernel
+    return std::max(1, std::min(std::min(want, 16), (int)std::min<size_t>(64, c->att_cap / f.rows)));
 }
 
 // With several k-splits every split repeats the query part of the prologue (it sums the QKV slices of its queries
@@ -508,7 +521,8 @@ static int attn_splits(const Ctx *c, const Fwd &f) {
 // for RoPE and the append: 8 rows over 4096 cached tokens 4.04 -> 3.92 ms per round; 96 rows, 2 splits 6.34 -> 6.15;
 // 72 rows, 3 splits 6.25 -> 6.09; 32 rows over 4096 tokens, 8 splits 4.98 -> 4.86; 24 rows over 8192 tokens, 16
 // splits 4.88 -> 4.89.  k_rope_append serves the shapes this kernel does not take.
-bool attn_mfma_fuses_rope(const Ctx *c, const Fwd &f) { return attn_splits(c, f) >= 1; }
+// A chunk cut into blocks cannot fuse it: a block reads the k, v rows of the blocks before it.
+bool attn_mfma_fuses_rope(const Ctx *c, const Fwd &f) { return attn_block(c, f) == f.k; }
 
 // c->o from the k-split partials in c->att_o / att_m / att_l
 void launch_attn_combine(Ctx *c, const Fwd &f, int n_splits) {
@@ -526,7 +540,7 @@ void launch_attn_combine(Ctx *c, const Fwd &f, int n_splits) {
 // itself; n_partial == 0: launch_rope_append has run
 bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_combine, int *n_splits, int n_ss) {
     const wisv_config &g = c->cfg;
-    const int rep = g.n_heads / g.n_kv_heads, R = rep * f.k;
+    const int block = attn_block(c, f), rep = g.n_heads / g.n_kv_heads, R = rep * block;
     AttnArgs a;
     a.n_splits = attn_splits(c, f);
     if (!a.n_splits || (n_partial > 0 && !attn_mfma_fuses_rope(c, f))) return false;
@@ -534,15 +548,15 @@ bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_
     a.kv_layer = (const bf16_t *)kv_ptr(c, layer, 0, 0);
     a.kv_write = (bf16_t *)kv_ptr(c, layer, 0, 0);
     a.slot_stride = (size_t)2 * g.n_kv_heads * c->ctx_pad * g.head_dim;
-    a.H = g.n_heads; a.G = g.n_kv_heads; a.rep = rep; a.K = f.k; a.max_ctx = g.max_ctx; a.ctx_pad = c->ctx_pad; a.rows = f.rows;
+    a.H = g.n_heads; a.G = g.n_kv_heads; a.rep = rep; a.K = block; a.max_ctx = g.max_ctx; a.ctx_pad = c->ctx_pad; a.rows = f.rows;
     a.row_slot = c->row_slot; a.row_pos = c->row_pos;
     a.po = c->att_o; a.pm = c->att_m; a.pl = c->att_l;
     a.o = act_planes(c->o, c->o_planes);
-    a.qkv = c->qkv; a.n_partial = n_partial; a.partial_stride = (size_t)c->rows_max * c->d_qkv;
+    a.qkv = c->qkv; a.n_partial = n_partial; a.partial_stride = (size_t)c->slice_rows * c->d_qkv;
     a.cs = c->rope_cos; a.sn = c->rope_sin;
     a.ss = c->ss; a.n_ss = n_ss; a.d_model = g.d_model; a.eps = g.rms_eps;
     if (n_ss > 0 && n_partial == 0) return false;   // only the fused prologue applies the scale
-    dim3 grid(a.n_splits, g.n_kv_heads, f.batch);
+    dim3 grid(a.n_splits, g.n_kv_heads, (f.rows + block - 1) / block);
     {
         ProfScope ps(c, KC_ATTN);
         bool ok;

@@ -1032,7 +1032,7 @@ int launch_gemm_ws_normfold(Ctx *c, const void *Wt, const float *x_in, float *x_
     s = std::max(1, std::min(s, std::min(max_splits, std::max(1, g.nkt / 8))));
     g.kt_per_split = (g.nkt + s - 1) / s;
     const int splits = (g.nkt + g.kt_per_split - 1) / g.kt_per_split;
-    g.xin = x_in; g.xout = x_out; g.ys = c->y; g.ys_stride = (size_t)c->rows_max * kd; g.n_partial = n_partial;
+    g.xin = x_in; g.xout = x_out; g.ys = c->y; g.ys_stride = (size_t)c->slice_rows * kd; g.n_partial = n_partial;
     g.gain = (const bf16_t *)gain; g.ss_out = ss;
     return launch_ws_t<1, 1, 8, 1, 4, EPI_PARTIAL, PRO_NORM>(c, g, splits, 40 * 1024) ? splits : 0;
 }

@@ -83,9 +83,10 @@ void launch_embed(Ctx *c, const Fwd &f) {
 // ------------------------------------------------------------------------------------------ RMSNorm
 // x[m] += y[0][m] + ... + y[n_partial-1][m] (fixed order), then out[m] = x[m] / sqrt(mean(x^2)+eps) * g
 // NP: the most slices a launch may hold (the loads of all NP are issued whatever n_partial is)
+// ss_out != null: the 1 / rms is left to whoever adds up the product's slices (out = x * g, ss_out[m] = sum of x^2)
 template <typename WT, typename AT, int NP>
 __global__ __launch_bounds__(1024) void k_rmsnorm(float *x, const float *__restrict__ y, int n_partial, size_t partial_stride,
-                          const WT *__restrict__ g, int d, float eps, ActBuf out, float *out_f32) {
+                          const WT *__restrict__ g, int d, float eps, ActBuf out, float *out_f32, float *ss_out) {
     __shared__ float red[16];
     const int m = blockIdx.x;
     float *xr = x + (size_t)m * d;
@@ -111,7 +112,8 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float *x, const float *__restr
         ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     }
     ss = block_sum<1024>(ss, red);
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+    const float inv = ss_out ? 1.0f : 1.0f / sqrtf(ss / (float)d + eps);
+    if (ss_out && threadIdx.x == 0) ss_out[m] = ss;
     for (int i = threadIdx.x * 4; i < d; i += 4096) {
         const float4 v = i < 4096 ? v0 : *reinterpret_cast<const float4 *>(xr + i);
         float4 r;
@@ -138,24 +140,25 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float *x, const float *__restr
 }
 
 template <int NP>
-static void launch_rmsnorm_np(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32) {
+static void launch_rmsnorm_np(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32, int row0, float *ss_out) {
     const int d = c->cfg.d_model;
-    const size_t stride = (size_t)c->rows_max * d;
+    const size_t stride = (size_t)c->slice_rows * d;
+    float *x = c->x + (size_t)row0 * d, *y = c->y + (size_t)row0 * d;
     if (c->bf16)
-        hipLaunchKernelGGL((k_rmsnorm<bf16_t, float, NP>), dim3(rows), dim3(1024), 0, c->stream, c->x, c->y, n_partial,
-                           stride, (const bf16_t *)g, d, c->cfg.rms_eps, out, out_f32);
+        hipLaunchKernelGGL((k_rmsnorm<bf16_t, float, NP>), dim3(rows), dim3(1024), 0, c->stream, x, y, n_partial,
+                           stride, (const bf16_t *)g, d, c->cfg.rms_eps, out, out_f32, ss_out);
     else
-        hipLaunchKernelGGL((k_rmsnorm<float, float, NP>), dim3(rows), dim3(1024), 0, c->stream, c->x, c->y, n_partial,
-                           stride, (const float *)g, d, c->cfg.rms_eps, out, out_f32);
+        hipLaunchKernelGGL((k_rmsnorm<float, float, NP>), dim3(rows), dim3(1024), 0, c->stream, x, y, n_partial,
+                           stride, (const float *)g, d, c->cfg.rms_eps, out, out_f32, ss_out);
 }
 
-void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32) {
+void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32, int row0, float *ss_out) {
     ProfScope ps(c, KC_NORM);
     static_assert(MAX_SPLITS <= 16, "the widest instantiation below covers every slice count");
     // the kernel requests as many slices as its instantiation holds: the smallest one that covers n_partial
-    if (n_partial <= 4) launch_rmsnorm_np<4>(c, rows, n_partial, g, out, out_f32);
-    else if (n_partial <= 8) launch_rmsnorm_np<8>(c, rows, n_partial, g, out, out_f32);
-    else launch_rmsnorm_np<16>(c, rows, n_partial, g, out, out_f32);
+    if (n_partial <= 4) launch_rmsnorm_np<4>(c, rows, n_partial, g, out, out_f32, row0, ss_out);
+    else if (n_partial <= 8) launch_rmsnorm_np<8>(c, rows, n_partial, g, out, out_f32, row0, ss_out);
+    else launch_rmsnorm_np<16>(c, rows, n_partial, g, out, out_f32, row0, ss_out);
 }
 
 // ------------------------------------------------------------------------------------------ GEMM (fallback)
@@ -239,7 +242,7 @@ __global__ void k_rope_append(const float *__restrict__ qkv, int n_partial, size
 }
 
 void launch_rope_append(Ctx *c, const Fwd &f, int layer, int n_partial, int n_ss) {
-    const size_t pstride = (size_t)c->rows_max * c->d_qkv;
+    const size_t pstride = (size_t)c->slice_rows * c->d_qkv;
     ProfScope ps(c, KC_ROPE);
     const wisv_config &g = c->cfg;
     const size_t slot_stride = (size_t)2 * g.n_kv_heads * c->ctx_pad * g.head_dim;
@@ -401,10 +404,10 @@ void launch_argmax(Ctx *c, int rows) {
     hipLaunchKernelGGL(k_argmax_rows, dim3(rows), dim3(256), 0, c->stream, c->logits, c->cfg.vocab, c->amax);
 }
 
-// after a prefill chunk: the slot's length grows by the chunk, pred_next = greedy token of its last row
+// after a prefill chunk: the slot's length grows by the chunk; after the last one pred_next = the last row's greedy token
 __global__ void k_set_pred_next(int32_t *kv_len, int32_t *pred_next, const int32_t *amax, int slot, int row,
                                 int new_len) {
-    pred_next[slot] = amax[row];
+    if (row >= 0) pred_next[slot] = amax[row];
     kv_len[slot] = new_len;
 }
 

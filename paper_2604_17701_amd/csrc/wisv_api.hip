@@ -14,6 +14,13 @@ using namespace wisv;
 
 struct wisv_ctx : public wisv::Ctx {};
 
+// Rows of one prefill chunk: a prompt is bound by the weight stream while a chunk is short (a pass costs the same up to
+// a few dozen rows) and by the matrix cores beyond some hundred.  Measured on four layers of the 8B shape, 1999 tokens:
+// chunks of 96 rows with the generic attention kernel 82.6 ms; of 512 rows 6.08 ms, 1024 rows 5.52 ms, 2048 rows
+// 5.25 ms.  512 tokens in chunks of 4 rows 62.3 ms, in one chunk 2.15 ms.  The buffers of 1024 rows hold about 0.5 GB
+// at the 8B shape; doubling them would buy 5 %.
+constexpr int PREFILL_ROWS = 1024;
+
 namespace wisv {
 
 void *kv_ptr(const Ctx *c, int layer, int slot, int which) {
@@ -155,6 +162,9 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     c->d_kv = config->n_kv_heads * config->head_dim;
     c->d_qkv = c->d_q + 2 * c->d_kv;
     c->rows_max = config->max_batch * config->max_k;
+    c->prefill_rows = std::min(PREFILL_ROWS, c->ctx_pad);
+    c->slice_cap = std::max(MAX_SPLITS * c->rows_max, 4 * c->prefill_rows);
+    c->slice_rows = c->rows_max;
     c->profiling = false;
     c->ev_used = 0;
     c->ev_round[0] = c->ev_round[1] = nullptr;
@@ -183,6 +193,7 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     const wisv_config &g = c->cfg;
     const size_t esz = c->esz;
     const int d = g.d_model, F = g.d_ff, V = g.vocab, R = c->rows_max;
+    const int RF = std::max(R, c->prefill_rows);   // rows of a forward
     CREATE_TRY(hipSetDevice(g.device_id));
     if (!c->stream) {
         CREATE_TRY(hipStreamCreate(&c->stream));
@@ -339,7 +350,7 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
 
     // ---- staging of a round's inputs / outputs, scratch of the forward
     CREATE_TRY(dalloc(c, &c->d_stream_ids, g.max_batch));
-    CREATE_TRY(dalloc(c, &c->d_tokens, R));
+    CREATE_TRY(dalloc(c, &c->d_tokens, RF));
     CREATE_TRY(dalloc(c, &c->d_proto, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_hd_row, R));
     {
@@ -355,23 +366,23 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     CREATE_TRY(dalloc(c, &c->d_pacc, R));
     CREATE_TRY(dalloc(c, &c->d_mask, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_status, g.max_batch));
-    CREATE_TRY(dalloc(c, &c->row_slot, R));
-    CREATE_TRY(dalloc(c, &c->row_pos, R));
+    CREATE_TRY(dalloc(c, &c->row_slot, RF));
+    CREATE_TRY(dalloc(c, &c->row_pos, RF));
     CREATE_TRY(dalloc(c, &c->amax, R));
     CREATE_TRY(dalloc(c, &c->scored, R));
-    CREATE_TRY(dalloc(c, &c->x, (size_t)R * d));
-    CREATE_TRY(dalloc(c, &c->x_alt, (size_t)R * d));
-    CREATE_TRY(dalloc(c, &c->ss, (size_t)MAX_SPLITS * R));
-    CREATE_TRY(dalloc(c, &c->ss2, (size_t)((d + 15) / 16) * std::min(R, 16)));
+    CREATE_TRY(dalloc(c, &c->x, (size_t)RF * d));
+    CREATE_TRY(dalloc(c, &c->x_alt, (size_t)RF * d));
+    CREATE_TRY(dalloc(c, &c->ss, std::max((size_t)MAX_SPLITS * std::max(R, 16), (size_t)RF)));
+    CREATE_TRY(dalloc(c, &c->ss2, (size_t)((d + 15) / 16) * 16));
     c->graph_refused = false;
-    CREATE_TRY(dalloc(c, &c->y, (size_t)MAX_SPLITS * R * d));
-    CREATE_TRY(dalloc(c, &c->qkv, (size_t)MAX_SPLITS * R * c->d_qkv));
+    CREATE_TRY(dalloc(c, &c->y, (size_t)c->slice_cap * d));
+    CREATE_TRY(dalloc(c, &c->qkv, (size_t)c->slice_cap * c->d_qkv));
     {
         const size_t n_cand = ws_padded_row_blocks(V);
         CREATE_TRY(dalloc(c, &c->cand_val, (size_t)R * n_cand));
         CREATE_TRY(dalloc(c, &c->cand_idx, (size_t)R * n_cand));
     }
-    CREATE_TRY(dalloc(c, &c->gu, (size_t)R * 2 * F));
+    CREATE_TRY(dalloc(c, &c->gu, (size_t)(c->ws_ok ? std::min(RF, 16) : RF) * 2 * F));   // read by the generic kernels only
     CREATE_TRY(dalloc(c, &c->h_t, (size_t)R * d));
     CREATE_TRY(dalloc(c, &c->hu, (size_t)((g.d_head_hidden + 15) / 16) * R));   // the head's partial sums [row-block][row]
     auto act_alloc = [&](ActBuf *a, size_t n, bool half) -> hipError_t {
@@ -382,17 +393,17 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
         if (e == hipSuccess && half) e = dalloc(c, &a->h16, n);
         return e;
     };
-    CREATE_TRY(act_alloc(&c->a, (size_t)R * d, c->half_ok));
-    CREATE_TRY(act_alloc(&c->o, (size_t)R * c->d_q, c->half_ok));
-    CREATE_TRY(act_alloc(&c->h, (size_t)R * F, c->half_ok));
-    CREATE_TRY(dalloc(c, &c->q, (size_t)R * c->d_q));
+    CREATE_TRY(act_alloc(&c->a, (size_t)RF * d, c->half_ok));
+    CREATE_TRY(act_alloc(&c->o, (size_t)RF * c->d_q, c->half_ok));
+    CREATE_TRY(act_alloc(&c->h, (size_t)RF * F, c->half_ok));
+    CREATE_TRY(dalloc(c, &c->q, (size_t)RF * c->d_q));
     {
-        // split-KV attention partials: as many splits as fit 64 MiB, at most 64
+        // split-KV attention partials: as many splits of the largest round as fit 64 MiB, at most 64
         const size_t per_split = (size_t)R * c->d_q;
-        c->att_max_splits = (int)std::max<size_t>(1, std::min<size_t>(64, ((size_t)16 << 20) / per_split));
-        CREATE_TRY(dalloc(c, &c->att_o, per_split * c->att_max_splits));
-        CREATE_TRY(dalloc(c, &c->att_m, (size_t)R * g.n_heads * c->att_max_splits));
-        CREATE_TRY(dalloc(c, &c->att_l, (size_t)R * g.n_heads * c->att_max_splits));
+        c->att_cap = R * std::max<size_t>(1, std::min<size_t>(64, ((size_t)16 << 20) / per_split));
+        CREATE_TRY(dalloc(c, &c->att_o, c->att_cap * c->d_q));
+        CREATE_TRY(dalloc(c, &c->att_m, c->att_cap * g.n_heads));
+        CREATE_TRY(dalloc(c, &c->att_l, c->att_cap * g.n_heads));
     }
     CREATE_TRY(dalloc(c, &c->logits, (size_t)R * V));
     c->logits_rows = R;
@@ -430,20 +441,24 @@ constexpr int FOLD_MAX_ROWS = 4;
 static void enqueue_forward(Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
     const int d = g.d_model, F = g.d_ff;
+    c->slice_rows = f.rows;
+    // a prompt's chunk ends with its last row, and only the last chunk needs that row's greedy token
+    const int out_rows = f.prefill ? 1 : f.rows, out_row0 = f.rows - out_rows;
     launch_prep_rows(c, f);
     launch_embed(c, f);
     c->o_planes = ACT_ALL;
     if (c->ws_ok) {
         // bf16 weight-streaming path: every product leaves k-split partial slices that the next
         // kernel sums in a fixed order; gate/up and the LM head fuse SwiGLU / argmax instead
-        const size_t ys = (size_t)c->rows_max * d, qs = (size_t)c->rows_max * c->d_qkv;
+        const size_t ys = (size_t)f.rows * d, qs = (size_t)f.rows * c->d_qkv;
+        const int max_splits = std::min(MAX_SPLITS, c->slice_cap / f.rows);
         // a product whose shape the streaming kernel cannot serve falls back to the generic kernel (one slice)
         // wh: the half-precision tiles when this product class runs with one term (more than 16 rows only)
         auto half = [&](const void *wh, uint32_t cls) { return f.rows > 16 && (c->one_term_mask & cls) ? wh : nullptr; };
         // have_f: the float plane of X is current (the generic kernel reads that one)
         auto product = [&](const void *wt, const void *w, const void *wh, const ActBuf &X, float *Yp, size_t stride, int n, int kd, int kclass,
                            bool have_f = true) {
-            int ns = launch_gemm_ws_partial(c, wt, X, Yp, stride, MAX_SPLITS, f.rows, n, kd, kclass, nullptr, wh);
+            int ns = launch_gemm_ws_partial(c, wt, X, Yp, stride, max_splits, f.rows, n, kd, kclass, nullptr, wh);
             if (!ns) {
                 if (!have_f) {
                     c->launch_failed = true;
@@ -489,12 +504,19 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
             // prologue, which sums the QKV slices anyway, applies 1 / rms.  One launch less per layer.
             int nq = 0, n_ss = 0;
             if (fuse_rope && f.rows <= FOLD_MAX_ROWS) {
-                nq = n_ss = launch_gemm_ws_normfold(c, L.wqkv_t, c->x, c->x_alt, ny, L.attn_norm, c->qkv, qs, MAX_SPLITS, f.rows,
+                nq = n_ss = launch_gemm_ws_normfold(c, L.wqkv_t, c->x, c->x_alt, ny, L.attn_norm, c->qkv, qs, max_splits, f.rows,
                                                     c->d_qkv, d, c->ss, KC_GEMM_QKV);
                 if (nq) std::swap(c->x, c->x_alt);
             }
             if (!nq) {
-                launch_rmsnorm(c, f.rows, ny, L.attn_norm, act_planes(c->a, planes_for(half(L.wqkv_h, TERM_QKV))), nullptr);
+                // A prompt's chunk leaves the 1 / rms to whoever adds up the QKV slices, as the folded norm does: the
+                // first layer's x * gain, a product of two bf16 values, is then exact in two bf16 terms (512 tokens: 0.02 %
+                // of its cached values off by a step, 0.26 % when the normalised value is split, and deeper layers inherit
+                // the steps)
+                const bool defer_rms = f.prefill && !half(L.wqkv_h, TERM_QKV);
+                n_ss = defer_rms ? 1 : 0;
+                launch_rmsnorm(c, f.rows, ny, L.attn_norm, act_planes(c->a, planes_for(half(L.wqkv_h, TERM_QKV))), nullptr, 0,
+                               defer_rms ? c->ss : nullptr);
                 nq = product(L.wqkv_t, L.wqkv, half(L.wqkv_h, TERM_QKV), c->a, c->qkv, qs, c->d_qkv, d, KC_GEMM_QKV, full);
             }
             // with few k-splits and few rows the O projection combines the attention partials while it stages them
@@ -521,7 +543,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
                 if (defer && att_splits > 1) {
                     if (att_splits <= WS_PRO_SPLITS) {
                         const AttnPartials ap{c->att_o, c->att_m, c->att_l, att_splits, f.rows, g.n_heads};
-                        ny = launch_gemm_ws_partial(c, L.wo_t, c->o, c->y, ys, MAX_SPLITS, f.rows, d, c->d_q, KC_GEMM_O, &ap);
+                        ny = launch_gemm_ws_partial(c, L.wo_t, c->o, c->y, ys, max_splits, f.rows, d, c->d_q, KC_GEMM_O, &ap);
                     }
                     if (!ny) launch_attn_combine(c, f, att_splits);   // more splits than the projection takes: a kernel of its own
                 }
@@ -531,16 +553,19 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
             gate_up(L, n_ss2);
             ny = product(L.wdown_t, L.wdown, half(L.wdown_h, TERM_DOWN), c->h, c->y, ys, d, F, KC_GEMM_DOWN, h_has_f);
         }
-        launch_rmsnorm(c, f.rows, ny, c->final_norm, act_planes(c->a, planes_for(half(c->lm_head_h, TERM_LM_HEAD))), c->h_t);
-        if (!launch_gemm_ws_argmax(c, c->lm_head_t, c->a, f.keep_logits ? c->logits : nullptr, f.rows, g.vocab, d,
-                                   KC_LMHEAD, half(c->lm_head_h, TERM_LM_HEAD))) {
-            if (!full) {
+        if (f.prefill && !f.want_last) return;
+        const bool out_full = out_rows <= 16;
+        const void *lm_h = out_full ? nullptr : half(c->lm_head_h, TERM_LM_HEAD);
+        launch_rmsnorm(c, out_rows, ny, c->final_norm, out_full ? c->a : act_planes(c->a, planes_for(lm_h)), c->h_t, out_row0);
+        if (!launch_gemm_ws_argmax(c, c->lm_head_t, c->a, f.keep_logits ? c->logits : nullptr, out_rows, g.vocab, d,
+                                   KC_LMHEAD, lm_h)) {
+            if (!out_full) {
                 c->launch_failed = true;
                 c->launch_err = "the LM head fell back to the generic kernel after its input was written without the float plane";
                 return;
             }
-            launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, f.rows, g.vocab, d, KC_LMHEAD);
-            launch_argmax(c, f.rows);
+            launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, out_rows, g.vocab, d, KC_LMHEAD);
+            launch_argmax(c, out_rows);
         }
         return;
     }
@@ -556,9 +581,10 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
         launch_swiglu(c, f.rows);
         launch_gemm_ref(c, c->h.f, L.wdown, c->y, f.rows, d, F, KC_GEMM_DOWN);
     }
-    launch_rmsnorm(c, f.rows, 1, c->final_norm, c->a, c->h_t);
-    launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, f.rows, g.vocab, d, KC_LMHEAD);
-    launch_argmax(c, f.rows);
+    if (f.prefill && !f.want_last) return;
+    launch_rmsnorm(c, out_rows, 1, c->final_norm, c->a, c->h_t, out_row0);
+    launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, out_rows, g.vocab, d, KC_LMHEAD);
+    launch_argmax(c, out_rows);
 }
 
 // ------------------------------------------------------------------------------------------ verify round
@@ -1022,9 +1048,14 @@ extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tok
     if (len + n > g.max_ctx) return fail(c, WISV_ESTATE, "prefill of %d tokens at length %d exceeds max_ctx %d", n, len, g.max_ctx);
     c->pending_valid = false;   // the forward below overwrites h^T, the greedy tokens and the row map a VERIFY_ONLY call left
     HIP_TRY(c, hipMemcpyAsync(c->d_stream_ids, &stream_id, 4, hipMemcpyHostToDevice, c->stream));
-    const int chunk = c->rows_max;
-    for (int c0 = 0; c0 < n; c0 += chunk) {
-        const int rows = std::min(chunk, n - c0);
+    // Chunks of up to prefill_rows rows, as even as possible (whole 32-row tiles).  Where rounds run with one
+    // half-precision term beyond 16 rows, up to 16 tokens left over from whole blocks of rows_max keep two terms: they
+    // are a pass of their own.
+    const int rest = c->half_ok && n % c->rows_max <= 16 ? n % c->rows_max : 0, body = n - rest;
+    const int n_chunks = (body + c->prefill_rows - 1) / c->prefill_rows;
+    const int chunk = body ? std::min(c->prefill_rows, ((body + n_chunks - 1) / n_chunks + 31) / 32 * 32) : 0;
+    for (int c0 = 0, rows; c0 < n; c0 += rows) {
+        rows = c0 < body ? std::min(chunk, body - c0) : rest;
         HIP_TRY(c, hipMemcpyAsync(c->d_tokens, tokens + c0, rows * 4, hipMemcpyHostToDevice, c->stream));
         Fwd f;
         f.rows = rows;
@@ -1034,16 +1065,19 @@ extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tok
         f.tokens = c->d_tokens;
         f.keep_logits = false;
         f.max_len_ub = len + c0 + rows;
+        f.prefill = true;
+        f.want_last = c0 + rows == n;
         c->launch_failed = false;
         enqueue_forward(c, f);
-        // the slot's state moves only past chunks whose every kernel was launched
-        if (c->launch_failed) return fail(c, WISV_EUNSUPPORTED, "%s", c->launch_err.c_str());
+        if (c->launch_failed) {   // a chunk is not served: the slot is what it was before the call
+            launch_set_pred_next(c, stream_id, -1, len);
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            return fail(c, WISV_EUNSUPPORTED, "%s", c->launch_err.c_str());
+        }
         HIP_TRY(c, hipGetLastError());
-        launch_set_pred_next(c, stream_id, rows - 1, len + c0 + rows);
-        HIP_TRY(c, hipStreamSynchronize(c->stream));   // d_tokens is reused by the next chunk
-        c->h_len_ub[stream_id] = len + c0 + rows;
+        launch_set_pred_next(c, stream_id, f.want_last ? 0 : -1, len + c0 + rows);
     }
-    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipStreamSynchronize(c->stream));   // the caller's tokens have been read, the slot's state is final
     c->h_len_ub[stream_id] = len + n;
     return WISV_OK;
 }

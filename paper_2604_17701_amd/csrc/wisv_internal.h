@@ -126,6 +126,9 @@ struct Ctx {
     bool bf16;
     size_t esz;          // bytes per weight / cache element
     int d_q, d_kv, d_qkv, rows_max;
+    int prefill_rows;    // rows of one prefill chunk (>= 1): the forward's buffers hold max(rows_max, prefill_rows)
+    int slice_cap;       // k-split slices x rows that y and qkv hold
+    int slice_rows;      // rows of one slice in the forward being enqueued (== its row count)
 
     // parameters (private copies)
     void *embed, *lm_head, *final_norm, *lm_head_t, *lm_head_h;
@@ -160,10 +163,10 @@ struct Ctx {
 
     // scratch
     int32_t *row_slot, *row_pos, *amax, *scored;
-    float *x, *y, *qkv, *gu, *h_t, *logits;   // y and qkv hold up to MAX_SPLITS partial slices
+    float *x, *y, *qkv, *gu, *h_t, *logits;   // y and qkv hold slice_cap rows of partial slices
     float *x_alt;                 // second residual-stream buffer: a product that folds the norm in reads x and writes here
-    float *ss;                    // [MAX_SPLITS][rows_max] sums of squares left by such a product
-    float *ss2;                   // [d_model / 16][min(rows_max, 16)]: those of the O projection that folds the FFN norm in
+    float *ss;                    // [MAX_SPLITS][max(rows_max, 16)], or one per row of a prompt's chunk: sums of squares left by such a product
+    float *ss2;                   // [d_model / 16][16]: those of the O projection that folds the FFN norm in
     bool graph_refused;           // a capture of the round failed once: later rounds run eagerly without trying again
     float *cand_val;
     int32_t *cand_idx;
@@ -172,8 +175,8 @@ struct Ctx {
     int o_planes;                 // ACT_*: the representations of o that this round's attention kernels write
     float *hu;                    // decision head: second-layer partial sums [row-block of hidden units][row]
     float *att_o, *att_m, *att_l; // split-KV attention partials: [split][rows][heads][head_dim], [split][rows][heads]
-    int att_max_splits;
     size_t logits_rows;
+    size_t att_cap;               // query rows of width d_q that att_o holds
     void *ss_ws;                  // speculative-sampling scratch: chunk statistics, normalisers, chunk weights
     float *d_ss_q, *d_ss_u, *d_ss_v;   // its host-mode input staging (d_ss_q is allocated by the first call that needs it)
 
@@ -206,6 +209,8 @@ struct Fwd {
     const int32_t *tokens;       // device [rows]
     bool keep_logits;
     int max_len_ub;              // upper bound of kv_len + k over the streams of this forward
+    bool prefill = false;        // a chunk of a prompt (batch 1): only its last row's greedy token matters, ...
+    bool want_last = false;      // ... and that only in the last chunk; it is left in c->amax[0]
 };
 
 // ---------------------------------------------------------------- kernel launchers (kernels_ref.hip)
@@ -213,7 +218,10 @@ void launch_prep_rows(Ctx *c, const Fwd &f);
 void launch_embed(Ctx *c, const Fwd &f);
 void launch_v_reblock(Ctx *c, void *rows, void *plane, int len, bool to_plane);
 // x += sum of n_partial slices of y (if n_partial > 0); out = RMSNorm(x) * g; optional second float copy
-void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32);
+// row0: the first row of x and y that is normalised (its result is row 0 of the outputs)
+// ss_out != null: out = x * g without the 1 / rms, whose sum of squares goes to ss_out[row] for a later kernel to apply
+void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32, int row0 = 0,
+                    float *ss_out = nullptr);
 // Y[rows, n] = A[rows, kd] * W[n, kd]^T (float accumulate, float out)
 void launch_gemm_ref(Ctx *c, const float *A, const void *W, float *Y, int rows, int n, int kd, int kclass);
 // n_ss > 0: the slices are scaled by 1 / rms from the n_ss partial sums of squares in c->ss (folded RMSNorm)
@@ -221,6 +229,7 @@ void launch_rope_append(Ctx *c, const Fwd &f, int layer, int n_partial, int n_ss
 void launch_attn_ref(Ctx *c, const Fwd &f, int layer);
 void launch_swiglu(Ctx *c, int rows);
 void launch_argmax(Ctx *c, int rows);
+// kv_len[slot] = new_len; pred_next[slot] = amax[row] unless row is negative
 void launch_set_pred_next(Ctx *c, int slot, int row, int new_len);
 
 // ---------------------------------------------------------------- decision head + scan (kernels_head.hip)

@@ -545,3 +545,47 @@ def test_mixed_context_lengths_in_one_round(lengths, k):
         compare_stream(g, b, o, k, 0.5, tol, stats, logits[rows])
     record(base.name, stats)
     ctx.wisv_destroy()
+
+
+@pytest.mark.parametrize("model,batch,k,lens", [
+    (MID128, 1, 4, (15, 16, 17, 31, 33, 64, 65, 130)),       # two bf16 terms; 16-row blocks of query tokens, short last one
+    (MID128, 1, 1, (3, 20)),                                 # more rows in a prompt's chunk than the largest round has
+    (MID128, 6, 4, (24, 40, 97, 1061)),                      # rounds beyond 16 rows exist: a leftover of 1, 16, 1, 5 tokens
+    (replace(MID128, n_heads=12, n_kv_heads=4), 1, 4, (21, 43, 150)),   # three query heads per KV head: blocks of 21 tokens
+    (MID, 2, 3, (40, 77)),                                   # head size 64: the generic attention kernel
+    (W0.model, 1, 4, (5, 33, 100)),                          # fp32
+])
+def test_prefill_chunks_agree_with_small_steps(model, batch, k, lens):
+    """A prompt is ingested in chunks of many rows; the same tokens given a few per call (one pass of at most k rows
+    each) must leave the same cache, length and greedy token.  Both paths take activations as two bf16 terms (all
+    precision classes cleared), so cached values differ by at most a bf16 step where float sums straddle a rounding
+    boundary, inherited by deeper layers: the bound is one step of the plane's largest entry (2^-7 of it), and 32-bit
+    sums of a few thousand terms for fp32.  A second prompt behind the first covers a chunk that starts in mid-cache."""
+    dev = torch.device("cuda:0")
+    wd = gen.make_weights(model, 5, dev)
+    n_all = max(lens) + 37
+    toks = gen.randint(7, "prompt", (n_all,), model.vocab).numpy().astype(np.int32)
+    f32 = model.dtype == "f32"
+    ctx = binding.Context(model, wd, batch, n_all + k, k)
+    if ctx.wisv_get_option(binding.WISV_OPT_ONE_TERM_CLASSES):
+        ctx.wisv_set_option(binding.WISV_OPT_ONE_TERM_CLASSES, 0)
+    step = min(k, 4)
+    for n in lens:
+        got = []
+        for pieces in ([n, 37], [step] * (n // step) + ([n % step] if n % step else []) + [step] * (37 // step) + ([37 % step] if 37 % step else [])):
+            ctx.wisv_set_state(0, 0, 0)
+            at = 0
+            for p in pieces:
+                ctx.wisv_prefill(0, toks[at:at + p])
+                at += p
+            assert at == n + 37
+            got.append((ctx.wisv_get_state(0), [ctx.wisv_kv_export(0, l, n + 37) for l in range(model.n_layers)]))
+        assert got[0][0] == got[1][0] and got[0][0][0] == n + 37
+        for l in range(model.n_layers):
+            for a, b in zip(got[0][1][l], got[1][1][l]):
+                a, b = a.float(), b.float()
+                top = float(b.abs().max())
+                assert float((a - b).abs().max()) <= (2e-5 if f32 else 2.0 ** -7) * top, (n, l)
+                if l == 0 and not f32:
+                    assert float((a == b).float().mean()) > 0.99
+    ctx.wisv_destroy()
