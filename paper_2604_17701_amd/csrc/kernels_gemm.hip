@@ -505,7 +505,7 @@ __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_
 }
 
 // ------------------------------------------------------------------------------------------ many rows
-// The compute-bound regime (tens to hundreds of rows) uses the 32x32x16 MFMA, which sustains about 1.5 times
+// The compute-bound regime (hundreds of rows) uses the 32x32x16 MFMA, which sustains about 1.5 times
 // the rate of the 16x16x32 one and needs half the B-operand bytes per flop.  Its A operand wants lane l to
 // hold row l % 32 and the 8 k-values of slot l / 32.  Two vertically adjacent re-tiled row-blocks (lane l:
 // row l % 16, k-group l / 16 of a 32-wide k-tile) hold two such operands - 32 weight rows with k-groups (0, 2)
@@ -514,8 +514,8 @@ __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_
 // 32-row tile t holds, at lane l, X[32 t + l % 32][32 kt + 8 op + 16 (l / 32) ..+8] - a wave stores and later
 // reads a contiguous KiB.
 //
-// Eight waves, two per SIMD (a lone wave issues in order and leaves the matrix pipe idle while it issues
-// anything else): WN x WM of them, a wave owns RP pairs of row-blocks of W, streamed straight into a ring of U
+// More than 160 rows.  Eight waves, two per SIMD (a lone wave issues in order and leaves the matrix pipe idle while it
+// issues anything else): WN x WM of them, a wave owns RP pairs of row-blocks of W, streamed straight into a ring of U
 // register slots as above, and meets 32 NT rows of the workgroup's row tile.  Staging is double-buffered in chunks of KC k-tiles: the loads of chunk ch + 1 are
 // issued before the MFMAs of chunk ch and written to LDS after them.  The 1-D grid is decoded so that the row
 // tiles sharing a slice of W run on the same XCD at the same time (workgroup ids are dealt round-robin to the
@@ -523,9 +523,10 @@ __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 // acc[p][t][e] = Y[m = m_base + 32 t + lane % 32][row 8 (e / 4) + 4 (lane / 32) + e % 4 of the 32 rows that
 // row-blocks rb0 + 2 p and rb0 + 2 p + 1 make]
+// rb_end: row-blocks from here on belong to another workgroup (SwiGLU only)
 template <int NT, int RP, int EPI>
 __device__ __forceinline__ void mm_epilogue(const GemmArgs &g, floatx16 (&acc)[RP][NT], int m_base, int rb0, int split,
-                                            int slot, int lane) {
+                                            int slot, int lane, int rb_end = 0x7fffffff) {
     const int mj = lane & 31, h = lane >> 5;
     if (EPI == EPI_PARTIAL) {
         float *out = g.Yp + (size_t)split * g.split_stride;
@@ -556,6 +557,7 @@ __device__ __forceinline__ void mm_epilogue(const GemmArgs &g, floatx16 (&acc)[R
             for (int p = 0; p < RP; ++p)
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
+                    if (rb0 + 2 * p + b >= rb_end) continue;
                     const int f = (rb0 + 2 * p + b) * 8 + 4 * h;
                     float hv[4];
 #pragma unroll
@@ -597,9 +599,8 @@ __device__ __forceinline__ void mm_epilogue(const GemmArgs &g, floatx16 (&acc)[R
     }
 }
 
-// NT: 32-row tiles per wave; NW waves: WM along the rows, WK along k (each takes KC / WK of a chunk's k-tiles and
-// the WK partial results are added through LDS at the end, in order), NW / (WM WK) along the row-blocks; RP: pairs
-// of row-blocks per wave; KC: k-tiles per LDS chunk; U: register slots of a wave's weight stream
+// NT: 32-row tiles per wave; NW waves: WM along the rows, NW / WM along the row-blocks; RP: pairs of row-blocks per
+// wave; KC: k-tiles per LDS chunk; U: register slots of a wave's weight stream
 // NPL: 2 = activations as two bf16 terms (planes hi and lo, two MFMAs per operand pair); 1 = one half-precision term
 // (plane X16 against half-precision weight tiles, one MFMA per pair: half the matrix-core work and half the staging)
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -607,20 +608,17 @@ template <int NPL> __device__ __forceinline__ floatx16 mm_mfma(const u32x4 &a, c
     if (NPL == 2) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&a), *reinterpret_cast<const bf16x8 *>(&b), c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const f16x8 *>(&a), *reinterpret_cast<const f16x8 *>(&b), c, 0, 0, 0);
 }
-template <int NT, int WM, int NW, int WK, int RP, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false>
+template <int NT, int WM, int NW, int RP, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
     extern __shared__ __align__(16) unsigned char lds[];
-    static_assert(KC % WK == 0, "every k-slice takes the same number of k-tiles of a chunk");
-    constexpr int KW = KC / WK;                           // k-tiles of a chunk one wave multiplies
-    static_assert(U % KW == 0, "a turn of the ring is a whole number of chunks");
-    constexpr int WN = NW / (WM * WK), RB = 2 * RP;
+    static_assert(U % KC == 0, "a turn of the ring is a whole number of chunks");
+    constexpr int WN = NW / WM, RB = 2 * RP;
     constexpr int NTW = NT * WM;                          // 32-row tiles of the workgroup
     constexpr int OPS = KC * NTW * 2;                     // B operands of one plane in a chunk
     constexpr int PER_WAVE = (NPL * OPS + NW - 1) / NW;   // operand loads a wave issues per chunk (all planes)
     constexpr int BUF = NPL * OPS * 1024;                 // bytes of one chunk buffer
     constexpr int G = 2 * NPL;                            // operand groups (op, plane) of a k-tile
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wn = wave / (WM * WK), wm = wave % WM;
-    const int wk = WK == 1 ? 0 : __builtin_amdgcn_readfirstlane((wave / WM) % WK);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wn = wave / WM, wm = wave % WM;
     // ---- which (row-block group bx, k-split by, row tile z)
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int z = slot % g.gz, q = (slot / g.gz) * 8 + xcd;
@@ -646,7 +644,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
         for (int p = 0; p < RP; ++p)
 #pragma unroll
             for (int op = 0; op < 2; ++op)   // a slot past the last k-tile re-reads that tile and is never used
-                abuf[u][p][op] = wp[p * wstep + (size_t)min((u / KW) * KC + wk * KW + u % KW, ntile - 1) * 64 + 16 * op];
+                abuf[u][p][op] = wp[p * wstep + (size_t)min(u, ntile - 1) * 64 + 16 * op];
 
     floatx16 acc[RP][NT];
 #pragma unroll
@@ -663,7 +661,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
     static_assert((NPL * OPS) % NW == 0, "every wave stages the same number of operands");
     const int srow = m_base + (lane & 31);
     const int scol = (lane >> 5) * 16;
-    constexpr int TURN = U / KW;   // chunks per turn of the ring
+    constexpr int TURN = U / KC;   // chunks per turn of the ring
     constexpr int SD = DEEP ? TURN : 1;   // chunks of activations in flight
     u32x4 sreg[SD][PER_WAVE];
 #define WISV_MM_STAGE_LOAD(ch, S)                                                                                   \
@@ -708,19 +706,18 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
         const unsigned char *buf = lds + (size_t)((ch) & 1) * BUF + (size_t)(wm * NT) * 2048 + lane * 16;          \
         const int kbase = (ch) * KC;                                                                               \
         if (!DEEP) { WISV_MM_STAGE_LOAD((ch) + 1, 0) }                                                             \
-        _Pragma("unroll") for (int lw = 0; lw < KW; ++lw) {                                                        \
-            const int lt = wk * KW + lw; /* this wave's k-tile of the chunk */                                    \
+        _Pragma("unroll") for (int lt = 0; lt < KC; ++lt) {                                                        \
             if (kbase + lt < ntile) { /* uniform per wave; no load inside, so the load counts hold on every path */ \
-                if (!WEAVE || lw == 0) {                                                                           \
+                if (!WEAVE || lt == 0) {                                                                           \
                     WISV_MM_READ_B(lt, 0, bv[0])                                                                   \
                     if (WEAVE) __builtin_amdgcn_sched_barrier(0);                                                  \
                 }                                                                                                  \
                 _Pragma("unroll") for (int og = 0; og < G; ++og) {                                                 \
                     if (og < G - 1) { WISV_MM_READ_B(lt, og + 1, bv[(og + 1) & 1]) }                               \
-                    else if (WEAVE && lw + 1 < KW) { WISV_MM_READ_B(lt + 1, 0, bv[0]) }                            \
+                    else if (WEAVE && lt + 1 < KC) { WISV_MM_READ_B(lt + 1, 0, bv[0]) }                            \
                     if (!WEAVE) __builtin_amdgcn_sched_barrier(0);                                                 \
-                    WISV_MM_GROUP(og, abuf[(CC) * KW + lw], bv[og & 1])                                            \
-                    if (WEAVE && (og < G - 1 || lw + 1 < KW)) {                                                    \
+                    WISV_MM_GROUP(og, abuf[(CC) * KC + lt], bv[og & 1])                                            \
+                    if (WEAVE && (og < G - 1 || lt + 1 < KC)) {                                                    \
                         /* one LDS read of the next group after every RP matrix instructions of this one */       \
                         _Pragma("unroll") for (int t = 0; t < NT; ++t) {                                           \
                             __builtin_amdgcn_sched_group_barrier(0x008, RP, 0);                                    \
@@ -732,7 +729,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
             }                                                                                                      \
             /* refill the slot right after its use; past the end the last tile is re-read into a slot nobody uses */ \
             _Pragma("unroll") for (int p = 0; p < RP; ++p) _Pragma("unroll") for (int op = 0; op < 2; ++op)        \
-                abuf[(CC) * KW + lw][p][op] = wp[p * wstep + (size_t)min(kbase + lt + TURN * KC, ntile - 1) * 64 + 16 * op]; \
+                abuf[(CC) * KC + lt][p][op] = wp[p * wstep + (size_t)min(kbase + lt + TURN * KC, ntile - 1) * 64 + 16 * op]; \
             __builtin_amdgcn_sched_barrier(0);                                                                     \
         }                                                                                                          \
         WISV_MM_STAGE_STORE((ch) + 1, DEEP ? ((CC) + 1) % TURN : 0)                                                \
@@ -762,40 +759,263 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 #undef WISV_MM_STAGE_STORE
 #undef WISV_MM_READ_B
 #undef WISV_MM_GROUP
-    if (WK > 1) {
-        // the k-slices of a tile are added in slice order through LDS (the staging buffers are free after a barrier)
-        floatx4 *red = reinterpret_cast<floatx4 *>(lds);   // [WN WM][RP][NT][4][64]
-        const int grp = wn * WM + wm;
-        for (int sl = 1; sl < WK; ++sl) {
-            __syncthreads();
-            if (wk == sl) {
-#pragma unroll
-                for (int p = 0; p < RP; ++p)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            red[((((size_t)grp * RP + p) * NT + t) * 4 + e) * 64 + lane] =
-                                floatx4{acc[p][t][4 * e], acc[p][t][4 * e + 1], acc[p][t][4 * e + 2], acc[p][t][4 * e + 3]};
-            }
-            __syncthreads();
-            if (wk == 0) {
-#pragma unroll
-                for (int p = 0; p < RP; ++p)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const floatx4 v = red[((((size_t)grp * RP + p) * NT + t) * 4 + e) * 64 + lane];
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) acc[p][t][4 * e + c] += v[c];
-                        }
-            }
-        }
-        if (wk != 0) return;
-    }
     if (!active) return;
     mm_epilogue<NT, RP, EPI>(g, acc, m_base + wm * (32 * NT), rb0, by, bx * WN + wn, lane);
+}
+
+// ------------------------------------------------------------------------------------------ tens of rows
+// One row tile (17 to 160 rows) against the whole weight stream.  Weights and activations both go to LDS by direct loads
+// (global_load_lds, 1 KiB per wave instruction, no registers) through a ring of NS stages of KC k-tiles.  A stage is
+// waited for by count (loads complete in order) by the waves that loaded it, and one barrier per stage makes it visible
+// and frees the buffer of the stage before.  The loads are inline assembly without outputs: the compiler orders every
+// LDS read after every such load it knows of, which would drain the ring at each stage; the waits below are the only
+// ones.
+//
+// Four of the eight waves multiply, the other four only issue loads, two of them the weights and two the activations:
+// issuing one takes tens of cycles, which a multiplying wave loses on the matrix pipe.
+//
+// The order of the sums is that of k_gemm_mm and of the k-slice workgroups this kernel replaced, bit for bit (a token
+// of a near-tie, once turned, stays turned).  CH == 1: every output is one chain of products over the workgroup's
+// k-tiles, a wave multiplies 32 weight rows by every row tile.  CH == 4 (at most 64 rows): four chains, k-tile i in
+// chain i % 4, added as ((0 + 1) + 2) + 3; the waves are 2 x 2, 64 weight rows (wn) and one k-tile of every stage (wk)
+// each, a wave's stages alternate between its two chains, and at the end it hands one of its two row-block pairs to its
+// partner and finishes the other.
+//
+// What bounds it: bytes into a CU.  Weights and activations together arrive at about 41 GB/s per CU whatever the depth
+// of the ring (3, 4 and 5 stages the same +- 1 %, 2 stages 30 % slower) and whether or not anything is multiplied (in
+// a first form, 143 rows, gate/up of the 8B shape: 56 us, 54 without the matrix instructions, 47 with the weights
+// alone), so beyond 32 rows, where weights alone (6.2 TB/s over 256 CUs) stop being the limit, time grows with the
+// activations every workgroup re-reads from L2.  Against the workgroups it replaced, us per launch at the 8B shape, 32 /
+// 96 / 143 rows: gate/up 49.0 / 61.8 / 76.3 -> 38.0 / 42.8 / 49.2, down 23.6 / 33.3 -> 19.8 / 23.1 (143 rows: k_gemm_mm),
+// QKV (two terms) 14.1 / 20.4 / 27.3 -> 10.3 / 18.4 / 23.1, O (two terms) 10.9 / 14.8 / 20.4 -> 8.3 / 12.4 / 16.8, LM head of
+// 32000 tokens 53.3 / 70.0 / 82.8 -> 45.4 / 49.4 / 55.1, of 128256 tokens over 28 rows 207 -> 188.
+
+// a wave-uniform pointer, in scalar registers
+__device__ __forceinline__ const unsigned char *scalar_ptr(const void *p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (const unsigned char *)(((uint64_t)hi << 32) | lo);
+}
+// lane l: 16 bytes from base + voff to lds_addr + 16 l
+__device__ __forceinline__ void lds_load_1k(uint32_t lds_addr, uint32_t voff, const void *base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory");
+}
+__device__ __forceinline__ void lds_load_1k_nt(uint32_t lds_addr, uint32_t voff, const void *base) {   // read once: streamed
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory");
+}
+// at most `left` stages of N loads each may still be on their way; then meet the other waves
+template <int N, int NS> __device__ __forceinline__ void pipe_wait(int left) {
+    static_assert(NS >= 2 && N * (NS - 2) <= 63, "vmcnt holds six bits");
+    if (NS > 2 && left >= NS - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 2 ? N * (NS - 2) : 0) : "memory");
+    else if (NS > 5 && left >= 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 5 ? 3 * N : 0) : "memory");
+    else if (NS > 4 && left == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 4 ? 2 * N : 0) : "memory");
+    else if (NS > 3 && left == 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 3 ? N : 0) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// RBW: row-blocks of weights per workgroup, 8 or 7 (with 7 the last pair's second half is another workgroup's: its
+// products are of whatever the ring holds there and are not written)
+template <int NT, int KC, int NS, int RBW, int CH, int EPI, int NPL>
+__global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    static_assert(CH == 1 || (CH == 4 && KC == 2 && NT <= 2), "four chains: a k-tile per wave half and stage");
+    constexpr int WB = RBW * KC, AB = NPL * KC * NT * 2;  // 1 KiB loads of weights / activations in a stage
+    constexpr int NW = WB / 2, NA = AB / 2;               // per loading wave
+    static_assert(WB % 2 == 0 && AB % 2 == 0, "the two waves of a kind issue the same number of loads");
+    constexpr int WSLOT = 8 * KC, STAGE = (WSLOT + AB) * 1024;
+    const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    // (quotients come out of vector registers: made scalar here, so that every address below is)
+    const int zq = __builtin_amdgcn_readfirstlane(slot / g.gz), z = slot - zq * g.gz, q = zq * 8 + xcd;
+    if (q >= g.gx * g.gs) return;                         // the whole workgroup leaves: no barrier is reached
+    const int by = __builtin_amdgcn_readfirstlane(q / g.gx), bx = q - by * g.gx;
+    const int kt0 = by * g.kt_per_split, ntile = min(g.kt_per_split, g.nkt - kt0);
+    const int m_base = z * (32 * NT);
+    const int nst = (ntile + KC - 1) / KC;                // every wave passes nst barriers (CH == 4: and two more)
+
+    if (wave8 >= 4) {
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+        const int half = wave & 1;
+        if (wave < 2) {
+            // ---- weights: NW tiles of a stage (tile i = half NW + j: row-block i / KC, k-tile i % KC)
+            const unsigned char *base = scalar_ptr(g.Wt + ((size_t)bx * RBW * g.nkt + kt0) * 64);
+            const int rb_last = g.nrb - 1 - bx * RBW;         // row-blocks past the last re-read it (RBW == 7)
+            auto issue = [&](int st) {
+                const uint32_t buf = lds0 + (uint32_t)(st % NS) * STAGE;
+#pragma unroll
+                for (int j = 0; j < NW; ++j) {
+                    const int i = half * NW + j, rb = min(i / KC, rb_last), kt = min(st * KC + i % KC, ntile - 1);
+                    lds_load_1k_nt(buf + i * 1024, lane * 16 + (uint32_t)(rb * g.nkt + kt) * 1024u, base);
+                }
+            };
+            for (int st = 0; st < min(NS - 1, nst); ++st) issue(st);
+            for (int st = 0; st < nst; ++st) {
+                pipe_wait<NW, NS>(min(NS - 2, nst - 1 - st));
+                if (st + NS - 1 < nst) issue(st + NS - 1);    // into the buffer of stage st - 1, which nobody reads any more
+            }
+        } else {
+            // ---- activations: NA KiB of a stage (two planes: one wave each), 8 rows x 64 columns or 16 rows x 32 per load,
+            //      so that a row contributes whole 128- or 64-byte runs.  LDS keeps rows of KC * 64 bytes whose 16-byte
+            //      pieces are permuted (piece c of row r sits at c ^ swz(r)): the operand reads then spread over the banks.
+            constexpr int PCS = KC * 4, RPL = 64 / PCS;       // pieces per row, rows per load
+            const unsigned char *base = scalar_ptr((const unsigned char *)(NPL == 1 ? g.X16 : half ? g.Xlo : g.Xhi) + (size_t)kt0 * 64);
+            const int piece = (lane % PCS) ^ (KC == 2 ? lane / 8 : (lane / 16) & 3);
+            const uint32_t last_odd = piece >= 4 ? 64u : 0u;  // of a last stage with one k-tile: the missing tile re-reads the present one
+            uint32_t avo[NA];
+#pragma unroll
+            for (int j = 0; j < NA; ++j) {
+                const int r = (half * NA + j) % (NT * 32 / RPL) * RPL + lane / PCS;
+                // rows past M re-read row M - 1; their results are not written
+                avo[j] = (uint32_t)min(m_base + r, g.M - 1) * (uint32_t)g.kd * 2u + (uint32_t)(piece * 16);
+            }
+            auto issue = [&](int st) {
+                const uint32_t buf = lds0 + (uint32_t)(st % NS) * STAGE + (WSLOT + half * NA) * 1024, k = (uint32_t)st * (KC * 64u);
+#pragma unroll
+                for (int j = 0; j < NA; ++j) lds_load_1k(buf + j * 1024, avo[j] + (KC == 2 && st * 2 + 1 >= ntile ? k - last_odd : k), base);
+            };
+            for (int st = 0; st < min(NS - 1, nst); ++st) issue(st);
+            for (int st = 0; st < nst; ++st) {
+                pipe_wait<NA, NS>(min(NS - 2, nst - 1 - st));
+                if (st + NS - 1 < nst) issue(st + NS - 1);
+            }
+        }
+        if (CH == 4) asm volatile("s_barrier\n\ts_barrier" ::: "memory");   // the two of the chains' sum below
+        return;
+    }
+
+    // ---- the multiplying waves
+    constexpr int P = CH == 4 ? 2 : 1, SETS = CH == 4 ? 2 : 1, UN = CH == 4 ? 2 : 2 * KC;   // pairs, chains, operands of a stage
+    const int wn = CH == 4 ? wave >> 1 : wave, wk = CH == 4 ? wave & 1 : 0;
+    floatx16 acc[SETS][P][NT];
+#pragma unroll
+    for (int c = 0; c < SETS; ++c)
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[c][p][t][e] = 0.f;
+    // operand `op` of pair p: lane l wants row l % 32 of the pair and k-group 2 (l / 32) + op (as in k_gemm_mm)
+    const unsigned char *ap = lds + (wn * 2 * P + ((lane & 31) >> 4)) * KC * 1024 + (32 * (lane >> 5) + (lane & 15)) * 16;
+    const unsigned char *bp = lds + WSLOT * 1024 + (lane & 31) * (KC * 64);
+    const int swz = KC == 2 ? lane & 7 : (lane >> 2) & 3;
+    struct Ops { u32x4 a[UN][P], b[UN][NPL][NT]; };
+    // Where the registers allow it (AHEAD) a stage's operands are read while the products of the stage before run; else
+    // those products must not sink below the reads
+    constexpr bool AHEAD = 16 * SETS * P * NT + 8 * UN * (P + NPL * NT) <= 200;
+    auto fetch = [&](int st, Ops &o) {
+        if (!AHEAD) __builtin_amdgcn_sched_barrier(0);
+        // this wave's reads of the stage before are done (its buffer is overwritten after the barrier); stage st is there
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const unsigned char *as = ap + (size_t)(st % NS) * STAGE, *bs = bp + (size_t)(st % NS) * STAGE;
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int kt = CH == 4 ? wk : u >> 1, op = u & 1;
+#pragma unroll
+            for (int p = 0; p < P; ++p) o.a[u][p] = *reinterpret_cast<const u32x4 *>(as + (p * 2 * KC + kt) * 1024 + op * 256);
+#pragma unroll
+            for (int pl = 0; pl < NPL; ++pl)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    o.b[u][pl][t] = *reinterpret_cast<const u32x4 *>(bs + (pl * NT + t) * (KC * 2048) + ((kt * 4 + op + 2 * (lane >> 5)) ^ swz) * 16);
+        }
+    };
+    auto multiply = [&](const Ops &o, floatx16 (&ac)[P][NT], int u0, int u1) {   // compile-time numbers once inlined
+#pragma unroll
+        for (int u = u0; u < u1; ++u)
+#pragma unroll
+            for (int pl = 0; pl < NPL; ++pl)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) ac[p][t] = mm_mfma<NPL>(o.a[u][p], o.b[u][pl][t], ac[p][t]);
+    };
+    // No branch around the products in the loops: a merge would move every accumulator between register files.
+    const bool odd = KC == 2 && (ntile & 1);              // the last stage holds one k-tile
+    auto last = [&](const Ops &o, floatx16 (&ac)[P][NT]) {
+        if (CH == 4) {
+            if (!odd || wk == 0) multiply(o, ac, 0, UN);
+        } else {
+            multiply(o, ac, 0, 2);
+            if (KC == 2 && !odd) multiply(o, ac, 2, UN);
+        }
+    };
+    Ops o0, o1;
+    int st = 0;
+    if (AHEAD) {
+        fetch(0, o0);
+        for (; st + 2 < nst; st += 2) {
+            fetch(st + 1, o1);
+            multiply(o0, acc[0], 0, UN);
+            fetch(st + 2, o0);
+            multiply(o1, acc[SETS - 1], 0, UN);
+        }
+        if (st + 1 < nst) {
+            fetch(st + 1, o1);
+            multiply(o0, acc[0], 0, UN);
+            last(o1, acc[SETS - 1]);
+        } else {
+            last(o0, acc[0]);
+        }
+    } else if (CH == 1) {
+        for (; st + 1 < nst; ++st) {
+            fetch(st, o0);
+            multiply(o0, acc[0], 0, UN);
+        }
+        fetch(st, o0);
+        last(o0, acc[0]);
+    } else {
+        for (; st + 2 < nst; st += 2) {
+            fetch(st, o0);
+            multiply(o0, acc[0], 0, UN);
+            fetch(st + 1, o0);
+            multiply(o0, acc[SETS - 1], 0, UN);
+        }
+        fetch(st, o0);
+        if (st + 1 < nst) {
+            multiply(o0, acc[0], 0, UN);
+            fetch(st + 1, o0);
+            last(o0, acc[SETS - 1]);
+        } else {
+            last(o0, acc[0]);
+        }
+    }
+
+    const int rb0 = bx * RBW + wn * 2 * P + wk * 2, rb_end = min(g.nrb, (bx + 1) * RBW);
+    if constexpr (CH == 4) {
+        // wave (wn, wk) holds chains wk and 2 + wk; it hands pair 1 - wk to its partner and finishes pair wk
+        floatx4 *red = reinterpret_cast<floatx4 *>(lds);   // [wave][chain][NT][4][64]
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every read of the last stages is done
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    floatx4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = wk ? acc[c][0][t][4 * e + i] : acc[c][1][t][4 * e + i];
+                    red[(((wave * 2 + c) * NT + t) * 4 + e) * 64 + lane] = v;
+                }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        floatx16 out[1][NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const floatx4 p0 = red[((((wave ^ 1) * 2 + 0) * NT + t) * 4 + e) * 64 + lane];
+                const floatx4 p1 = red[((((wave ^ 1) * 2 + 1) * NT + t) * 4 + e) * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float m0 = wk ? acc[0][1][t][4 * e + i] : acc[0][0][t][4 * e + i];
+                    const float m1 = wk ? acc[1][1][t][4 * e + i] : acc[1][0][t][4 * e + i];
+                    out[0][t][4 * e + i] = wk ? ((p0[i] + m0) + p1[i]) + m1 : ((m0 + p0[i]) + m1) + p1[i];
+                }
+            }
+        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, out, m_base, rb0, by, rb0 >> 1, lane, rb_end);
+    } else {
+        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], m_base, rb0, by, rb0 >> 1, lane, rb_end);
+    }
 }
 
 // final argmax over the per-group candidates of every row
@@ -874,42 +1094,68 @@ static bool launch_ws_t(Ctx *c, GemmArgs &g, int splits, size_t soft_budget) {
 constexpr int MM_RP = 2;            // pairs of row-blocks per wave of k_gemm_mm
 constexpr int MM_RB = 2 * MM_RP;
 
-template <int NT, int WM, int NW, int WK, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false>
+template <int NT, int WM, int NW, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false>
 static bool launch_mm_t(Ctx *c, GemmArgs &g, int splits) {
-    constexpr int WN = NW / (WM * WK), NTW = NT * WM;
+    constexpr int WN = NW / WM, NTW = NT * WM;
     g.gx = (g.nrb + WN * MM_RB - 1) / (WN * MM_RB);
     g.gz = (g.M + 32 * NTW - 1) / (32 * NTW);
     g.gs = splits;
-    // two buffers, two planes, 2 operands per (k-tile, row tile); or the k-slice reduction: one accumulator set per tile group
-    const size_t lds = std::max((size_t)2 * NPL * KC * NTW * 2 * 1024, WK > 1 ? (size_t)WN * WM * MM_RP * NT * 4096 : (size_t)0);
+    const size_t lds = (size_t)2 * NPL * KC * NTW * 2 * 1024;   // two buffers, NPL planes, 2 operands per (k-tile, row tile)
     static bool allowed[MAX_DEVICES];     // per instantiation
     if (lds > 64 * 1024 &&
-        !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_mm<NT, WM, NW, WK, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE>), allowed))
+        !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_mm<NT, WM, NW, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE>), allowed))
         return false;
     const unsigned grid = (unsigned)((g.gx * g.gs + 7) / 8 * 8 * g.gz);
-    hipLaunchKernelGGL((k_gemm_mm<NT, WM, NW, WK, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE>), dim3(grid), dim3(64 * NW), lds, c->stream, g);
+    hipLaunchKernelGGL((k_gemm_mm<NT, WM, NW, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE>), dim3(grid), dim3(64 * NW), lds, c->stream, g);
     return true;
 }
 
-// Workgroup shapes of k_gemm_mm.  Up to 64 rows: one row tile met by all eight waves (each 64 weight rows).
-// Beyond: tiles of 128 rows, met by 4 x 2 waves (256 weight rows per workgroup, every weight tile loaded by two
-// waves), or - "wide" - by 8 x 1 waves with four row tiles each (512 weight rows, half the L2 traffic per flop,
-// but half as many workgroups), or - "narrow" - by 2 x 2 waves (128 weight rows; two workgroups share a CU).
-// With k-splits wide pays when it still fills the chip (>= 200 workgroups) and a split keeps >= 24 k-tiles; without
-// them the shape with the fewest rounds of workgroups, weighted by what a round of that shape costs, is taken.
-// A product without k-splits over at most 64 rows and few row-blocks (gate/up) would fill a quarter of the chip
-// that way: "k-slice" workgroups cover 128 weight rows only and their waves split each chunk's k-tiles among them
-// (98.9 -> 50.5 us at 32 rows, 116.9 -> 76.8 us at 64).  Beyond 64 rows workgroups that narrow re-read the
-// activations so often that the L2 fabric binds, and the shape gains nothing.
-enum { MM_NARROW = 0, MM_NORMAL = 1, MM_WIDE = 2, MM_KSLICE = 3 };   // 2 x 2, 4 x 2, 8 x 1 waves for more than 64 rows
+// ---- k_gemm_pipe: 128 (or 112) weight rows x one row tile per workgroup
+constexpr int PIPE_RB = 8, PIPE_MAX_ROWS = 160;
+template <int NT, int KC, int RBW, int CH, int EPI, int NPL> static bool launch_pipe_t(Ctx *c, GemmArgs &g, int splits) {
+    constexpr int NS = KC == 2 ? 3 : 4;                        // see the kernel: deeper rings measure the same
+    constexpr int STAGE = KC * (8 + NPL * NT * 2);             // KiB
+    constexpr size_t lds = (size_t)std::max(NS * STAGE, CH == 4 ? 32 * NT : 0) * 1024;
+    static_assert(lds <= 150 * 1024, "what allow_big_lds asks for");
+    g.gx = (g.nrb + RBW - 1) / RBW;
+    g.gz = 1;
+    g.gs = splits;
+    static bool allowed[MAX_DEVICES];     // per instantiation
+    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL>), allowed)) return false;
+    const unsigned grid = (unsigned)((g.gx * g.gs + 7) / 8 * 8);
+    hipLaunchKernelGGL((k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL>), dim3(grid), dim3(512), lds, c->stream, g);
+    return true;
+}
+template <int NT, int CH, int EPI, int NPL> static bool launch_pipe_nt(Ctx *c, GemmArgs &g, int splits) {
+    if constexpr (NPL == 1 && EPI == EPI_SWIGLU) {
+        // no k-split here: seven row-blocks per workgroup when that fills whole rounds of 256 CUs better (14336 features:
+        // 256 workgroups instead of 224: 32 / 96 / 143 rows 39.0 / 46.5 / 55.9 -> 36.6 / 44.6 / 52.8 us in an earlier form)
+        auto fill = [&](int rbw) { const int wgs = (g.nrb + rbw - 1) / rbw; return (double)wgs / ((wgs + 255) / 256 * 256); };
+        if (fill(7) > fill(8)) return launch_pipe_t<NT, 2, 7, CH, EPI, NPL>(c, g, splits);
+    }
+    return launch_pipe_t<NT, NPL == 1 || CH == 4 ? 2 : 1, 8, CH, EPI, NPL>(c, g, splits);
+}
+template <int EPI, int NPL> static bool launch_pipe(Ctx *c, GemmArgs &g, int splits) {
+    // Four chains up to 64 rows, except for a product without k-splits over so many weight rows (>= 200 groups of 512: a
+    // vocabulary of 100 thousand) that one chain per output always filled the chip
+    const bool four = g.M <= 64 && (EPI == EPI_PARTIAL || (g.nrb + 31) / 32 < 200);
+    switch ((g.M + 31) / 32) {
+        case 1: return four ? launch_pipe_nt<1, 4, EPI, NPL>(c, g, splits) : launch_pipe_nt<1, 1, EPI, NPL>(c, g, splits);
+        case 2: return four ? launch_pipe_nt<2, 4, EPI, NPL>(c, g, splits) : launch_pipe_nt<2, 1, EPI, NPL>(c, g, splits);
+        case 3: return launch_pipe_nt<3, 1, EPI, NPL>(c, g, splits);
+        case 4: return launch_pipe_nt<4, 1, EPI, NPL>(c, g, splits);
+        default: return launch_pipe_nt<5, 1, EPI, NPL>(c, g, splits);
+    }
+}
+
+// Workgroup shapes of k_gemm_mm (more than 160 rows), tiles of 128 rows: met by 4 x 2 waves (256 weight rows per
+// workgroup, every weight tile loaded by two waves), or - "wide" - by 8 x 1 waves with four row tiles each (512 weight
+// rows, half the L2 traffic per flop, but half as many workgroups), or - "narrow" - by 2 x 2 waves (128 weight rows; two
+// workgroups share a CU).  With k-splits wide pays when it still fills the chip (>= 200 workgroups) and a split keeps
+// >= 24 k-tiles; without them the shape with the fewest rounds of workgroups, weighted by what a round of that shape
+// costs, is taken.
+enum { MM_NARROW = 0, MM_NORMAL = 1, MM_WIDE = 2 };   // 2 x 2, 4 x 2, 8 x 1 waves
 static int mm_layout(int rows, int nrb, int nkt, bool can_split, int max_splits) {
-    if (!can_split && rows <= 64 && (nrb + 8 * MM_RB - 1) / (8 * MM_RB) < 200) return MM_KSLICE;
-    // Products with k-splits over at most 128 rows: every slice costs rows x n floats to write and to read back, so
-    // narrow workgroups that need fewer splits to fill the chip win: k-slice workgroups up to 64 rows (32 rows at
-    // the 8B shape: round 5.07 -> 4.63 ms, 64 rows: 5.89 -> 5.59), 2 x 2 waves beyond (96 rows: 7.10 -> 6.63 ms).
-    if (can_split && rows <= 64) return MM_KSLICE;
-    if (can_split && rows <= 128) return MM_NARROW;
-    if (rows <= 64) return MM_NORMAL;
     const int tiles = (rows + 127) / 128;
     const int base8 = ((nrb + 8 * MM_RB - 1) / (8 * MM_RB)) * tiles, base4 = ((nrb + 4 * MM_RB - 1) / (4 * MM_RB)) * tiles;
     if (!can_split) {
@@ -927,45 +1173,38 @@ static int mm_layout(int rows, int nrb, int nkt, bool can_split, int max_splits)
 
 // returns the number of row tiles and of row-blocks a workgroup covers
 static int mm_shape(int rows, int layout, int *rb_per_wg) {
-    if (layout == MM_KSLICE) {
-        *rb_per_wg = 2 * MM_RB;
-        return 1;
-    }
-    *rb_per_wg = (rows <= 64 || layout == MM_WIDE ? 8 : layout == MM_NORMAL ? 4 : 2) * MM_RB;
-    return rows <= 64 ? 1 : (rows + 127) / 128;
+    *rb_per_wg = (layout == MM_WIDE ? 8 : layout == MM_NORMAL ? 4 : 2) * MM_RB;
+    return (rows + 127) / 128;
 }
 
-// More than 16 rows: k_gemm_mm
+// More than 160 rows: k_gemm_mm
 template <int EPI, int NPL> static bool launch_ws_many_t(Ctx *c, GemmArgs &g, int splits, int layout) {
-    if (layout == MM_KSLICE) {   // 2 row-block groups x 4 k-slices
-        if (g.M <= 32) return launch_mm_t<1, 1, 8, 4, 4, 4, EPI, NPL>(c, g, splits);
-        if (g.M <= 64) return launch_mm_t<2, 1, 8, 4, 4, 4, EPI, NPL>(c, g, splits);
-        if (g.M <= 96) return launch_mm_t<3, 1, 8, 4, 4, 4, EPI, NPL>(c, g, splits);
-        return launch_mm_t<4, 1, 8, 4, 4, 4, EPI, NPL>(c, g, splits);
-    }
-    if (g.M <= 32) {   // one row tile, one plane: chunks of four k-tiles give every wave an operand to stage
-        if (NPL == 1) return launch_mm_t<1, 1, 8, 1, 4, 4, EPI, NPL>(c, g, splits);
-        return launch_mm_t<1, 1, 8, 1, 2, 2, EPI, 2>(c, g, splits);
-    }
-    if (g.M <= 64) return launch_mm_t<2, 1, 8, 1, 2, 2, EPI, NPL>(c, g, splits);
     if (layout == MM_WIDE) {
-        if (EPI != EPI_PARTIAL) return launch_mm_t<4, 1, 8, 1, 2, 2, EPI, NPL, false, true>(c, g, splits);
-        return launch_mm_t<4, 1, 8, 1, 2, 2, EPI, NPL>(c, g, splits);
+        if (EPI != EPI_PARTIAL) return launch_mm_t<4, 1, 8, 2, 2, EPI, NPL, false, true>(c, g, splits);
+        return launch_mm_t<4, 1, 8, 2, 2, EPI, NPL>(c, g, splits);
     }
-    if (layout == MM_NARROW) {
-        // gate/up (no k-split, 65 to 128 rows) streams the most weights per workgroup: a ring of two chunks with the
-        // activations staged as deep (96 rows: 72.8 -> 65.8 us; the split products measured no gain from it)
-        if (EPI == EPI_SWIGLU) return launch_mm_t<2, 2, 4, 1, 2, 4, EPI, NPL, true>(c, g, splits);
-        return launch_mm_t<2, 2, 4, 1, 2, 2, EPI, NPL>(c, g, splits);
+    if constexpr (EPI != EPI_PARTIAL) {   // products with k-splits never take it
+        if (layout == MM_NARROW) {
+            // a ring of two chunks with the activations staged as deep pays for gate/up only (96 rows: 72.8 -> 65.8 us)
+            if (EPI == EPI_SWIGLU) return launch_mm_t<2, 2, 4, 2, 4, EPI, NPL, true>(c, g, splits);
+            return launch_mm_t<2, 2, 4, 2, 2, EPI, NPL>(c, g, splits);
+        }
     }
-    return launch_mm_t<2, 2, 8, 1, 2, 2, EPI, NPL>(c, g, splits);
+    return launch_mm_t<2, 2, 8, 2, 2, EPI, NPL>(c, g, splits);
 }
 // Wh: the half-precision tiles, or null for the two-term product on the bf16 tiles already in g.Wt
 template <int EPI> static bool launch_ws_many(Ctx *c, GemmArgs &g, int splits, int layout, const void *Wh) {
+    // Up to 160 rows (five 32-row tiles: the accumulators of a sixth do not fit a wave's registers) one pass over the
+    // weights in k_gemm_pipe; see there for both sides.  Beyond 128 rows a product whose k-splits were chosen for wide
+    // workgroups (512 weight rows: 16 splits of the down projection at the 8B shape) stays in k_gemm_mm: as 512
+    // workgroups of 128 weight rows it takes 45 us over 143 rows, there 40.
+    const bool pipe = g.M <= PIPE_MAX_ROWS && !(EPI == EPI_PARTIAL && layout == MM_WIDE);
     if (Wh && g.X16) {
         g.Wt = (const u32x4 *)Wh;
+        if (pipe) return launch_pipe<EPI, 1>(c, g, splits);
         return launch_ws_many_t<EPI, 1>(c, g, splits, layout);
     }
+    if (pipe) return launch_pipe<EPI, 2>(c, g, splits);
     return launch_ws_many_t<EPI, 2>(c, g, splits, layout);
 }
 
@@ -997,11 +1236,14 @@ int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, s
         s = std::max(1, std::min(s, std::min(max_splits, std::max(1, g.nkt / 8))));
     } else {
         // about one workgroup per CU over (row-block groups) x (row tiles) x splits; a split keeps >= 8 k-tiles
-        int rb_per_wg;
-        layout = mm_layout(rows, g.nrb, g.nkt, true, std::min(max_splits, std::max(1, g.nkt / 8)));
-        const int tiles = mm_shape(rows, layout, &rb_per_wg);
+        const int max_s = std::min(max_splits, std::max(1, g.nkt / 8));
+        int rb_per_wg = PIPE_RB, tiles = 1;
+        if (rows > 128) {   // (k_gemm_pipe up to 160 rows keeps the split counts of the tiles of 128 rows)
+            layout = mm_layout(rows, g.nrb, g.nkt, true, max_s);
+            tiles = mm_shape(rows, layout, &rb_per_wg);
+        }
         const int base = ((g.nrb + rb_per_wg - 1) / rb_per_wg) * tiles;
-        s = std::max(1, std::min(256 / std::max(1, base), std::min(max_splits, std::max(1, g.nkt / 8))));
+        s = std::max(1, std::min(256 / std::max(1, base), max_s));
     }
     g.kt_per_split = (g.nkt + s - 1) / s;
     const int splits = (g.nkt + g.kt_per_split - 1) / g.kt_per_split;
@@ -1094,7 +1336,7 @@ bool launch_gemm_ws_argmax(Ctx *c, const void *Wt, const ActBuf &X, float *logit
     g.n_cand = g.nrb;                     // at most one candidate slot per row-block
     g.Yp = logits;
     g.cand_val = c->cand_val; g.cand_idx = c->cand_idx;
-    const int slots = rows <= 16 ? g.nrb : (g.nrb + MM_RB - 1) / MM_RB;
+    const int slots = rows <= 16 ? g.nrb : rows <= PIPE_MAX_ROWS ? g.nrb / 2 : (g.nrb + MM_RB - 1) / MM_RB;
     {
         ProfScope ps(c, kclass);
         const bool ok = rows <= 16 ? launch_ws_t<1, 1, 8, 1, 16, EPI_ARGMAX>(c, g, 1, 70 * 1024)

@@ -589,3 +589,17 @@ def test_prefill_chunks_agree_with_small_steps(model, batch, k, lens):
                 if l == 0 and not f32:
                     assert float((a == b).float().mean()) > 0.99
     ctx.wisv_destroy()
+
+
+@pytest.mark.parametrize("batch,k,one_term", [
+    (17, 1, None), (4, 8, None), (3, 11, 0), (16, 4, None), (13, 5, 0), (8, 12, None), (97, 1, None), (8, 16, 0), (43, 3, None),
+    (10, 16, None), (10, 16, 0), (23, 7, None), (23, 7, 0),
+])
+def test_row_tiles_of_the_many_rows_products(batch, k, one_term):
+    """Row counts at both ends of every tile count of the kernel for tens of rows (1 to 5 tiles of 32), in one- and
+    two-term form, and the first count beyond it (161 rows): an odd number of k-tiles (43), a last workgroup with a
+    single row-block, rows past the last, against the oracle."""
+    protos = tuple(PROTO_FH if b % 2 == 0 else PROTO_SH for b in range(batch))
+    w = replace(configs.get(3), model=MID128, batch=batch, ctx=37, k=k, protos=protos, kv_source="synthetic",
+                name=f"mid128_tiles_b{batch}_k{k}_t{one_term}", index=31, taus=(0.5,))
+    _run_workload(w, TOL_BF16, kv="synthetic", one_term=one_term)
