@@ -38,7 +38,7 @@ struct AttnArgs {
     size_t partial_stride;
     const float *cs, *sn;     // rotary tables [max_ctx][64]
     // FUSE, n_ss > 0: the slices are products of x * gain; row m is scaled by 1 / sqrt(sum_p ss[p][m] / d_model + eps)
-    const float *ss;          // [n_ss][rows] (always a readable address)
+    const float *ss;          // [n_ss][rows]
     int n_ss, d_model;
     float eps;
     bf16_t *kv_write;         // == kv_layer
@@ -47,7 +47,9 @@ struct AttnArgs {
 // NQ: 16-row query tiles; NW: waves per workgroup; FUSE: RoPE and the cache append happen here: every workgroup
 // rotates the queries it needs from the slices of the QKV product, and the workgroup of a (stream, KV head) whose
 // k-split ends the sequence writes the new k, v rows before any of its waves reads them (no other split reads them)
-template <int NQ, int NW, bool FUSE>
+// NP: the most slices of the QKV product a fused launch may hold (all NP are requested whatever n_partial is, slices past
+// the last re-read it); SS: the rows still want the 1 / rms of a folded RMSNorm
+template <int NQ, int NW, bool FUSE, int NP, bool SS>
 __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
@@ -127,22 +129,24 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
             }
             const float *src = a.qkv + (size_t)(m0 + j) * d_all + col + i;
             // every slice is requested before the first is used (slices past the last re-read it and count as 0)
-            floatx4 xs[MAX_SPLITS], ys[MAX_SPLITS];
+            floatx4 xs[NP], ys[NP];
 #pragma unroll
-            for (int p = 0; p < MAX_SPLITS; ++p) {
+            for (int p = 0; p < NP; ++p) {
                 const size_t off = (size_t)min(p, a.n_partial - 1) * a.partial_stride;
                 xs[p] = *reinterpret_cast<const floatx4 *>(src + off);
                 ys[p] = *reinterpret_cast<const floatx4 *>(src + off + 64);
             }
             float ssp[MAX_SPLITS];
+            if (SS) {
 #pragma unroll
-            for (int p = 0; p < MAX_SPLITS; ++p) ssp[p] = a.ss[(size_t)min(p, max(a.n_ss, 1) - 1) * a.rows + m0 + j];
+                for (int p = 0; p < MAX_SPLITS; ++p) ssp[p] = a.ss[(size_t)min(p, a.n_ss - 1) * a.rows + m0 + j];
+            }
             const int pos = min(L + j, a.max_ctx - 1);
             const floatx4 co = *reinterpret_cast<const floatx4 *>(a.cs + (size_t)pos * 64 + i);
             const floatx4 si = *reinterpret_cast<const floatx4 *>(a.sn + (size_t)pos * 64 + i);
             floatx4 x = xs[0], y = ys[0];
 #pragma unroll
-            for (int p = 1; p < MAX_SPLITS; ++p) {
+            for (int p = 1; p < NP; ++p) {
                 const bool on = p < a.n_partial;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
@@ -150,7 +154,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
                     y[c] += on ? ys[p][c] : 0.f;
                 }
             }
-            if (a.n_ss > 0) {   // the deferred 1 / rms of the folded RMSNorm (sums of squares in slice order)
+            if (SS) {   // the deferred 1 / rms of the folded RMSNorm (sums of squares in slice order)
                 float t = 0.f;
 #pragma unroll
                 for (int p = 0; p < MAX_SPLITS; ++p) t += p < a.n_ss ? ssp[p] : 0.f;
@@ -479,13 +483,22 @@ __global__ void k_attn_combine(const float *__restrict__ po, const float *__rest
     act_store(o, ((size_t)m * H + h) * HD + d, num / den);
 }
 
-template <int NQ, int NW, bool FUSE> static bool launch_nq(Ctx *c, const AttnArgs &a, dim3 grid) {
+template <int NQ, int NW, bool FUSE, int NP, bool SS> static bool launch_nq_t(Ctx *c, const AttnArgs &a, dim3 grid) {
     // the merge area at the end of the kernel, which also holds the parked query operands before that
     const size_t lds = std::max((size_t)NW * NQ * (2 * 16 * 4 + 8 * 64 * 16), (size_t)NQ * 8 * 1024);
     static bool allowed[MAX_DEVICES];
-    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_attn_mfma<NQ, NW, FUSE>), allowed)) return false;
-    hipLaunchKernelGGL((k_attn_mfma<NQ, NW, FUSE>), grid, dim3(64 * NW), lds, c->stream, a);
+    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_attn_mfma<NQ, NW, FUSE, NP, SS>), allowed)) return false;
+    hipLaunchKernelGGL((k_attn_mfma<NQ, NW, FUSE, NP, SS>), grid, dim3(64 * NW), lds, c->stream, a);
     return true;
+}
+// The fused prologue requests as many slices as its instantiation holds, 32 bytes of each per item: the smallest one that
+// covers the count (rounds of more than 16 rows leave 2 to 10)
+template <int NQ, int NW> static bool launch_nq(Ctx *c, const AttnArgs &a, dim3 grid) {
+    if (a.n_partial == 0) return launch_nq_t<NQ, NW, false, 1, false>(c, a, grid);
+    if (a.n_ss > 0) return launch_nq_t<NQ, NW, true, MAX_SPLITS, true>(c, a, grid);
+    if (a.n_partial <= 2) return launch_nq_t<NQ, NW, true, 2, false>(c, a, grid);
+    if (a.n_partial <= 5) return launch_nq_t<NQ, NW, true, 5, false>(c, a, grid);
+    return launch_nq_t<NQ, NW, true, MAX_SPLITS, false>(c, a, grid);
 }
 
 // One workgroup per (stream, KV head) when that fills the chip (then the workgroup writes the output itself);
@@ -560,12 +573,11 @@ bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_
     {
         ProfScope ps(c, KC_ATTN);
         bool ok;
-        const bool fuse = n_partial > 0;
         switch ((R + 15) / 16) {
-            case 1: ok = fuse ? launch_nq<1, 8, true>(c, a, grid) : launch_nq<1, 8, false>(c, a, grid); break;
-            case 2: ok = fuse ? launch_nq<2, 8, true>(c, a, grid) : launch_nq<2, 8, false>(c, a, grid); break;
-            case 3: ok = fuse ? launch_nq<3, 4, true>(c, a, grid) : launch_nq<3, 4, false>(c, a, grid); break;
-            default: ok = fuse ? launch_nq<4, 4, true>(c, a, grid) : launch_nq<4, 4, false>(c, a, grid); break;
+            case 1: ok = launch_nq<1, 8>(c, a, grid); break;
+            case 2: ok = launch_nq<2, 8>(c, a, grid); break;
+            case 3: ok = launch_nq<3, 4>(c, a, grid); break;
+            default: ok = launch_nq<4, 4>(c, a, grid); break;
         }
         if (!ok) return false;
     }
