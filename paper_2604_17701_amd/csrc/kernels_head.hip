@@ -60,22 +60,27 @@ struct HeadArgs {
 // is position m scored, and from which row of hd: Alg. 1's localisation (mismatch against the target's greedy token)
 // and the upload protocol (Sec. III-B: full-hidden streams are scored everywhere, selective-hidden ones at mismatches)
 __device__ __forceinline__ bool head_scored(const HeadArgs &a, int m, int *hr_out) {
+    // every load is unconditional (one behind a branch is waited for on the spot): they go out together, pred_next after
+    // the slot id
     const int b = m / a.k, j = m - b * a.k;
     const int slot = min(max(a.stream_ids[b], 0), a.max_batch - 1);
-    const int t_pred = j == 0 ? a.pred_next[slot] : a.amax[m - 1];
-    const bool mismatch = a.tokens[m] != t_pred;
-    int hr = a.hd_row ? a.hd_row[m] : m;
+    const int before = a.amax[max(m - 1, 0)], token = a.tokens[m], proto = a.proto[b];
+    int hr = (a.hd_row ? a.hd_row : a.tokens)[m];
+    if (!a.hd_row) hr = m;
+    const int pending = a.pred_next[slot];
+    const bool mismatch = token != (j == 0 ? pending : before);
     if (hr >= a.n_hd) hr = -1;
     *hr_out = hr;
-    return (a.gate_all || a.proto[b] == WISV_PROTO_FH || mismatch) && hr >= 0;
+    return (a.gate_all || proto == WISV_PROTO_FH || mismatch) && hr >= 0;
 }
 
-// element c of z = [h^D ; h^T ; c ; 0...] of position m
+// element c < din of z = [h^D ; h^T ; c] of position m
 template <typename WT> __device__ __forceinline__ float head_z(const HeadArgs &a, int m, int hr, int c) {
-    if (c < a.dD) return Elem<WT>::load((const WT *)a.hd + (size_t)hr * a.dD + c);
-    if (c < a.dD + a.dT) return a.h_t[(size_t)m * a.dT + c - a.dD];
-    if (c < a.din) return a.csi[(size_t)(m / a.k) * a.dC + c - a.dD - a.dT];
-    return 0.f;
+    // all three sources at clamped places (no load behind a branch), the right one selected
+    const float d = Elem<WT>::load((const WT *)a.hd + (size_t)hr * a.dD + min(c, a.dD - 1));
+    const float t = a.h_t[(size_t)m * a.dT + min(max(c - a.dD, 0), a.dT - 1)];
+    const float v = a.csi[(size_t)(m / a.k) * a.dC + min(max(c - a.dD - a.dT, 0), a.dC - 1)];
+    return c < a.dD ? d : c < a.dD + a.dT ? t : v;
 }
 
 __device__ __forceinline__ float head_act(int act, float v) { return act == WISV_ACT_RELU ? fmaxf(v, 0.f) : v / (1.0f + expf(-v)); }
@@ -100,6 +105,16 @@ __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
         hd_row[t] = (const bf16_t *)a.hd + (size_t)max(hr[t], 0) * a.dD;
         ht_row[t] = a.h_t + (size_t)min(m[t], a.rows - 1) * a.dT;
     }
+    // bias and second-layer weights of this lane's hidden units, for the end of the kernel (units past the last re-read it)
+    bf16_t b1v[RB][4], w2v[RB][4];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = min((rb0 + r) * 16 + bg * 4 + e, a.dJ - 1);
+            b1v[r][e] = ((const bf16_t *)a.b1)[j];
+            w2v[r][e] = ((const bf16_t *)a.w2)[j];
+        }
     if (tid == 0) any_scored = 0;
     __syncthreads();
     if (wk == 0) {
@@ -202,9 +217,22 @@ __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
         for (int r = 0; r < RB; ++r) av[r] = wt[r][(size_t)kt * 64];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            float z[8];
+            // the three sources are read at clamped places and the right one is selected: one latency for the tile instead
+            // of one per element (positions that are not scored are zeroed by mma)
+            float z[8], zd[8], zt[8], zc[8];
+            const float *csi = a.csi + (size_t)(min(m[t], a.rows - 1) / a.k) * a.dC;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) z[e] = sc[t] ? head_z<bf16_t>(a, m[t], hr[t], kt * 32 + bg * 8 + e) : 0.f;
+            for (int e = 0; e < 8; ++e) {
+                const int col = kt * 32 + bg * 8 + e;
+                zd[e] = bf16_to_f32(hd_row[t][min(col, a.dD - 1)]);
+                zt[e] = ht_row[t][min(max(col - a.dD, 0), a.dT - 1)];
+                zc[e] = csi[min(max(col - a.dD - a.dT, 0), a.dC - 1)];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int col = kt * 32 + bg * 8 + e;
+                z[e] = col < a.dD ? zd[e] : col < a.dD + a.dT ? zt[e] : col < a.din ? zc[e] : 0.f;
+            }
             u32x4 bh, bl;
             split8(z, bh, bl);
             mma(av, t, bh, bl, true);
@@ -229,7 +257,7 @@ __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
             for (int e = 0; e < 4; ++e) {
                 const int j = (rb0 + r) * 16 + bg * 4 + e;
                 if (j < a.dJ)
-                    s2 = fmaf(bf16_to_f32(((const bf16_t *)a.w2)[j]), head_act(a.act, u[e] + bf16_to_f32(((const bf16_t *)a.b1)[j])), s2);
+                    s2 = fmaf(bf16_to_f32(w2v[r][e]), head_act(a.act, u[e] + bf16_to_f32(b1v[r][e])), s2);
             }
             s2 += __shfl_xor(s2, 16, 64);
             s2 += __shfl_xor(s2, 32, 64);
@@ -237,25 +265,47 @@ __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
         }
 }
 
-// Generic form (float weights, or shapes the re-tiled form does not serve): one workgroup per position, its waves
-// take the hidden units in turn; one partial sum per position.
+// Generic form (float weights, or shapes the re-tiled form does not serve): one workgroup of 16 waves per position; one
+// partial sum per position.  Bound by latency (4 rows of the tiny fp32 target: 18 us when four waves took one hidden unit
+// after the other, 5 us now): a wave works on UJ hidden units at once, all loads of a step of columns before the first use.  The
+// units' products are then added by four threads, unit j by thread j % 4 in rising order, and the four sums in pairs.
 template <typename WT>
-__global__ __launch_bounds__(256) void k_head_ref(HeadArgs a) {
-    __shared__ float red[4];
+__global__ __launch_bounds__(1024) void k_head_ref(HeadArgs a) {
+    constexpr int UJ = 4, GROUP = 16 * UJ * 4;            // hidden units per wave at once; per pass over val
+    __shared__ float val[GROUP], red[4];
     const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int hr;
     const bool sc = head_scored(a, m, &hr);
     if (tid == 0) a.scored[m] = sc ? 1 : 0;
     if (!sc) return;
     float t = 0.f;
-    for (int j = wave; j < a.dJ; j += 4) {
-        const WT *wr = (const WT *)a.w1 + (size_t)j * a.din;
-        float dot = 0.f;
-        for (int c = lane; c < a.din; c += 64) dot = fmaf(Elem<WT>::load(wr + c), head_z<WT>(a, m, hr, c), dot);
-        dot = wave_sum(dot);
-        t = fmaf(Elem<WT>::load((const WT *)a.w2 + j), head_act(a.act, dot + Elem<WT>::load((const WT *)a.b1 + j)), t);
+    for (int g0 = 0; g0 < a.dJ; g0 += GROUP) {
+        for (int j0 = g0 + wave * UJ; j0 < min(g0 + GROUP, a.dJ); j0 += 16 * UJ) {
+            float dot[UJ], bias[UJ];
+            const WT *wr[UJ];
+#pragma unroll
+            for (int i = 0; i < UJ; ++i) {                // units past the last re-read it
+                dot[i] = 0.f;
+                wr[i] = (const WT *)a.w1 + (size_t)min(j0 + i, a.dJ - 1) * a.din;
+                bias[i] = Elem<WT>::load((const WT *)a.b1 + min(j0 + i, a.dJ - 1));
+            }
+            for (int c = lane; c < a.din; c += 64) {
+                const float z = head_z<WT>(a, m, hr, c);
+#pragma unroll
+                for (int i = 0; i < UJ; ++i) dot[i] = fmaf(Elem<WT>::load(wr[i] + c), z, dot[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < UJ; ++i) {
+                dot[i] = wave_sum(dot[i]);
+                if (lane == 0 && j0 + i < a.dJ) val[j0 + i - g0] = head_act(a.act, dot[i] + bias[i]);
+            }
+        }
+        __syncthreads();
+        if (tid < 4)
+            for (int j = g0 + tid; j < min(g0 + GROUP, a.dJ); j += 4) t = fmaf(Elem<WT>::load((const WT *)a.w2 + j), val[j - g0], t);
+        __syncthreads();
     }
-    if (lane == 0) red[wave] = t;
+    if (tid < 4) red[tid] = t;
     __syncthreads();
     if (tid == 0) a.sp[m] = (red[0] + red[1]) + (red[2] + red[3]);
 }
@@ -338,16 +388,22 @@ void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in, const wis
     {
         ProfScope ps(c, KC_HEAD);
         if (c->head_w1_t && g.d_draft % 8 == 0 && g.d_draft >= 8) {
-            // sixteen waves split the columns when few positions leave the chip empty otherwise, four when there are many
+            // A workgroup's time is what it reads (a row-block of W1, 200 KB at the 8B shape, and 260 KB of h^T per tile), so
+            // the smallest tiles are taken that make at most one round of 256 workgroups: one row-block x one tile of 16
+            // positions (96 rows: 18.7 us against 31.3 with 2 x 2 tiles), then two row-blocks (143 rows: 21.3 against 29.8;
+            // as 288 workgroups of one 35.8), then 2 x 2 operand tiles per wave (512 rows: 32.3 us; two row-blocks 42.0).
+            const int tiles = (f.rows + 15) / 16;
             parts = a.nrb;
-            if (f.rows <= 64)
-                hipLaunchKernelGGL((k_head_fused<16, 1, 1, 8>), dim3(a.nrb, (f.rows + 15) / 16), dim3(1024), 0, c->stream, a);
-            else   // many positions: 2 x 2 operand tiles per wave halve what every workgroup reads
-                hipLaunchKernelGGL((k_head_fused<8, 2, 2, 4>), dim3((a.nrb + 1) / 2, (f.rows + 31) / 32), dim3(512), 0, c->stream, a);
+            if (a.nrb * tiles <= 256)
+                hipLaunchKernelGGL((k_head_fused<16, 1, 1, 8>), dim3(a.nrb, tiles), dim3(1024), 0, c->stream, a);
+            else if ((a.nrb + 1) / 2 * tiles <= 256)
+                hipLaunchKernelGGL((k_head_fused<16, 2, 1, 4>), dim3((a.nrb + 1) / 2, tiles), dim3(1024), 0, c->stream, a);
+            else
+                hipLaunchKernelGGL((k_head_fused<8, 2, 2, 4>), dim3((a.nrb + 1) / 2, (tiles + 1) / 2), dim3(512), 0, c->stream, a);
         } else {
             parts = 1;
-            if (c->bf16) hipLaunchKernelGGL(k_head_ref<bf16_t>, dim3(f.rows), dim3(256), 0, c->stream, a);
-            else hipLaunchKernelGGL(k_head_ref<float>, dim3(f.rows), dim3(256), 0, c->stream, a);
+            if (c->bf16) hipLaunchKernelGGL(k_head_ref<bf16_t>, dim3(f.rows), dim3(1024), 0, c->stream, a);
+            else hipLaunchKernelGGL(k_head_ref<float>, dim3(f.rows), dim3(1024), 0, c->stream, a);
         }
     }
     {

@@ -603,3 +603,20 @@ def test_row_tiles_of_the_many_rows_products(batch, k, one_term):
     w = replace(configs.get(3), model=MID128, batch=batch, ctx=37, k=k, protos=protos, kv_source="synthetic",
                 name=f"mid128_tiles_b{batch}_k{k}_t{one_term}", index=31, taus=(0.5,))
     _run_workload(w, TOL_BF16, kv="synthetic", one_term=one_term)
+
+
+@pytest.mark.parametrize("base,d_draft,d_head,act,batch,k", [
+    (MID128, 200, 520, configs.ACT_SILU, 13, 10),     # 130 rows, 33 row-blocks: two per workgroup; h^D ends inside a 32-column tile
+    (MID128, 192, 520, configs.ACT_RELU, 30, 10),     # 300 rows: 2 x 2 tiles, an odd number of both
+    (MID128, 8, 40, configs.ACT_SILU, 2, 3),          # h^D of eight columns: its only tile straddles into h^T
+    (MID128, 100, 300, configs.ACT_SILU, 2, 5),       # a width the tiled form does not serve: generic form on bf16 weights
+    (W0.model, 131, 300, configs.ACT_RELU, 1, 4),     # generic form, fp32, more than one pass over the hidden units
+    (W0.model, 3, 1, configs.ACT_SILU, 1, 4),         # a single hidden unit
+])
+def test_decision_head_forms(base, d_draft, d_head, act, batch, k):
+    """Every form of the head kernel at odd widths, against the oracle (probabilities to the path's tolerance)."""
+    protos = tuple(PROTO_FH if b % 2 == 0 else PROTO_SH for b in range(batch))
+    f32 = base.dtype == "f32"
+    w = replace(W0 if f32 else configs.get(3), model=replace(base, d_draft=d_draft, d_head_hidden=d_head, head_act=act), batch=batch,
+                ctx=33, k=k, protos=protos, kv_source="synthetic", name=f"head_{d_draft}_{d_head}_b{batch}_k{k}", index=41, taus=(0.5,))
+    _run_workload(w, TOL_F32 if f32 else TOL_BF16, kv="synthetic")
