@@ -21,6 +21,33 @@ struct wisv_ctx : public wisv::Ctx {};
 // at the 8B shape; doubling them would buy 5 %.
 constexpr int PREFILL_ROWS = 1024;
 
+// Uploaded hidden states of a host-pointer round up to this size are packed with the other arguments (512 rows of 2048
+// bf16 values are 2 MB); larger ones are worth a copy command of their own.
+constexpr size_t IO_HIDDEN_BYTES = (size_t)4 << 20;
+
+// Packs the arguments of a host-pointer round one behind the other
+struct IoPack {
+    Ctx *c;
+    size_t used = 0;
+    // room for n bytes: where to put them on the host, and where they will be on the device
+    void *add(const void *src, size_t n) {
+        memcpy(c->io_in + used, src, n);
+        void *dev = c->d_in + used;
+        used += (n + 63) / 64 * 64;
+        return dev;
+    }
+};
+// Places of a host-pointer round's results in pinned memory
+struct IoOut {
+    Ctx *c;
+    size_t used = 0;
+    template <typename T> T *take(size_t n) {
+        T *p = (T *)(c->io_out + used);
+        used += (n * sizeof(T) + 63) / 64 * 64;
+        return p;
+    }
+};
+
 namespace wisv {
 
 void *kv_ptr(const Ctx *c, int layer, int slot, int which) {
@@ -120,6 +147,7 @@ static void destroy_ctx(Ctx *c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     for (void *p : c->owned) (void)hipFree(p);
+    if (c->io_in) (void)hipHostFree(c->io_in);
     if (c->stream_owned) (void)hipStreamDestroy(c->stream);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->ev_round[0]) (void)hipEventDestroy(c->ev_round[0]);
@@ -171,7 +199,8 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     c->logits = nullptr;
     c->logits_rows = 0;
     c->ss_ws = nullptr;
-    c->d_ss_q = c->d_ss_u = c->d_ss_v = nullptr;
+    c->io_in = c->io_out = c->d_in = nullptr;
+    c->d_ss_q = nullptr;
     c->last_rows = 0;
     c->launch_failed = false;
     memset(c->prof_ms, 0, sizeof c->prof_ms);
@@ -349,23 +378,31 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     CREATE_TRY(hipMemsetAsync(c->d_pred_next, 0, g.max_batch * 4, c->stream));
 
     // ---- staging of a round's inputs / outputs, scratch of the forward
+    {
+        // every argument and result of the largest round, each on a 64-byte boundary; uploaded hidden states beyond
+        // IO_HIDDEN_BYTES are copied by themselves
+        auto pad = [](size_t n) { return (n + 63) / 64 * 64; };
+        const size_t B = g.max_batch;
+        c->io_in_bytes = 2 * pad(B * 4) + 2 * pad((size_t)R * 4) + pad(B * g.d_csi * 4) + pad(B * 4) + pad((size_t)R * 4) +
+                         pad(std::min((size_t)R * g.d_draft * esz, IO_HIDDEN_BYTES));
+        const size_t out_bytes = 4 * pad(B * 4) + pad((size_t)R * 4) + pad(B * (g.max_k + 1) * 4);
+        void *h = nullptr;
+        CREATE_TRY(hipHostMalloc(&h, c->io_in_bytes + out_bytes, hipHostMallocDefault));
+        c->io_in = (unsigned char *)h;
+        c->io_out = c->io_in + c->io_in_bytes;
+        CREATE_TRY(dalloc(c, &c->d_in, c->io_in_bytes));
+    }
     CREATE_TRY(dalloc(c, &c->d_stream_ids, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_tokens, RF));
-    CREATE_TRY(dalloc(c, &c->d_proto, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_hd_row, R));
     {
         char *p;
         CREATE_TRY(dalloc(c, &p, (size_t)R * g.d_draft * esz));
         c->d_hd = p;
     }
-    CREATE_TRY(dalloc(c, &c->d_csi, (size_t)g.max_batch * g.d_csi));
-    CREATE_TRY(dalloc(c, &c->d_tau, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_alen, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_ytok, g.max_batch));
-    CREATE_TRY(dalloc(c, &c->d_targ, (size_t)g.max_batch * (g.max_k + 1)));
     CREATE_TRY(dalloc(c, &c->d_pacc, R));
-    CREATE_TRY(dalloc(c, &c->d_mask, g.max_batch));
-    CREATE_TRY(dalloc(c, &c->d_status, g.max_batch));
     CREATE_TRY(dalloc(c, &c->row_slot, RF));
     CREATE_TRY(dalloc(c, &c->row_pos, RF));
     CREATE_TRY(dalloc(c, &c->amax, R));
@@ -385,17 +422,19 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     CREATE_TRY(dalloc(c, &c->gu, (size_t)(c->ws_ok ? std::min(RF, 16) : RF) * 2 * F));   // read by the generic kernels only
     CREATE_TRY(dalloc(c, &c->h_t, (size_t)R * d));
     CREATE_TRY(dalloc(c, &c->hu, (size_t)((g.d_head_hidden + 15) / 16) * R));   // the head's partial sums [row-block][row]
-    auto act_alloc = [&](ActBuf *a, size_t n, bool half) -> hipError_t {
-        hipError_t e = dalloc(c, &a->f, n);
+    // (beyond 16 rows the matrix-core path never writes or reads a float plane)
+    auto act_alloc = [&](ActBuf *a, size_t rows, size_t width, bool half) -> hipError_t {
+        const size_t n = rows * width;
+        hipError_t e = dalloc(c, &a->f, c->ws_ok ? std::min<size_t>(rows, 16) * width : n);
         if (e == hipSuccess) e = dalloc(c, &a->hi, n);
         if (e == hipSuccess) e = dalloc(c, &a->lo, n);
         a->h16 = nullptr;
         if (e == hipSuccess && half) e = dalloc(c, &a->h16, n);
         return e;
     };
-    CREATE_TRY(act_alloc(&c->a, (size_t)RF * d, c->half_ok));
-    CREATE_TRY(act_alloc(&c->o, (size_t)RF * c->d_q, c->half_ok));
-    CREATE_TRY(act_alloc(&c->h, (size_t)RF * F, c->half_ok));
+    CREATE_TRY(act_alloc(&c->a, RF, d, c->half_ok));
+    CREATE_TRY(act_alloc(&c->o, RF, c->d_q, c->half_ok));
+    CREATE_TRY(act_alloc(&c->h, RF, F, c->half_ok));
     CREATE_TRY(dalloc(c, &c->q, (size_t)RF * c->d_q));
     {
         // split-KV attention partials: as many splits of the largest round as fit 64 MiB, at most 64
@@ -412,8 +451,6 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
         CREATE_TRY(dalloc(c, &p, ss_workspace_bytes(R, V, g.max_batch)));
         c->ss_ws = p;
     }
-    CREATE_TRY(dalloc(c, &c->d_ss_u, R));
-    CREATE_TRY(dalloc(c, &c->d_ss_v, g.max_batch));
     c->d_ss_q = nullptr;
     CREATE_TRY(hipStreamSynchronize(c->stream));
 #undef CREATE_TRY
@@ -665,27 +702,28 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
     wisv_round_in din = *in;
     wisv_round_out dout = *out;
     if (!dev_io) {
-        HIP_TRY(c, hipMemcpyAsync(c->d_stream_ids, in->stream_ids, B * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_tokens, in->draft_tokens, R * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_proto, in->proto, B * 4, hipMemcpyHostToDevice, c->stream));
-        if (in->hd_row) HIP_TRY(c, hipMemcpyAsync(c->d_hd_row, in->hd_row, R * 4, hipMemcpyHostToDevice, c->stream));
-        if (in->n_hd)
-            HIP_TRY(c, hipMemcpyAsync(c->d_hd, in->hd, (size_t)in->n_hd * g.d_draft * c->esz, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_csi, in->csi, (size_t)B * g.d_csi * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_tau, in->tau, B * 4, hipMemcpyHostToDevice, c->stream));
-        din.stream_ids = c->d_stream_ids;
-        din.draft_tokens = c->d_tokens;
-        din.proto = c->d_proto;
-        din.hd_row = in->hd_row ? c->d_hd_row : nullptr;
+        IoPack pack{c};
+        const size_t hd_bytes = (size_t)in->n_hd * g.d_draft * c->esz;
+        din.stream_ids = (const int32_t *)pack.add(in->stream_ids, (size_t)B * 4);
+        din.draft_tokens = (const int32_t *)pack.add(in->draft_tokens, (size_t)R * 4);
+        din.proto = (const int32_t *)pack.add(in->proto, (size_t)B * 4);
+        din.hd_row = in->hd_row ? (const int32_t *)pack.add(in->hd_row, (size_t)R * 4) : nullptr;
+        din.csi = (const float *)pack.add(in->csi, (size_t)B * g.d_csi * 4);
+        din.tau = (const float *)pack.add(in->tau, (size_t)B * 4);
         din.hd = c->d_hd;
-        din.csi = c->d_csi;
-        din.tau = c->d_tau;
-        dout.accepted_len = c->d_alen;
-        dout.correction_token = c->d_ytok;
-        dout.p_accept = c->d_pacc;
-        dout.target_argmax = c->d_targ;
-        dout.mismatch_mask = c->d_mask;
-        dout.status = c->d_status;
+        if (hd_bytes > IO_HIDDEN_BYTES)
+            HIP_TRY(c, hipMemcpyAsync(c->d_hd, in->hd, hd_bytes, hipMemcpyHostToDevice, c->stream));
+        else if (hd_bytes)
+            din.hd = pack.add(in->hd, hd_bytes);
+        launch_unpack(c, c->io_in, c->d_in, pack.used);
+        HIP_TRY(c, hipGetLastError());
+        IoOut res{c};
+        dout.accepted_len = res.take<int32_t>(B);
+        dout.correction_token = res.take<int32_t>(B);
+        dout.p_accept = res.take<float>(R);
+        dout.target_argmax = res.take<int32_t>((size_t)B * (K + 1));
+        dout.mismatch_mask = res.take<uint32_t>(B);
+        dout.status = res.take<uint32_t>(B);
     }
 
     Fwd f;
@@ -776,18 +814,15 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
     c->last_rows = R;
 
     if (!dev_io) {
-        std::vector<int32_t> alen(B);
-        HIP_TRY(c, hipMemcpyAsync(alen.data(), c->d_alen, B * 4, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(out->correction_token, c->d_ytok, B * 4, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(out->p_accept, c->d_pacc, R * 4, hipMemcpyDeviceToHost, c->stream));
-        if (out->target_argmax)
-            HIP_TRY(c, hipMemcpyAsync(out->target_argmax, c->d_targ, (size_t)B * (K + 1) * 4, hipMemcpyDeviceToHost, c->stream));
-        if (out->mismatch_mask) HIP_TRY(c, hipMemcpyAsync(out->mismatch_mask, c->d_mask, B * 4, hipMemcpyDeviceToHost, c->stream));
-        if (out->status) HIP_TRY(c, hipMemcpyAsync(out->status, c->d_status, B * 4, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
+        memcpy(out->correction_token, dout.correction_token, (size_t)B * 4);
+        memcpy(out->p_accept, dout.p_accept, (size_t)R * 4);
+        if (out->target_argmax) memcpy(out->target_argmax, dout.target_argmax, (size_t)B * (K + 1) * 4);
+        if (out->mismatch_mask) memcpy(out->mismatch_mask, dout.mismatch_mask, (size_t)B * 4);
+        if (out->status) memcpy(out->status, dout.status, (size_t)B * 4);
         for (int b = 0; b < B; ++b) {
-            out->accepted_len[b] = alen[b];
-            if (commit) c->h_len_ub[in->stream_ids[b]] += alen[b];
+            out->accepted_len[b] = dout.accepted_len[b];
+            if (commit) c->h_len_ub[in->stream_ids[b]] += dout.accepted_len[b];
         }
         if (verify_only) {
             c->pending_valid = true;
@@ -853,16 +888,15 @@ extern "C" int wisv_ss_verify_round(wisv_ctx *ctx, const wisv_ss_in *in, wisv_ss
     a.commit = commit;
     if (!dev_io) {
         if (!c->d_ss_q) HIP_TRY(c, dalloc(c, &c->d_ss_q, (size_t)c->rows_max * V));
-        HIP_TRY(c, hipMemcpyAsync(c->d_stream_ids, in->stream_ids, B * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_tokens, in->draft_tokens, R * 4, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipMemcpyAsync(c->d_ss_q, in->draft_probs, (size_t)R * V * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_ss_u, in->u_accept, R * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_ss_v, in->u_sample, B * 4, hipMemcpyHostToDevice, c->stream));
-        a.stream_ids = c->d_stream_ids;
-        a.tokens = c->d_tokens;
+        IoPack pack{c};
+        a.stream_ids = (const int32_t *)pack.add(in->stream_ids, (size_t)B * 4);
+        a.tokens = (const int32_t *)pack.add(in->draft_tokens, (size_t)R * 4);
+        a.u_accept = (const float *)pack.add(in->u_accept, (size_t)R * 4);
+        a.u_sample = (const float *)pack.add(in->u_sample, (size_t)B * 4);
+        launch_unpack(c, c->io_in, c->d_in, pack.used);
+        HIP_TRY(c, hipGetLastError());
         a.draft_probs = c->d_ss_q;
-        a.u_accept = c->d_ss_u;
-        a.u_sample = c->d_ss_v;
         a.accepted_len = c->d_alen;
         a.emitted_token = c->d_ytok;
         a.alpha = c->d_pacc;

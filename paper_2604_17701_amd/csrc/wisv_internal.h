@@ -152,14 +152,16 @@ struct Ctx {
     int32_t *d_kv_len, *d_pred_next;
     std::vector<int32_t> h_len_ub;
 
-    // round inputs staged on the device (host-pointer mode)
-    int32_t *d_stream_ids, *d_tokens, *d_proto, *d_hd_row;
+    // a prompt's slot and tokens; the row map of a round without uploads; uploaded hidden states too large to be packed
+    int32_t *d_stream_ids, *d_tokens, *d_hd_row;
     void *d_hd;
-    float *d_csi, *d_tau;
-    // round outputs staged on the device
-    int32_t *d_alen, *d_ytok, *d_targ;
+    // host-pointer mode: a round's inputs are packed into io_in (pinned host memory the GPU can read), which a kernel
+    // copies to d_in as it is; the last kernel writes the results straight into io_out (pinned as well)
+    unsigned char *io_in, *io_out, *d_in;
+    size_t io_in_bytes;
+    // outputs of a host-pointer sampling round
+    int32_t *d_alen, *d_ytok;
     float *d_pacc;
-    uint32_t *d_mask, *d_status;
 
     // scratch
     int32_t *row_slot, *row_pos, *amax, *scored;
@@ -178,7 +180,7 @@ struct Ctx {
     size_t logits_rows;
     size_t att_cap;               // query rows of width d_q that att_o holds
     void *ss_ws;                  // speculative-sampling scratch: chunk statistics, normalisers, chunk weights
-    float *d_ss_q, *d_ss_u, *d_ss_v;   // its host-mode input staging (d_ss_q is allocated by the first call that needs it)
+    float *d_ss_q;                // its host-mode staging of the drafter's distributions (allocated by the first call that needs it)
 
     // timing
     hipEvent_t ev_round[2];
@@ -216,6 +218,8 @@ struct Fwd {
 // ---------------------------------------------------------------- kernel launchers (kernels_ref.hip)
 void launch_prep_rows(Ctx *c, const Fwd &f);
 void launch_embed(Ctx *c, const Fwd &f);
+// bytes (a multiple of 16) from pinned host memory to the device
+void launch_unpack(Ctx *c, const void *host, void *dev, size_t bytes);
 void launch_v_reblock(Ctx *c, void *rows, void *plane, int len, bool to_plane);
 // x += sum of n_partial slices of y (if n_partial > 0); out = RMSNorm(x) * g; optional second float copy
 // row0: the first row of x and y that is normalised (its result is row 0 of the outputs)

@@ -612,6 +612,7 @@ def test_row_tiles_of_the_many_rows_products(batch, k, one_term):
     (MID128, 100, 300, configs.ACT_SILU, 2, 5),       # a width the tiled form does not serve: generic form on bf16 weights
     (W0.model, 131, 300, configs.ACT_RELU, 1, 4),     # generic form, fp32, more than one pass over the hidden units
     (W0.model, 3, 1, configs.ACT_SILU, 1, 4),         # a single hidden unit
+    (W0.model, 70000, 5, configs.ACT_SILU, 2, 16),    # uploads beyond the packed staging (4 MB): a copy of their own
 ])
 def test_decision_head_forms(base, d_draft, d_head, act, batch, k):
     """Every form of the head kernel at odd widths, against the oracle (probabilities to the path's tolerance)."""
