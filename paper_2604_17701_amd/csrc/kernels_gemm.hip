@@ -94,7 +94,8 @@ struct GemmArgs {
     float *cand_val;           // EPI_ARGMAX: [M][n_cand]
     int32_t *cand_idx;
     int n_cand;
-    int gx, gz, gs;            // k_gemm_mm: row-block groups, row tiles and k-splits the 1-D grid decodes into
+    int gx, gz, gs;            // k_gemm_mm, k_gemm_pipe: row-block groups, row tiles and k-splits the 1-D grid decodes into
+    int per;                   // k_gemm_pipe: consecutive k-splits a workgroup takes one after the other
     // PRO: the activations are the attention output, still in k-split partials (up to WS_PRO_SPLITS of them):
     // o [split][rows][heads][128], running maximum m (in units of ln 2) and sum l [split][rows][heads]
     const float *att_o, *att_m, *att_l;
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 // a first form, 143 rows, gate/up of the 8B shape: 56 us, 54 without the matrix instructions, 47 with the weights
 // alone), so beyond 32 rows, where weights alone (6.2 TB/s over 256 CUs) stop being the limit, time grows with the
 // activations every workgroup re-reads from L2.  Against the workgroups it replaced, us per launch at the 8B shape, 32 /
-// 96 / 143 rows: gate/up 49.0 / 61.8 / 76.3 -> 38.0 / 42.8 / 49.2, down 23.6 / 33.3 -> 19.8 / 23.1 (143 rows: k_gemm_mm),
+// 96 / 143 rows: gate/up 49.0 / 61.8 / 76.3 -> 38.0 / 42.8 / 49.2, down 23.6 / 33.3 / 40.9 -> 19.6 / 24.6 / 34.6,
 // QKV (two terms) 14.1 / 20.4 / 27.3 -> 10.3 / 18.4 / 23.1, O (two terms) 10.9 / 14.8 / 20.4 -> 8.3 / 12.4 / 16.8, LM head of
 // 32000 tokens 53.3 / 70.0 / 82.8 -> 45.4 / 49.4 / 55.1, of 128256 tokens over 28 rows 207 -> 188.
 
@@ -826,12 +827,15 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
     const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     // (quotients come out of vector registers: made scalar here, so that every address below is)
-    const int zq = __builtin_amdgcn_readfirstlane(slot / g.gz), z = slot - zq * g.gz, q = zq * 8 + xcd;
-    if (q >= g.gx * g.gs) return;                         // the whole workgroup leaves: no barrier is reached
+    const int q = slot * 8 + xcd, groups = (g.gs + g.per - 1) / g.per;
+    if (q >= g.gx * groups) return;                       // the whole workgroup leaves: no barrier is reached
     const int by = __builtin_amdgcn_readfirstlane(q / g.gx), bx = q - by * g.gx;
-    const int kt0 = by * g.kt_per_split, ntile = min(g.kt_per_split, g.nkt - kt0);
-    const int m_base = z * (32 * NT);
-    const int nst = (ntile + KC - 1) / KC;                // every wave passes nst barriers (CH == 4: and two more)
+    // k-tiles of the first split and of the workgroup's last one; their stages run through the ring without a break
+    const int split0 = by * g.per, n_split = min(g.per, g.gs - split0);
+    const int kt0 = split0 * g.kt_per_split, whole = g.kt_per_split;
+    const int tail = min(whole, g.nkt - kt0 - (n_split - 1) * whole), ntile = n_split == 1 ? tail : whole;
+    const int per_split = (whole + KC - 1) / KC;
+    const int nst = (n_split - 1) * per_split + (tail + KC - 1) / KC;   // every wave passes nst barriers (CH == 4: and two more)
 
     if (wave8 >= 4) {
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
@@ -840,13 +844,16 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
             // ---- weights: NW tiles of a stage (tile i = half NW + j: row-block i / KC, k-tile i % KC)
             const unsigned char *base = scalar_ptr(g.Wt + ((size_t)bx * RBW * g.nkt + kt0) * 64);
             const int rb_last = g.nrb - 1 - bx * RBW;         // row-blocks past the last re-read it (RBW == 7)
+            int first = 0, at = 0;                            // of the next stage to load: its split's first k-tile, its place there
             auto issue = [&](int st) {
                 const uint32_t buf = lds0 + (uint32_t)(st % NS) * STAGE;
+                const int kt_last = min(whole, g.nkt - kt0 - first) - 1;
 #pragma unroll
                 for (int j = 0; j < NW; ++j) {
-                    const int i = half * NW + j, rb = min(i / KC, rb_last), kt = min(st * KC + i % KC, ntile - 1);
+                    const int i = half * NW + j, rb = min(i / KC, rb_last), kt = first + min(at * KC + i % KC, kt_last);
                     lds_load_1k_nt(buf + i * 1024, lane * 16 + (uint32_t)(rb * g.nkt + kt) * 1024u, base);
                 }
+                if (++at == per_split) at = 0, first += whole;
             };
             for (int st = 0; st < min(NS - 1, nst); ++st) issue(st);
             for (int st = 0; st < nst; ++st) {
@@ -866,12 +873,15 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
             for (int j = 0; j < NA; ++j) {
                 const int r = (half * NA + j) % (NT * 32 / RPL) * RPL + lane / PCS;
                 // rows past M re-read row M - 1; their results are not written
-                avo[j] = (uint32_t)min(m_base + r, g.M - 1) * (uint32_t)g.kd * 2u + (uint32_t)(piece * 16);
+                avo[j] = (uint32_t)min(r, g.M - 1) * (uint32_t)g.kd * 2u + (uint32_t)(piece * 16);
             }
+            int first = 0, at = 0;
             auto issue = [&](int st) {
-                const uint32_t buf = lds0 + (uint32_t)(st % NS) * STAGE + (WSLOT + half * NA) * 1024, k = (uint32_t)st * (KC * 64u);
+                const uint32_t buf = lds0 + (uint32_t)(st % NS) * STAGE + (WSLOT + half * NA) * 1024, k = (uint32_t)(first + at * KC) * 64u;
+                const bool alone = KC == 2 && at * 2 + 1 >= min(whole, g.nkt - kt0 - first);
 #pragma unroll
-                for (int j = 0; j < NA; ++j) lds_load_1k(buf + j * 1024, avo[j] + (KC == 2 && st * 2 + 1 >= ntile ? k - last_odd : k), base);
+                for (int j = 0; j < NA; ++j) lds_load_1k(buf + j * 1024, avo[j] + (alone ? k - last_odd : k), base);
+                if (++at == per_split) at = 0, first += whole;
             };
             for (int st = 0; st < min(NS - 1, nst); ++st) issue(st);
             for (int st = 0; st < nst; ++st) {
@@ -931,8 +941,8 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
                     for (int p = 0; p < P; ++p) ac[p][t] = mm_mfma<NPL>(o.a[u][p], o.b[u][pl][t], ac[p][t]);
     };
     // No branch around the products in the loops: a merge would move every accumulator between register files.
-    const bool odd = KC == 2 && (ntile & 1);              // the last stage holds one k-tile
-    auto last = [&](const Ops &o, floatx16 (&ac)[P][NT]) {
+    auto last = [&](const Ops &o, floatx16 (&ac)[P][NT], int nt) {   // of a split of nt k-tiles: with KC == 2 its last stage may hold one
+        const bool odd = KC == 2 && (nt & 1);
         if (CH == 4) {
             if (!odd || wk == 0) multiply(o, ac, 0, UN);
         } else {
@@ -940,9 +950,11 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
             if (KC == 2 && !odd) multiply(o, ac, 2, UN);
         }
     };
+    const int rb0 = bx * RBW + wn * 2 * P + wk * 2, rb_end = min(g.nrb, (bx + 1) * RBW);
     Ops o0, o1;
     int st = 0;
-    if (AHEAD) {
+    static_assert(NT < 5 || !AHEAD, "several splits per workgroup: the plain loop only");
+    if constexpr (AHEAD) {
         fetch(0, o0);
         for (; st + 2 < nst; st += 2) {
             fetch(st + 1, o1);
@@ -953,17 +965,31 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
         if (st + 1 < nst) {
             fetch(st + 1, o1);
             multiply(o0, acc[0], 0, UN);
-            last(o1, acc[SETS - 1]);
+            last(o1, acc[SETS - 1], ntile);
         } else {
-            last(o0, acc[0]);
+            last(o0, acc[0], ntile);
         }
-    } else if (CH == 1) {
+    } else if constexpr (CH == 1) {
+        // (the only form that takes several splits: see the launcher)
+        for (int sp = 0; sp + 1 < n_split; ++sp) {
+            for (const int end = st + per_split - 1; st < end; ++st) {
+                fetch(st, o0);
+                multiply(o0, acc[0], 0, UN);
+            }
+            fetch(st++, o0);
+            last(o0, acc[0], whole);
+            if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], 0, rb0, split0 + sp, rb0 >> 1, lane, rb_end);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][0][t][e] = 0.f;
+        }
         for (; st + 1 < nst; ++st) {
             fetch(st, o0);
             multiply(o0, acc[0], 0, UN);
         }
         fetch(st, o0);
-        last(o0, acc[0]);
+        last(o0, acc[0], tail);
     } else {
         for (; st + 2 < nst; st += 2) {
             fetch(st, o0);
@@ -975,13 +1001,13 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
         if (st + 1 < nst) {
             multiply(o0, acc[0], 0, UN);
             fetch(st + 1, o0);
-            last(o0, acc[SETS - 1]);
+            last(o0, acc[SETS - 1], ntile);
         } else {
-            last(o0, acc[0]);
+            last(o0, acc[0], ntile);
         }
     }
 
-    const int rb0 = bx * RBW + wn * 2 * P + wk * 2, rb_end = min(g.nrb, (bx + 1) * RBW);
+    const int split = split0 + n_split - 1;
     if constexpr (CH == 4) {
         // wave (wn, wk) holds chains wk and 2 + wk; it hands pair 1 - wk to its partner and finishes pair wk
         floatx4 *red = reinterpret_cast<floatx4 *>(lds);   // [wave][chain][NT][4][64]
@@ -1012,9 +1038,9 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
                     out[0][t][4 * e + i] = wk ? ((p0[i] + m0) + p1[i]) + m1 : ((m0 + p0[i]) + m1) + p1[i];
                 }
             }
-        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, out, m_base, rb0, by, rb0 >> 1, lane, rb_end);
+        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, out, 0, rb0, split, rb0 >> 1, lane, rb_end);
     } else {
-        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], m_base, rb0, by, rb0 >> 1, lane, rb_end);
+        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], 0, rb0, split, rb0 >> 1, lane, rb_end);
     }
 }
 
@@ -1120,9 +1146,13 @@ template <int NT, int KC, int RBW, int CH, int EPI, int NPL> static bool launch_
     g.gx = (g.nrb + RBW - 1) / RBW;
     g.gz = 1;
     g.gs = splits;
+    // More splits than fill the chip once (129 to 160 rows keep the counts that tiles of 512 weight rows asked for: 16 for the
+    // down projection at the 8B shape, 512 workgroups): a workgroup takes several in one pass of the ring.  143 rows: 45 us
+    // as 512 workgroups, 41 in k_gemm_mm, 34.6 as 256 of two splits.
+    g.per = NT == 5 ? std::max(1, std::min(splits, (g.gx * splits + 255) / 256)) : 1;
     static bool allowed[MAX_DEVICES];     // per instantiation
     if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL>), allowed)) return false;
-    const unsigned grid = (unsigned)((g.gx * g.gs + 7) / 8 * 8);
+    const unsigned grid = (unsigned)((g.gx * ((splits + g.per - 1) / g.per) + 7) / 8 * 8);
     hipLaunchKernelGGL((k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL>), dim3(grid), dim3(512), lds, c->stream, g);
     return true;
 }
@@ -1195,10 +1225,8 @@ template <int EPI, int NPL> static bool launch_ws_many_t(Ctx *c, GemmArgs &g, in
 // Wh: the half-precision tiles, or null for the two-term product on the bf16 tiles already in g.Wt
 template <int EPI> static bool launch_ws_many(Ctx *c, GemmArgs &g, int splits, int layout, const void *Wh) {
     // Up to 160 rows (five 32-row tiles: the accumulators of a sixth do not fit a wave's registers) one pass over the
-    // weights in k_gemm_pipe; see there for both sides.  Beyond 128 rows a product whose k-splits were chosen for wide
-    // workgroups (512 weight rows: 16 splits of the down projection at the 8B shape) stays in k_gemm_mm: as 512
-    // workgroups of 128 weight rows it takes 45 us over 143 rows, there 40.
-    const bool pipe = g.M <= PIPE_MAX_ROWS && !(EPI == EPI_PARTIAL && layout == MM_WIDE);
+    // weights in k_gemm_pipe; see there for both sides.
+    const bool pipe = g.M <= PIPE_MAX_ROWS;
     if (Wh && g.X16) {
         g.Wt = (const u32x4 *)Wh;
         if (pipe) return launch_pipe<EPI, 1>(c, g, splits);

@@ -621,3 +621,14 @@ def test_decision_head_forms(base, d_draft, d_head, act, batch, k):
     w = replace(W0 if f32 else configs.get(3), model=replace(base, d_draft=d_draft, d_head_hidden=d_head, head_act=act), batch=batch,
                 ctx=33, k=k, protos=protos, kv_source="synthetic", name=f"head_{d_draft}_{d_head}_b{batch}_k{k}", index=41, taus=(0.5,))
     _run_workload(w, TOL_F32 if f32 else TOL_BF16, kv="synthetic")
+
+
+@pytest.mark.parametrize("one_term", [None, 0])
+def test_several_splits_per_workgroup(one_term):
+    """143 rows against a down projection of 16 k-splits of 25 k-tiles (the last one shorter): 512 workgroups' worth, taken
+    two splits at a time; in the one-term form a split's last stage holds a single k-tile."""
+    m = replace(MID128, n_layers=1, d_model=4096, n_heads=8, n_kv_heads=2, d_ff=12448, vocab=2003)
+    protos = tuple(PROTO_FH if b % 2 == 0 else PROTO_SH for b in range(13))
+    w = replace(configs.get(3), model=m, batch=13, ctx=35, k=11, protos=protos, kv_source="synthetic",
+                name=f"splits_b13_k11_t{one_term}", index=43, taus=(0.5,))
+    _run_workload(w, TOL_BF16, kv="synthetic", one_term=one_term)
