@@ -516,7 +516,7 @@ static int attn_block(const Ctx *c, const Fwd &f) {
     const int rep = g.n_heads / g.n_kv_heads;
     if (!c->bf16 || g.head_dim != HD || rep > 64 || f.rows != f.batch * f.k) return 0;
     if (rep * f.k <= 64) return f.k;
-    return f.batch == 1 ? 64 / rep : 0;
+    return f.prefill ? 64 / rep : 0;   // a round's larger block goes to the generic kernel
 }
 static int attn_splits(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
