@@ -151,8 +151,8 @@ def read_hash(path: str):
     return None
 
 
-# position of the epilogue in the template arguments of the two GEMM kernels, and which class an epilogue means
-_EPI_ARG = {"k_gemm_ws": 6, "k_gemm_mm": 7}
+# position of the epilogue in the template arguments of the three GEMM kernels, and which class an epilogue means
+_EPI_ARG = {"k_gemm_ws": 6, "k_gemm_mm": 6, "k_gemm_pipe": 5}
 _EPI_CLASS = {"0": "gemm_qkv_o_down", "1": "gemm_gate_up", "2": "lm_head", "3": "gemm_qkv_o_down"}
 
 
