@@ -604,12 +604,20 @@ __device__ __forceinline__ void mm_epilogue(const GemmArgs &g, floatx16 (&acc)[R
 // wave; KC: k-tiles per LDS chunk; U: register slots of a wave's weight stream
 // NPL: 2 = activations as two bf16 terms (planes hi and lo, two MFMAs per operand pair); 1 = one half-precision term
 // (plane X16 against half-precision weight tiles, one MFMA per pair: half the matrix-core work and half the staging)
+// SHORT: an accumulator holds one chunk's products only (2 KC NPL of them); finished chunks are added up in a second set of
+// registers.  Every addition to a float sum rounds at the size of the whole sum, so one chain over k rounds 2 NPL times per
+// k-tile at full size, short chains mostly at a fraction of it.  Prompts take this form for their two-term products over k:
+// a bf16 key that lands on the wrong side of a rounding boundary moves every later score of its stream (512 tokens, first
+// layer of the 8B shape: 1 of 2600 cached entries with one chain, 1 of 6200 so, 1 of 6000 and 1 of 5400 with chains of 2 and 4
+// chunks; passes of four rows, whose k is split into 16 slices, 1 of 5500).  The additions hide behind the matrix
+// instructions of the other wave (512 rows: QKV 66.6 -> 69.4 us, down 120.7 -> 123.9).  gate/up keeps one chain: the cache's
+// error does not see it (5.63e-4 either way), and 512 rows would take 253 us in this shape against 197 in the wide one.
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 template <int NPL> __device__ __forceinline__ floatx16 mm_mfma(const u32x4 &a, const u32x4 &b, const floatx16 &c) {
     if (NPL == 2) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&a), *reinterpret_cast<const bf16x8 *>(&b), c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const f16x8 *>(&a), *reinterpret_cast<const f16x8 *>(&b), c, 0, 0, 0);
 }
-template <int NT, int WM, int NW, int RP, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false>
+template <int NT, int WM, int NW, int RP, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false, bool SHORT = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
     extern __shared__ __align__(16) unsigned char lds[];
     static_assert(U % KC == 0, "a turn of the ring is a whole number of chunks");
@@ -654,6 +662,14 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[p][t][e] = 0.f;
+    floatx16 sum[SHORT ? RP : 1][SHORT ? NT : 1];         // SHORT: the finished chains
+    const floatx16 zero = {};
+    if (SHORT) {
+#pragma unroll
+        for (int p = 0; p < RP; ++p)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) sum[p][t] = zero;
+    }
 
     // ---- staging: operand id i in [0, 2 OPS): plane i / OPS, then (k-tile, row tile, op) = ((i % OPS) / (2 NTW),
     //      ((i % OPS) / 2) % NTW, i % 2); wave w takes ids w, w + NW, ...  No load is conditional (a branch would
@@ -687,9 +703,14 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 #define WISV_MM_READ_B(lt, og, DST)                                                                                \
     _Pragma("unroll") for (int t = 0; t < NT; ++t)                                                                 \
         DST[t] = *reinterpret_cast<const u32x4 *>(buf + ((((og) % NPL) * OPS) + (((lt) * NTW + t) * 2 + (og) / NPL)) * 1024);
-#define WISV_MM_GROUP(og, A, SRC)                                                                                  \
-    _Pragma("unroll") for (int t = 0; t < NT; ++t) _Pragma("unroll") for (int p = 0; p < RP; ++p)                  \
-        acc[p][t] = mm_mfma<NPL>(A[p][(og) / NPL], SRC[t], acc[p][t]);
+// (SHORT: the first group of a chunk starts new chains and adds up the old ones, finished a barrier ago)
+#define WISV_MM_GROUP(lt, og, A, SRC)                                                                              \
+    _Pragma("unroll") for (int t = 0; t < NT; ++t) _Pragma("unroll") for (int p = 0; p < RP; ++p) {                \
+        if (SHORT && (lt) == 0 && (og) == 0) {                                                                     \
+            sum[p][t] += acc[p][t];                                                                                \
+            acc[p][t] = mm_mfma<NPL>(A[p][0], SRC[t], zero);                                                       \
+        } else acc[p][t] = mm_mfma<NPL>(A[p][(og) / NPL], SRC[t], acc[p][t]);                                      \
+    }
     u32x4 bv[2][NT];
 
     // One chunk: CC (a compile-time number) places it in a turn of the weight ring, which spans U / KC chunks.
@@ -717,7 +738,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
                     if (og < G - 1) { WISV_MM_READ_B(lt, og + 1, bv[(og + 1) & 1]) }                               \
                     else if (WEAVE && lt + 1 < KC) { WISV_MM_READ_B(lt + 1, 0, bv[0]) }                            \
                     if (!WEAVE) __builtin_amdgcn_sched_barrier(0);                                                 \
-                    WISV_MM_GROUP(og, abuf[(CC) * KC + lt], bv[og & 1])                                            \
+                    WISV_MM_GROUP(lt, og, abuf[(CC) * KC + lt], bv[og & 1])                                        \
                     if (WEAVE && (og < G - 1 || lt + 1 < KC)) {                                                    \
                         /* one LDS read of the next group after every RP matrix instructions of this one */       \
                         _Pragma("unroll") for (int t = 0; t < NT; ++t) {                                           \
@@ -761,6 +782,12 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 #undef WISV_MM_READ_B
 #undef WISV_MM_GROUP
     if (!active) return;
+    if (SHORT) {
+#pragma unroll
+        for (int p = 0; p < RP; ++p)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[p][t] = sum[p][t] + acc[p][t];
+    }
     mm_epilogue<NT, RP, EPI>(g, acc, m_base + wm * (32 * NT), rb0, by, bx * WN + wn, lane);
 }
 
@@ -775,9 +802,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 // Four of the eight waves multiply, the other four only issue loads, two of them the weights and two the activations:
 // issuing one takes tens of cycles, which a multiplying wave loses on the matrix pipe.
 //
-// The order of the sums is that of k_gemm_mm and of the k-slice workgroups this kernel replaced, bit for bit (a token
+// Without SHORT the order of the sums is that of k_gemm_mm and of the k-slice workgroups this kernel replaced, bit for bit (a token
 // of a near-tie, once turned, stays turned).  CH == 1: every output is one chain of products over the workgroup's
-// k-tiles, a wave multiplies 32 weight rows by every row tile.  CH == 4 (at most 64 rows): four chains, k-tile i in
+// k-tiles (SHORT, as in k_gemm_mm: one per stage), a wave multiplies 32 weight rows by every row tile.  CH == 4 (at most 64 rows): four chains, k-tile i in
 // chain i % 4, added as ((0 + 1) + 2) + 3; the waves are 2 x 2, 64 weight rows (wn) and one k-tile of every stage (wk)
 // each, a wave's stages alternate between its two chains, and at the end it hands one of its two row-block pairs to its
 // partner and finishes the other.
@@ -816,10 +843,11 @@ template <int N, int NS> __device__ __forceinline__ void pipe_wait(int left) {
 
 // RBW: row-blocks of weights per workgroup, 8 or 7 (with 7 the last pair's second half is another workgroup's: its
 // products are of whatever the ring holds there and are not written)
-template <int NT, int KC, int NS, int RBW, int CH, int EPI, int NPL>
+template <int NT, int KC, int NS, int RBW, int CH, int EPI, int NPL, bool SHORT = false>
 __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
     extern __shared__ __align__(16) unsigned char lds[];
     static_assert(CH == 1 || (CH == 4 && KC == 2 && NT <= 2), "four chains: a k-tile per wave half and stage");
+    static_assert(!SHORT || CH == 1, "a stage's products are one chain");
     constexpr int WB = RBW * KC, AB = NPL * KC * NT * 2;  // 1 KiB loads of weights / activations in a stage
     constexpr int NW = WB / 2, NA = AB / 2;               // per loading wave
     static_assert(WB % 2 == 0 && AB % 2 == 0, "the two waves of a kind issue the same number of loads");
@@ -931,6 +959,18 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
         }
     };
     auto multiply = [&](const Ops &o, floatx16 (&ac)[P][NT], int u0, int u1) {   // compile-time numbers once inlined
+        if constexpr (SHORT) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                floatx16 chain = {};
+#pragma unroll
+                for (int u = u0; u < u1; ++u)
+#pragma unroll
+                    for (int pl = 0; pl < NPL; ++pl) chain = mm_mfma<NPL>(o.a[u][0], o.b[u][pl][t], chain);
+                ac[0][t] += chain;
+            }
+            return;
+        }
 #pragma unroll
         for (int u = u0; u < u1; ++u)
 #pragma unroll
@@ -1120,7 +1160,7 @@ static bool launch_ws_t(Ctx *c, GemmArgs &g, int splits, size_t soft_budget) {
 constexpr int MM_RP = 2;            // pairs of row-blocks per wave of k_gemm_mm
 constexpr int MM_RB = 2 * MM_RP;
 
-template <int NT, int WM, int NW, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false>
+template <int NT, int WM, int NW, int KC, int U, int EPI, int NPL, bool DEEP = false, bool WEAVE = false, bool SHORT = false>
 static bool launch_mm_t(Ctx *c, GemmArgs &g, int splits) {
     constexpr int WN = NW / WM, NTW = NT * WM;
     g.gx = (g.nrb + WN * MM_RB - 1) / (WN * MM_RB);
@@ -1129,16 +1169,16 @@ static bool launch_mm_t(Ctx *c, GemmArgs &g, int splits) {
     const size_t lds = (size_t)2 * NPL * KC * NTW * 2 * 1024;   // two buffers, NPL planes, 2 operands per (k-tile, row tile)
     static bool allowed[MAX_DEVICES];     // per instantiation
     if (lds > 64 * 1024 &&
-        !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_mm<NT, WM, NW, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE>), allowed))
+        !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_mm<NT, WM, NW, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE, SHORT>), allowed))
         return false;
     const unsigned grid = (unsigned)((g.gx * g.gs + 7) / 8 * 8 * g.gz);
-    hipLaunchKernelGGL((k_gemm_mm<NT, WM, NW, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE>), dim3(grid), dim3(64 * NW), lds, c->stream, g);
+    hipLaunchKernelGGL((k_gemm_mm<NT, WM, NW, MM_RP, KC, U, EPI, NPL, DEEP, WEAVE, SHORT>), dim3(grid), dim3(64 * NW), lds, c->stream, g);
     return true;
 }
 
 // ---- k_gemm_pipe: 128 (or 112) weight rows x one row tile per workgroup
 constexpr int PIPE_RB = 8, PIPE_MAX_ROWS = 160;
-template <int NT, int KC, int RBW, int CH, int EPI, int NPL> static bool launch_pipe_t(Ctx *c, GemmArgs &g, int splits) {
+template <int NT, int KC, int RBW, int CH, int EPI, int NPL, bool SHORT = false> static bool launch_pipe_t(Ctx *c, GemmArgs &g, int splits) {
     constexpr int NS = KC == 2 ? 3 : 4;                        // see the kernel: deeper rings measure the same
     constexpr int STAGE = KC * (8 + NPL * NT * 2);             // KiB
     constexpr size_t lds = (size_t)std::max(NS * STAGE, CH == 4 ? 32 * NT : 0) * 1024;
@@ -1151,9 +1191,9 @@ template <int NT, int KC, int RBW, int CH, int EPI, int NPL> static bool launch_
     // as 512 workgroups, 41 in k_gemm_mm, 34.6 as 256 of two splits.
     g.per = NT == 5 ? std::max(1, std::min(splits, (g.gx * splits + 255) / 256)) : 1;
     static bool allowed[MAX_DEVICES];     // per instantiation
-    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL>), allowed)) return false;
+    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL, SHORT>), allowed)) return false;
     const unsigned grid = (unsigned)((g.gx * ((splits + g.per - 1) / g.per) + 7) / 8 * 8);
-    hipLaunchKernelGGL((k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL>), dim3(grid), dim3(512), lds, c->stream, g);
+    hipLaunchKernelGGL((k_gemm_pipe<NT, KC, NS, RBW, CH, EPI, NPL, SHORT>), dim3(grid), dim3(512), lds, c->stream, g);
     return true;
 }
 template <int NT, int CH, int EPI, int NPL> static bool launch_pipe_nt(Ctx *c, GemmArgs &g, int splits) {
@@ -1222,8 +1262,20 @@ template <int EPI, int NPL> static bool launch_ws_many_t(Ctx *c, GemmArgs &g, in
     }
     return launch_mm_t<2, 2, 8, 2, 2, EPI, NPL>(c, g, splits);
 }
+// Two-term products of a prompt: the same kernels with short chains (see k_gemm_mm), no wide form (its accumulators leave no
+// registers for a second set)
+template <int EPI> static bool launch_short(Ctx *c, GemmArgs &g, int splits) {
+    switch ((g.M + 31) / 32) {
+        case 1: return launch_pipe_t<1, 2, 8, 1, EPI, 2, true>(c, g, splits);
+        case 2: return launch_pipe_t<2, 2, 8, 1, EPI, 2, true>(c, g, splits);
+        case 3: return launch_pipe_t<3, 1, 8, 1, EPI, 2, true>(c, g, splits);
+        case 4: return launch_pipe_t<4, 1, 8, 1, EPI, 2, true>(c, g, splits);
+        case 5: return launch_pipe_t<5, 1, 8, 1, EPI, 2, true>(c, g, splits);
+        default: return launch_mm_t<2, 2, 8, 2, 2, EPI, 2, false, false, true>(c, g, splits);
+    }
+}
 // Wh: the half-precision tiles, or null for the two-term product on the bf16 tiles already in g.Wt
-template <int EPI> static bool launch_ws_many(Ctx *c, GemmArgs &g, int splits, int layout, const void *Wh) {
+template <int EPI> static bool launch_ws_many(Ctx *c, GemmArgs &g, int splits, int layout, const void *Wh, bool short_chains = false) {
     // Up to 160 rows (five 32-row tiles: the accumulators of a sixth do not fit a wave's registers) one pass over the
     // weights in k_gemm_pipe; see there for both sides.
     const bool pipe = g.M <= PIPE_MAX_ROWS;
@@ -1232,6 +1284,8 @@ template <int EPI> static bool launch_ws_many(Ctx *c, GemmArgs &g, int splits, i
         if (pipe) return launch_pipe<EPI, 1>(c, g, splits);
         return launch_ws_many_t<EPI, 1>(c, g, splits, layout);
     }
+    if constexpr (EPI == EPI_PARTIAL)
+        if (short_chains) return launch_short<EPI>(c, g, splits);
     if (pipe) return launch_pipe<EPI, 2>(c, g, splits);
     return launch_ws_many_t<EPI, 2>(c, g, splits, layout);
 }
@@ -1250,13 +1304,14 @@ static void fill_args(GemmArgs &g, const void *Wt, const ActBuf &X, int rows, in
 // Y partial slices: returns the number of slices written to `Yp` ([S][split_stride]), 0 if the shape cannot
 // be served (nothing was launched)
 int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, size_t split_stride, int max_splits,
-                           int rows, int n, int kd, int kclass, const AttnPartials *ap, const void *Wh) {
+                           int rows, int n, int kd, int kclass, const AttnPartials *ap, const void *Wh, bool prompt) {
     ProfScope ps(c, kclass);
     GemmArgs g{};
     fill_args(g, Wt, X, rows, n, kd);
     g.Yp = Yp; g.split_stride = split_stride;
     int s;
     int layout = MM_NORMAL;
+    const bool short_chains = prompt && !(Wh && X.h16);
     if (rows <= 16) {
         // one row-block per wave: split k until about 6144 waves stream (three workgroups per CU), a wave keeps
         // at least 8 k-tiles
@@ -1267,11 +1322,19 @@ int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, s
         const int max_s = std::min(max_splits, std::max(1, g.nkt / 8));
         int rb_per_wg = PIPE_RB, tiles = 1;
         if (rows > 128) {   // (k_gemm_pipe up to 160 rows keeps the split counts of the tiles of 128 rows)
-            layout = mm_layout(rows, g.nrb, g.nkt, true, max_s);
+            layout = short_chains ? MM_NORMAL : mm_layout(rows, g.nrb, g.nkt, true, max_s);
             tiles = mm_shape(rows, layout, &rb_per_wg);
         }
         const int base = ((g.nrb + rb_per_wg - 1) / rb_per_wg) * tiles;
         s = std::max(1, std::min(256 / std::max(1, base), max_s));
+        if (short_chains) {
+            // up to four splits where they come to fewer rounds of 256 workgroups a split: slices are shorter sums (QKV at
+            // the 8B shape over 768 rows, 144 workgroups a split: 1 split 113 us, 2 splits 124, 3 splits 95; over 1000 rows, 192
+            // a split: 115, 127 and 138, 4 splits 117)
+            auto rounds = [&](int t) { return (base * t + 255) / 256; };
+            for (int t = s + 1; t <= std::min(4, max_s); ++t)
+                if (rounds(t) * s < rounds(s) * t + (rows <= PIPE_MAX_ROWS)) s = t;   // (few rows: slices cost little, a tie goes to more)
+        }
     }
     g.kt_per_split = (g.nkt + s - 1) / s;
     const int splits = (g.nkt + g.kt_per_split - 1) / g.kt_per_split;
@@ -1282,7 +1345,7 @@ int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, s
         return launch_ws_t<1, 1, 8, 1, 4, EPI_PARTIAL, PRO_ATTN>(c, g, splits, 40 * 1024) ? splits : 0;
     }
     const bool ok = rows <= 16 ? launch_ws_t<1, 1, 8, 1, 4, EPI_PARTIAL>(c, g, splits, 40 * 1024)
-                               : launch_ws_many<EPI_PARTIAL>(c, g, splits, layout, Wh);
+                               : launch_ws_many<EPI_PARTIAL>(c, g, splits, layout, Wh, short_chains);
     return ok ? splits : 0;
 }
 

@@ -495,7 +495,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
         // have_f: the float plane of X is current (the generic kernel reads that one)
         auto product = [&](const void *wt, const void *w, const void *wh, const ActBuf &X, float *Yp, size_t stride, int n, int kd, int kclass,
                            bool have_f = true) {
-            int ns = launch_gemm_ws_partial(c, wt, X, Yp, stride, max_splits, f.rows, n, kd, kclass, nullptr, wh);
+            int ns = launch_gemm_ws_partial(c, wt, X, Yp, stride, max_splits, f.rows, n, kd, kclass, nullptr, wh, f.prefill);
             if (!ns) {
                 if (!have_f) {
                     c->launch_failed = true;

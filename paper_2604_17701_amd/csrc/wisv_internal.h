@@ -278,8 +278,10 @@ constexpr int WS_PRO_SPLITS = 4;
 // ap != null: X is ignored and the activations are combined from the partials while they are staged (at most 16
 // rows and WS_PRO_SPLITS splits; 0 is returned otherwise)
 // Wh != null: with more than 16 rows the product runs on the half-precision tiles Wh and X.h16 (one MFMA per pair)
+// prompt: with more than 16 rows a two-term product adds up short chains (rounds keep the order of sums they have)
 int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, size_t split_stride, int max_splits,
-                           int rows, int n, int kd, int kclass, const AttnPartials *ap = nullptr, const void *Wh = nullptr);
+                           int rows, int n, int kd, int kclass, const AttnPartials *ap = nullptr, const void *Wh = nullptr,
+                           bool prompt = false);
 int launch_gemm_ws_normfold(Ctx *c, const void *Wt, const float *x_in, float *x_out, int n_partial, const void *gain,
                             float *Yp, size_t split_stride, int max_splits, int rows, int n, int kd, float *ss, int kclass);
 // n_ss > 0: X holds x * gain of a folded RMSNorm and ss the n_ss partial sums of squares per row ([n_ss][rows]); the

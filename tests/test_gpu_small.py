@@ -632,3 +632,31 @@ def test_several_splits_per_workgroup(one_term):
     w = replace(configs.get(3), model=m, batch=13, ctx=35, k=11, protos=protos, kv_source="synthetic",
                 name=f"splits_b13_k11_t{one_term}", index=43, taus=(0.5,))
     _run_workload(w, TOL_BF16, kv="synthetic", one_term=one_term)
+
+
+@pytest.mark.parametrize("n", [96, 160, 300, 777])
+def test_prompt_cache_is_as_exact_in_one_call_as_in_small_steps(n):
+    """The first layer's cached values of a prompt of n tokens against 64 bits, on a context that takes two bf16 terms
+    throughout.  The inputs are exact there (products of two bf16 values), so an entry is off its correctly rounded value
+    only where the rounding of a 32-bit sum over 4096 columns straddles a bf16 boundary, and the share of such entries
+    measures that rounding.  One call must leave no more of them than the same tokens given four per call, whose sums run in
+    16 slices: the two counts may differ by three times the spread (the root of their sum) of a difference of rare events."""
+    dev = torch.device("cuda:0")
+    m = replace(MID128, n_layers=1, d_model=4096, n_heads=32, n_kv_heads=32, d_ff=64, vocab=997)
+    wd = gen.make_weights(m, 5, dev)
+    toks = gen.randint(7, "prompt", (n,), m.vocab).numpy().astype(np.int32)
+    x = wd["embed"][torch.from_numpy(toks).long().to(dev)].double()
+    a = x / torch.sqrt((x * x).mean(-1, keepdim=True) + m.rms_eps) * wd["attn_norm"][0].double()
+    v = (a @ wd["wv"][0].double().t()).to(torch.bfloat16).view(n, m.n_kv_heads, m.head_dim).transpose(0, 1)
+    ctx = binding.Context(m, wd, 1, n + 4, 4)
+    off = []
+    for pieces in ([n], [4] * (n // 4) + ([n % 4] if n % 4 else [])):
+        ctx.wisv_set_state(0, 0, 0)
+        at = 0
+        for p in pieces:
+            ctx.wisv_prefill(0, toks[at:at + p])
+            at += p
+        off.append(int((ctx.wisv_kv_export(0, 0, n)[1].to(dev) != v).sum()))
+    ctx.wisv_destroy()
+    record(f"prompt_first_layer_{n}", {"entries": v.numel(), "off_in_one_call": off[0], "off_in_small_steps": off[1]})
+    assert off[0] - off[1] <= 3 * sum(off) ** 0.5, off
