@@ -1069,6 +1069,10 @@ extern "C" int wisv_get_state(wisv_ctx *ctx, int32_t stream_id, int32_t *kv_len,
     return WISV_OK;
 }
 
+// Enqueues the chunks of a prompt and waits for them; on an error some of them may be on their way, and the slot's length
+// on the device past `len`
+static int prefill_chunks(Ctx *c, const int32_t *stream_id, const int32_t *tokens, int32_t n, int32_t len);
+
 extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tokens, int32_t n) {
     if (!ctx) return WISV_EINVAL;
     Ctx *c = ctx;
@@ -1081,7 +1085,23 @@ extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tok
     if (int rc = wisv_get_state(ctx, stream_id, &len, nullptr)) return rc;
     if (len + n > g.max_ctx) return fail(c, WISV_ESTATE, "prefill of %d tokens at length %d exceeds max_ctx %d", n, len, g.max_ctx);
     c->pending_valid = false;   // the forward below overwrites h^T, the greedy tokens and the row map a VERIFY_ONLY call left
-    HIP_TRY(c, hipMemcpyAsync(c->d_stream_ids, &stream_id, 4, hipMemcpyHostToDevice, c->stream));
+    const int rc = prefill_chunks(c, &stream_id, tokens, n, len);
+    if (rc == WISV_OK) {
+        c->h_len_ub[stream_id] = len + n;
+        return WISV_OK;
+    }
+    // The slot is what it was before the call, and what was enqueued no longer reads the caller's tokens.  Should that fail
+    // too, the host's bound stays above whatever length the device may hold.
+    c->h_len_ub[stream_id] = len + n;
+    (void)hipGetLastError();
+    launch_set_pred_next(c, stream_id, -1, len);
+    if (hipGetLastError() == hipSuccess && hipStreamSynchronize(c->stream) == hipSuccess) c->h_len_ub[stream_id] = len;
+    (void)hipGetLastError();   // reported by rc, not by the next call
+    return rc;
+}
+
+static int prefill_chunks(Ctx *c, const int32_t *stream_id, const int32_t *tokens, int32_t n, int32_t len) {
+    HIP_TRY(c, hipMemcpyAsync(c->d_stream_ids, stream_id, 4, hipMemcpyHostToDevice, c->stream));
     // Chunks of up to prefill_rows rows, as even as possible (whole 32-row tiles).  Where rounds run with one
     // half-precision term beyond 16 rows, up to 16 tokens left over from whole blocks of rows_max keep two terms: they
     // are a pass of their own.
@@ -1103,16 +1123,11 @@ extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tok
         f.want_last = c0 + rows == n;
         c->launch_failed = false;
         enqueue_forward(c, f);
-        if (c->launch_failed) {   // a chunk is not served: the slot is what it was before the call
-            launch_set_pred_next(c, stream_id, -1, len);
-            HIP_TRY(c, hipStreamSynchronize(c->stream));
-            return fail(c, WISV_EUNSUPPORTED, "%s", c->launch_err.c_str());
-        }
+        if (c->launch_failed) return fail(c, WISV_EUNSUPPORTED, "%s", c->launch_err.c_str());
         HIP_TRY(c, hipGetLastError());
-        launch_set_pred_next(c, stream_id, f.want_last ? 0 : -1, len + c0 + rows);
+        launch_set_pred_next(c, *stream_id, f.want_last ? 0 : -1, len + c0 + rows);
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));   // the caller's tokens have been read, the slot's state is final
-    c->h_len_ub[stream_id] = len + n;
     return WISV_OK;
 }
 
