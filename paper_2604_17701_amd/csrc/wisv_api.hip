@@ -47,6 +47,17 @@ struct IoOut {
         return p;
     }
 };
+// A host-pointer round that has begun to enqueue: whichever way it ends, its copies have read the caller's buffers and
+// the pinned arguments, which the next call overwrites, before it returns
+struct HostCall {
+    Ctx *c;
+    bool open = false;
+    ~HostCall() {
+        if (!open) return;
+        (void)hipStreamSynchronize(c->stream);
+        (void)hipGetLastError();   // this call's error, not the next one's
+    }
+};
 
 namespace wisv {
 
@@ -701,7 +712,9 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
     HIP_TRY(c, hipSetDevice(g.device_id));
     wisv_round_in din = *in;
     wisv_round_out dout = *out;
+    HostCall host{c};
     if (!dev_io) {
+        host.open = true;
         IoPack pack{c};
         const size_t hd_bytes = (size_t)in->n_hd * g.d_draft * c->esz;
         din.stream_ids = (const int32_t *)pack.add(in->stream_ids, (size_t)B * 4);
@@ -815,6 +828,7 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
 
     if (!dev_io) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
+        host.open = false;
         memcpy(out->correction_token, dout.correction_token, (size_t)B * 4);
         memcpy(out->p_accept, dout.p_accept, (size_t)R * 4);
         if (out->target_argmax) memcpy(out->target_argmax, dout.target_argmax, (size_t)B * (K + 1) * 4);
@@ -886,7 +900,9 @@ extern "C" int wisv_ss_verify_round(wisv_ctx *ctx, const wisv_ss_in *in, wisv_ss
     a.logits = c->logits;
     a.pending_tokens = nullptr;
     a.commit = commit;
+    HostCall host{c};
     if (!dev_io) {
+        host.open = true;
         if (!c->d_ss_q) HIP_TRY(c, dalloc(c, &c->d_ss_q, (size_t)c->rows_max * V));
         HIP_TRY(c, hipMemcpyAsync(c->d_ss_q, in->draft_probs, (size_t)R * V * 4, hipMemcpyHostToDevice, c->stream));
         IoPack pack{c};
@@ -934,6 +950,7 @@ extern "C" int wisv_ss_verify_round(wisv_ctx *ctx, const wisv_ss_in *in, wisv_ss
         HIP_TRY(c, hipMemcpyAsync(out->correction_token, c->d_ytok, B * 4, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipMemcpyAsync(out->alpha, c->d_pacc, R * 4, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
+        host.open = false;
         if (commit)
             for (int b = 0; b < B; ++b) c->h_len_ub[in->stream_ids[b]] += out->accepted_len[b];
     } else if (commit) {

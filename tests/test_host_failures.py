@@ -116,3 +116,26 @@ def test_prompt_that_fails_half_way_leaves_the_slot_as_it_was(stub):
     assert state(h) == (0, 0) and verify(h, SMALL, 1, 4) == B.WISV_OK
     lib.wisv_destroy(h)
     """)
+
+
+@pytest.mark.parametrize("call", ["verify", "ss_verify"])
+@pytest.mark.parametrize("how", ["refused", "record"])
+def test_failed_host_pointer_round_has_read_its_arguments(stub, call, how):
+    """A host-pointer round that fails after its packed arguments were enqueued for copying must wait for that copy: the
+    next call packs its own arguments into the same pinned memory.  Once because a product is not served (32 rows want
+    more LDS than the runtime grants here), once because an event cannot be recorded."""
+    _run(stub, f"""
+    h = create(SMALL, 8, 64, 4)
+    if {how == "refused"}:
+        stub.stub_refuse_lds(1)
+    else:
+        stub.stub_fail(0, 0, {2 if how == "record" else 0})   # the record that ends the round
+    stub.stub_log_clear()
+    rc = {call}(h, SMALL, 8, 4)
+    assert rc == (B.WISV_EUNSUPPORTED if {how == "refused"} else B.WISV_EHIP), rc
+    l = log()
+    assert any("k_unpack" in x for x in l) and l[-1] == "sync", l[-3:]
+    stub.stub_refuse_lds(0)
+    assert {call}(h, SMALL, 8, 4) == B.WISV_OK
+    lib.wisv_destroy(h)
+    """)
