@@ -826,10 +826,10 @@ __device__ __forceinline__ const unsigned char *scalar_ptr(const void *p) {
 }
 // lane l: 16 bytes from base + voff to lds_addr + 16 l
 __device__ __forceinline__ void lds_load_1k(uint32_t lds_addr, uint32_t voff, const void *base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_load_1k_nt(uint32_t lds_addr, uint32_t voff, const void *base) {   // read once: streamed
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
 }
 // at most `left` stages of N loads each may still be on their way; then meet the other waves
 template <int N, int NS> __device__ __forceinline__ void pipe_wait(int left) {

@@ -130,3 +130,15 @@ def test_profile_summaries_parse_and_name_the_kernels_bench_looks_for():
     assert ps.kernel_class("k_gemm_mm<4, 1, 8, 1, 2, 2, 2, 2, 1>") == "lm_head"
     assert ps.kernel_class("k_attn_mfma<1, 8, true>") == "attention"
     assert ps.template_args("k_decide") == ("k_decide", []) and ps.kernel_class("k_decide") is None
+
+
+def test_inline_assembly_names_the_register_it_writes():
+    """An asm statement that writes m0 must say so: the compiler keeps LDS offsets and lane indices of its own there."""
+    csrc, found = os.path.join(ROOT, "paper_2604_17701_amd", "csrc"), 0
+    for name in sorted(os.listdir(csrc)):
+        with open(os.path.join(csrc, name)) as f:
+            for stmt in re.findall(r"\basm\b[^;]*;", f.read()):
+                if re.search(r"s_mov_b32 m0", stmt):
+                    found += 1
+                    assert re.search(r':\s*"memory",\s*"m0"\)', stmt), (name, stmt)
+    assert found >= 2
