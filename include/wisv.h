@@ -270,7 +270,10 @@ int wisv_get_option(wisv_ctx *ctx, int32_t option, int64_t *value);
 /* --- state helpers --------------------------------------------------------------------------- */
 
 /* Runs the target over n prompt tokens (host pointer) of an empty or partly filled slot with the
- * round's own kernels, appends their K/V, and sets pred_next to the greedy token after the last. */
+ * round's own kernels, appends their K/V, and sets pred_next to the greedy token after the last.  A prompt of more
+ * than max_batch * max_k tokens runs in buffers that the first such call allocates (8B shape: about 0.35 GB for 1024 tokens,
+ * the largest chunk) and the ctx keeps; where the device has no room for them it runs in smaller chunks.  A call that
+ * fails leaves the slot as it was. */
 int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tokens, int32_t n);
 
 /* Sets a slot's cached length and pred_next directly (cache contents: wisv_kv_import). */

@@ -17,7 +17,7 @@ struct wisv_ctx : public wisv::Ctx {};
 // Rows of one prefill chunk: a prompt is bound by the weight stream while a chunk is short (a pass costs the same up to
 // a few dozen rows) and by the matrix cores beyond some hundred.  Measured on four layers of the 8B shape, 1999 tokens:
 // chunks of 96 rows with the generic attention kernel 82.6 ms; of 512 rows 6.08 ms, 1024 rows 5.52 ms, 2048 rows
-// 5.25 ms.  512 tokens in chunks of 4 rows 62.3 ms, in one chunk 2.15 ms.  The buffers of 1024 rows hold about 0.5 GB
+// 5.25 ms.  512 tokens in chunks of 4 rows 62.3 ms, in one chunk 2.15 ms.  The buffers of 1024 rows hold about 0.35 GB
 // at the 8B shape; doubling them would buy 5 %.
 constexpr int PREFILL_ROWS = 1024;
 
@@ -158,12 +158,49 @@ static void destroy_ctx(Ctx *c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     for (void *p : c->owned) (void)hipFree(p);
+    if (c->prompt_mem) (void)hipFree(c->prompt_mem);
     if (c->io_in) (void)hipHostFree(c->io_in);
     if (c->stream_owned) (void)hipStreamDestroy(c->stream);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->ev_round[0]) (void)hipEventDestroy(c->ev_round[0]);
     if (c->ev_round[1]) (void)hipEventDestroy(c->ev_round[1]);
     delete static_cast<wisv_ctx *>(c);
+}
+
+// The buffers of a forward of up to `rows` rows, each from alloc(bytes); stops at the first null
+template <typename Alloc> static bool make_scratch(const Ctx *c, Scratch &s, int rows, Alloc alloc) {
+    const wisv_config &g = c->cfg;
+    bool ok = true;
+    auto put = [&](auto *&p, size_t n) {
+        p = ok ? static_cast<std::remove_reference_t<decltype(p)>>(alloc(n * sizeof(*p))) : nullptr;
+        ok = ok && p;
+    };
+    const size_t R = rows, d = g.d_model, F = g.d_ff;
+    // the matrix-core path writes and reads float planes up to 16 rows only
+    const size_t float_rows = c->ws_ok ? std::min<size_t>(R, 16) : R;
+    // a round's products may leave MAX_SPLITS slices; a prompt's hundreds of rows fill the chip with four
+    s.slice_cap = rows <= c->rows_max ? MAX_SPLITS * rows : std::min(MAX_SPLITS * rows, std::max(4 * rows, 4096));
+    put(s.d_tokens, R);
+    put(s.row_slot, R);
+    put(s.row_pos, R);
+    put(s.x, R * d);
+    put(s.x_alt, R * d);
+    put(s.y, s.slice_cap * d);
+    put(s.qkv, (size_t)s.slice_cap * c->d_qkv);
+    put(s.gu, float_rows * 2 * F);
+    put(s.q, R * c->d_q);
+    put(s.ss, MAX_SPLITS * std::max<size_t>(R, 16));
+    auto act = [&](ActBuf &b, size_t width) {
+        put(b.f, float_rows * width);
+        put(b.hi, R * width);
+        put(b.lo, R * width);
+        if (c->half_ok) put(b.h16, R * width);
+        else b.h16 = nullptr;
+    };
+    act(s.a, d);
+    act(s.o, c->d_q);
+    act(s.h, F);
+    return ok;
 }
 
 // ------------------------------------------------------------------------------------------ create / destroy
@@ -201,8 +238,6 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     c->d_kv = config->n_kv_heads * config->head_dim;
     c->d_qkv = c->d_q + 2 * c->d_kv;
     c->rows_max = config->max_batch * config->max_k;
-    c->prefill_rows = std::min(PREFILL_ROWS, c->ctx_pad);
-    c->slice_cap = std::max(MAX_SPLITS * c->rows_max, 4 * c->prefill_rows);
     c->slice_rows = c->rows_max;
     c->profiling = false;
     c->ev_used = 0;
@@ -233,7 +268,6 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     const wisv_config &g = c->cfg;
     const size_t esz = c->esz;
     const int d = g.d_model, F = g.d_ff, V = g.vocab, R = c->rows_max;
-    const int RF = std::max(R, c->prefill_rows);   // rows of a forward
     CREATE_TRY(hipSetDevice(g.device_id));
     if (!c->stream) {
         CREATE_TRY(hipStreamCreate(&c->stream));
@@ -404,7 +438,6 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
         CREATE_TRY(dalloc(c, &c->d_in, c->io_in_bytes));
     }
     CREATE_TRY(dalloc(c, &c->d_stream_ids, g.max_batch));
-    CREATE_TRY(dalloc(c, &c->d_tokens, RF));
     CREATE_TRY(dalloc(c, &c->d_hd_row, R));
     {
         char *p;
@@ -414,39 +447,26 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     CREATE_TRY(dalloc(c, &c->d_alen, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_ytok, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_pacc, R));
-    CREATE_TRY(dalloc(c, &c->row_slot, RF));
-    CREATE_TRY(dalloc(c, &c->row_pos, RF));
     CREATE_TRY(dalloc(c, &c->amax, R));
     CREATE_TRY(dalloc(c, &c->scored, R));
-    CREATE_TRY(dalloc(c, &c->x, (size_t)RF * d));
-    CREATE_TRY(dalloc(c, &c->x_alt, (size_t)RF * d));
-    CREATE_TRY(dalloc(c, &c->ss, std::max((size_t)MAX_SPLITS * std::max(R, 16), (size_t)RF)));
+    {
+        hipError_t e = hipSuccess;
+        make_scratch(c, *c, R, [&](size_t bytes) -> void * {
+            char *p;
+            e = dalloc(c, &p, bytes);
+            return p;
+        });
+        CREATE_TRY(e);
+    }
     CREATE_TRY(dalloc(c, &c->ss2, (size_t)((d + 15) / 16) * 16));
     c->graph_refused = false;
-    CREATE_TRY(dalloc(c, &c->y, (size_t)c->slice_cap * d));
-    CREATE_TRY(dalloc(c, &c->qkv, (size_t)c->slice_cap * c->d_qkv));
     {
         const size_t n_cand = ws_padded_row_blocks(V);
         CREATE_TRY(dalloc(c, &c->cand_val, (size_t)R * n_cand));
         CREATE_TRY(dalloc(c, &c->cand_idx, (size_t)R * n_cand));
     }
-    CREATE_TRY(dalloc(c, &c->gu, (size_t)(c->ws_ok ? std::min(RF, 16) : RF) * 2 * F));   // read by the generic kernels only
     CREATE_TRY(dalloc(c, &c->h_t, (size_t)R * d));
     CREATE_TRY(dalloc(c, &c->hu, (size_t)((g.d_head_hidden + 15) / 16) * R));   // the head's partial sums [row-block][row]
-    // (beyond 16 rows the matrix-core path never writes or reads a float plane)
-    auto act_alloc = [&](ActBuf *a, size_t rows, size_t width, bool half) -> hipError_t {
-        const size_t n = rows * width;
-        hipError_t e = dalloc(c, &a->f, c->ws_ok ? std::min<size_t>(rows, 16) * width : n);
-        if (e == hipSuccess) e = dalloc(c, &a->hi, n);
-        if (e == hipSuccess) e = dalloc(c, &a->lo, n);
-        a->h16 = nullptr;
-        if (e == hipSuccess && half) e = dalloc(c, &a->h16, n);
-        return e;
-    };
-    CREATE_TRY(act_alloc(&c->a, RF, d, c->half_ok));
-    CREATE_TRY(act_alloc(&c->o, RF, c->d_q, c->half_ok));
-    CREATE_TRY(act_alloc(&c->h, RF, F, c->half_ok));
-    CREATE_TRY(dalloc(c, &c->q, (size_t)RF * c->d_q));
     {
         // split-KV attention partials: as many splits of the largest round as fit 64 MiB, at most 64
         const size_t per_split = (size_t)R * c->d_q;
@@ -1117,14 +1137,61 @@ extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tok
     return rc;
 }
 
+// Buffers for chunks of up to `want` rows; returns how many rows a chunk may have.  They belong to no round, so a ctx
+// that ingests no prompt holds none, and where the device has no room for them a prompt runs in smaller chunks, down to
+// those of a round.  (Rounds captured in a graph keep their own buffers: these may move.)
+static int prompt_chunk_rows(Ctx *c, int want) {
+    if (want <= c->rows_max) return want;
+    if (want > c->prompt_rows) {
+        if (c->prompt_mem) (void)hipFree(c->prompt_mem);   // nothing is using them: every prompt ends with a wait
+        c->prompt_mem = nullptr;
+        c->prompt_rows = 0;
+        for (int rows = want; rows > c->rows_max; rows = (rows / 2 + 31) / 32 * 32) {
+            // one block, laid out at a stand-in address to learn its size, then where it is.  Buffers of megabytes begin on
+            // 2 MB, as blocks of their own would (1999 tokens: 5.53 ms; on the next 256 bytes 5.57)
+            char *base = (char *)4096;
+            size_t used = 0;
+            auto carve = [&](size_t bytes) -> void * {
+                const size_t align = bytes >= (2u << 20) ? 2u << 20 : 256, at = (used + align - 1) / align * align;
+                used = at + bytes;
+                return base + at;
+            };
+            make_scratch(c, c->prompt, rows, carve);
+            if (hipMalloc(&c->prompt_mem, used) == hipSuccess) {
+                base = (char *)c->prompt_mem;
+                used = 0;
+                make_scratch(c, c->prompt, rows, carve);
+                c->prompt_rows = rows;
+                break;
+            }
+            (void)hipGetLastError();   // no room: not this call's error
+            c->prompt_mem = nullptr;
+            if (rows <= 32) break;
+        }
+    }
+    return c->prompt_rows ? std::min(want, c->prompt_rows) : c->rows_max;
+}
+
+// The buffers of a prompt in the place of the rounds' ones, for the length of a call
+struct UsePromptScratch {
+    Ctx *c;
+    const Scratch own;
+    UsePromptScratch(Ctx *c, bool on) : c(c), own(*c) {
+        if (on) static_cast<Scratch &>(*c) = c->prompt;
+    }
+    ~UsePromptScratch() { static_cast<Scratch &>(*c) = own; }
+};
+
 static int prefill_chunks(Ctx *c, const int32_t *stream_id, const int32_t *tokens, int32_t n, int32_t len) {
+    const int max_rows = prompt_chunk_rows(c, std::min(std::min(PREFILL_ROWS, c->ctx_pad), (n + 31) / 32 * 32));
+    UsePromptScratch use(c, max_rows > c->rows_max);
     HIP_TRY(c, hipMemcpyAsync(c->d_stream_ids, stream_id, 4, hipMemcpyHostToDevice, c->stream));
-    // Chunks of up to prefill_rows rows, as even as possible (whole 32-row tiles).  Where rounds run with one
+    // Chunks of up to max_rows rows, as even as possible (whole 32-row tiles).  Where rounds run with one
     // half-precision term beyond 16 rows, up to 16 tokens left over from whole blocks of rows_max keep two terms: they
     // are a pass of their own.
     const int rest = c->half_ok && n % c->rows_max <= 16 ? n % c->rows_max : 0, body = n - rest;
-    const int n_chunks = (body + c->prefill_rows - 1) / c->prefill_rows;
-    const int chunk = body ? std::min(c->prefill_rows, ((body + n_chunks - 1) / n_chunks + 31) / 32 * 32) : 0;
+    const int n_chunks = (body + max_rows - 1) / max_rows;
+    const int chunk = body ? std::min(max_rows, ((body + n_chunks - 1) / n_chunks + 31) / 32 * 32) : 0;
     for (int c0 = 0, rows; c0 < n; c0 += rows) {
         rows = c0 < body ? std::min(chunk, body - c0) : rest;
         HIP_TRY(c, hipMemcpyAsync(c->d_tokens, tokens + c0, rows * 4, hipMemcpyHostToDevice, c->stream));

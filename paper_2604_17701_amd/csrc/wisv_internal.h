@@ -113,7 +113,20 @@ struct LayerW {
 // product classes whose many-rows kernel may take its activations as one half-precision term (wisv_set_option)
 enum { TERM_QKV = 1, TERM_O = 2, TERM_GATE_UP = 4, TERM_DOWN = 8, TERM_LM_HEAD = 16, TERM_ALL = 31 };
 
-struct Ctx {
+// The buffers a forward runs through.  The rounds of a ctx own one set, sized for the largest of them; a prompt's chunk
+// of more rows runs in another.
+struct Scratch {
+    int32_t *d_tokens;            // a prompt's tokens
+    int32_t *row_slot, *row_pos;
+    float *x, *x_alt;             // residual stream; a product that folds the norm in reads x and writes x_alt
+    float *y, *qkv;               // slice_cap rows of partial slices each
+    int slice_cap;                // k-split slices x rows that y and qkv hold
+    float *gu, *q;                // generic kernels: gate and up; rotated queries [rows][d_q]
+    float *ss;                    // [MAX_SPLITS][max(rows, 16)]: sums of squares left by a product that folds the norm in
+    ActBuf a, o, h;               // normalised activations, attention output, SwiGLU output
+};
+
+struct Ctx : Scratch {
     wisv_config cfg;
     hipStream_t stream;
     bool stream_owned;   // no stream was given: the ctx made its own (the null stream cannot be captured)
@@ -126,8 +139,6 @@ struct Ctx {
     bool bf16;
     size_t esz;          // bytes per weight / cache element
     int d_q, d_kv, d_qkv, rows_max;
-    int prefill_rows;    // rows of one prefill chunk (>= 1): the forward's buffers hold max(rows_max, prefill_rows)
-    int slice_cap;       // k-split slices x rows that y and qkv hold
     int slice_rows;      // rows of one slice in the forward being enqueued (== its row count)
 
     // parameters (private copies)
@@ -152,8 +163,13 @@ struct Ctx {
     int32_t *d_kv_len, *d_pred_next;
     std::vector<int32_t> h_len_ub;
 
-    // a prompt's slot and tokens; the row map of a round without uploads; uploaded hidden states too large to be packed
-    int32_t *d_stream_ids, *d_tokens, *d_hd_row;
+    // buffers of prompts of more than rows_max tokens: one allocation, made by the first such prompt and grown by longer ones
+    Scratch prompt;
+    void *prompt_mem;
+    int prompt_rows;              // rows they hold; 0: none
+
+    // a prompt's slot; the row map of a round without uploads; uploaded hidden states too large to be packed
+    int32_t *d_stream_ids, *d_hd_row;
     void *d_hd;
     // host-pointer mode: a round's inputs are packed into io_in (pinned host memory the GPU can read), which a kernel
     // copies to d_in as it is; the last kernel writes the results straight into io_out (pinned as well)
@@ -164,16 +180,12 @@ struct Ctx {
     float *d_pacc;
 
     // scratch
-    int32_t *row_slot, *row_pos, *amax, *scored;
-    float *x, *y, *qkv, *gu, *h_t, *logits;   // y and qkv hold slice_cap rows of partial slices
-    float *x_alt;                 // second residual-stream buffer: a product that folds the norm in reads x and writes here
-    float *ss;                    // [MAX_SPLITS][max(rows_max, 16)], or one per row of a prompt's chunk: sums of squares left by such a product
+    int32_t *amax, *scored;
+    float *h_t, *logits;
     float *ss2;                   // [d_model / 16][16]: those of the O projection that folds the FFN norm in
     bool graph_refused;           // a capture of the round failed once: later rounds run eagerly without trying again
     float *cand_val;
     int32_t *cand_idx;
-    float *q;                     // rotated queries [rows][d_q]
-    ActBuf a, o, h;               // normalised activations, attention output, SwiGLU output
     int o_planes;                 // ACT_*: the representations of o that this round's attention kernels write
     float *hu;                    // decision head: second-layer partial sums [row-block of hidden units][row]
     float *att_o, *att_m, *att_l; // split-KV attention partials: [split][rows][heads][head_dim], [split][rows][heads]

@@ -660,3 +660,32 @@ def test_prompt_cache_is_as_exact_in_one_call_as_in_small_steps(n):
     ctx.wisv_destroy()
     record(f"prompt_first_layer_{n}", {"entries": v.numel(), "off_in_one_call": off[0], "off_in_small_steps": off[1]})
     assert off[0] - off[1] <= 3 * sum(off) ** 0.5, off
+
+
+def test_prompts_leave_captured_rounds_alone():
+    """A device-buffer round that has become a graph keeps its buffers: prompts of growing length (other buffers, allocated
+    and replaced by longer ones) run between its replays, and every replay equals the first, eager run."""
+    dev = torch.device("cuda:0")
+    w = replace(configs.get(3), model=MID128, batch=3, ctx=40, k=4, protos=(PROTO_FH,) * 3, name="graph_prompts", index=47)
+    ctx = _ctx(w, gen.make_weights(w.model, w.seed, dev), max_batch=4, extra_ctx=400)
+    for b in range(3):
+        ctx.wisv_prefill(b, gen.context_tokens(w, b))
+    ids = [gen.randint(11, f"prompt{i}", (n,), w.model.vocab).numpy().astype(np.int32) for i, n in enumerate((10, 60, 200, 390, 30))]
+    hd, row_map = gen.pack_hidden(w, [gen.draft_hidden(w, b) for b in range(3)], [list(range(4))] * 3)
+    drafts = np.random.default_rng(5).integers(0, w.model.vocab, 12).astype(np.int32)
+    args = (np.arange(3), drafts, w.protos, hd, row_map, gen.csi_features(w), np.full(3, 0.5, np.float32), 4, binding.WISV_FLAG_NO_COMMIT)
+    ctx.wisv_set_state(3, 390, 0)          # the longest length there will be: the bound that sizes the launches stays put
+    rnd = ctx.device_round(*args)
+    want = None
+    for it in range(7):
+        rnd.run()
+        got = rnd.results()
+        want = want or got             # the first run is eager
+        for name in ("accepted_len", "correction_token", "target_argmax", "mismatch_mask", "status", "p_accept"):
+            assert np.array_equal(np.asarray(got[name]).reshape(-1), np.asarray(want[name]).reshape(-1)), (it, name)
+        if it < len(ids):
+            ctx.wisv_set_state(3, 0, 0)
+            ctx.wisv_prefill(3, ids[it])
+            assert ctx.wisv_get_state(3)[0] == ids[it].size
+            ctx.wisv_set_state(3, 390, 0)
+    ctx.wisv_destroy()

@@ -139,3 +139,41 @@ def test_failed_host_pointer_round_has_read_its_arguments(stub, call, how):
     assert {call}(h, SMALL, 8, 4) == B.WISV_OK
     lib.wisv_destroy(h)
     """)
+
+
+def test_prompt_buffers_are_not_part_of_the_context(stub):
+    """What a ctx allocates depends on its rounds, not on how long its prompts may be; the first long prompt allocates its
+    buffers, a device without room for them still ingests it (in chunks of half the rows, down to those of a round), and
+    wisv_destroy gives everything back."""
+    _run(stub, """
+    def chunks(h, n):
+        stub.stub_log_clear()
+        lib.wisv_set_state(h, 0, 0, 0)
+        assert prefill(h, n) == B.WISV_OK and state(h)[0] == n
+        return sum("k_set_pred_next" in x for x in log())
+
+    for model in (SMALL, configs.TINY):
+        e = 2 if model.dtype == "bf16" else 4
+        def grown(max_ctx):
+            h = create(model, 1, max_ctx, 4)
+            return h, stub.stub_used()
+        h, small = grown(64)
+        lib.wisv_destroy(h)
+        assert stub.stub_used() == 0
+        h, large = grown(1024)
+        per_token = model.n_layers * 2 * model.n_kv_heads * model.head_dim * e + 2 * (model.head_dim // 2) * 4   # cache, rotary tables
+        assert large - small == (1024 - 64) * per_token, (large - small, per_token)
+        stub.stub_limit(large)
+        assert chunks(h, 600) == 150 and stub.stub_used() == large       # no room at all: a round's four rows at a time
+        stub.stub_limit(2 ** 62)
+        assert chunks(h, 600) == 1
+        full = stub.stub_used() - large
+        assert chunks(h, 90) == 1 and stub.stub_used() - large == full   # kept, not grown
+        lib.wisv_destroy(h)
+        assert stub.stub_used() == 0
+        h, large = grown(1024)
+        stub.stub_limit(large + full - 1)
+        assert chunks(h, 600) == 2 and stub.stub_used() < large + full   # half the rows
+        lib.wisv_destroy(h)
+        assert stub.stub_used() == 0
+    """)
