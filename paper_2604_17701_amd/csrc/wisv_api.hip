@@ -680,6 +680,15 @@ static int check_round(Ctx *c, const wisv_round_in *in, const wisv_round_out *ou
     return WISV_OK;
 }
 
+// A commit of up to k tokens per stream is on its way (stream_ids null: of any streams).  A host-pointer round takes back
+// what was not accepted once it has the results.
+static void raise_len_bounds(Ctx *c, const int32_t *stream_ids, int batch, int k) {
+    if (stream_ids)
+        for (int b = 0; b < batch; ++b) c->h_len_ub[stream_ids[b]] += k;   // checked: within max_ctx
+    else
+        for (int &n : c->h_len_ub) n = std::min(n + k, c->cfg.max_ctx);
+}
+
 extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_round_out *out) {
     if (!ctx) return WISV_EINVAL;
     Ctx *c = ctx;
@@ -842,6 +851,7 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
         c->graph_len_ub = -1;
         return fail(c, WISV_EUNSUPPORTED, "%s", c->launch_err.c_str());
     }
+    if (commit) raise_len_bounds(c, dev_io ? nullptr : in->stream_ids, B, K);
     HIP_TRY(c, hipEventRecord(c->ev_round[1], c->stream));
     HIP_TRY(c, hipGetLastError());
     c->last_rows = R;
@@ -856,7 +866,7 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
         if (out->status) memcpy(out->status, dout.status, (size_t)B * 4);
         for (int b = 0; b < B; ++b) {
             out->accepted_len[b] = dout.accepted_len[b];
-            if (commit) c->h_len_ub[in->stream_ids[b]] += dout.accepted_len[b];
+            if (commit) c->h_len_ub[in->stream_ids[b]] -= K - dout.accepted_len[b];
         }
         if (verify_only) {
             c->pending_valid = true;
@@ -865,8 +875,6 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
             c->pending_ids.assign(in->stream_ids, in->stream_ids + B);
             c->pending_tokens.assign(in->draft_tokens, in->draft_tokens + R);
         }
-    } else if (commit) {
-        for (int s = 0; s < g.max_batch; ++s) c->h_len_ub[s] = std::min(c->h_len_ub[s] + K, g.max_ctx);
     }
     return WISV_OK;
 }
@@ -961,6 +969,7 @@ extern "C" int wisv_ss_verify_round(wisv_ctx *ctx, const wisv_ss_in *in, wisv_ss
     enqueue_forward(c, f);
     if (c->launch_failed) return fail(c, WISV_EUNSUPPORTED, "%s", c->launch_err.c_str());
     launch_ss(c, a);
+    if (commit) raise_len_bounds(c, dev_io ? nullptr : in->stream_ids, B, K);
     HIP_TRY(c, hipEventRecord(c->ev_round[1], c->stream));
     HIP_TRY(c, hipGetLastError());
     c->last_rows = R;
@@ -972,9 +981,7 @@ extern "C" int wisv_ss_verify_round(wisv_ctx *ctx, const wisv_ss_in *in, wisv_ss
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         host.open = false;
         if (commit)
-            for (int b = 0; b < B; ++b) c->h_len_ub[in->stream_ids[b]] += out->accepted_len[b];
-    } else if (commit) {
-        for (int s = 0; s < g.max_batch; ++s) c->h_len_ub[s] = std::min(c->h_len_ub[s] + K, g.max_ctx);
+            for (int b = 0; b < B; ++b) c->h_len_ub[in->stream_ids[b]] -= K - out->accepted_len[b];
     }
     return WISV_OK;
 }

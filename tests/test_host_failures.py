@@ -177,3 +177,18 @@ def test_prompt_buffers_are_not_part_of_the_context(stub):
         lib.wisv_destroy(h)
         assert stub.stub_used() == 0
     """)
+
+
+@pytest.mark.parametrize("call", ["verify", "ss_verify"])
+def test_round_that_fails_after_its_commit_keeps_the_length_bound(stub, call):
+    """The kernel that commits a round may have moved the stream's length when recording the round's last event fails: later
+    rounds are checked against a bound that counts the whole block, until the state is read back."""
+    _run(stub, f"""
+    h = create(SMALL, 1, 64, 4)
+    lib.wisv_set_state(h, 0, 60, 0)
+    stub.stub_fail(0, 0, 2)
+    assert {call}(h, SMALL, 1, 4) == B.WISV_EHIP
+    assert {call}(h, SMALL, 1, 4) == B.WISV_ESTATE
+    assert state(h) == (60, 0) and {call}(h, SMALL, 1, 4) == B.WISV_OK
+    lib.wisv_destroy(h)
+    """)
