@@ -138,7 +138,7 @@ def test_config4_batch64_ctx8192_k8_mixed_protocols(target8b):
 
 
 def test_8b_shape_real_prefill_then_round(target8b):
-    """The cache of the headline shape filled by the library's own prefill (the round's kernels in K-row chunks)
+    """The cache of the headline shape filled by the library's own prefill (one chunk of 64 rows, two bf16 terms)
     instead of synthetic contents: the oracle prefills the same 64 tokens itself, and the two sides are compared
     cache to cache (three layers, every head and position), by the greedy token after the context, and then on
     a K = 4 round against those caches.  Cached k, v are bf16 values: an entry differs by a bf16 step wherever the two

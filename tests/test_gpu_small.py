@@ -689,3 +689,52 @@ def test_prompts_leave_captured_rounds_alone():
             assert ctx.wisv_get_state(3)[0] == ids[it].size
             ctx.wisv_set_state(3, 390, 0)
     ctx.wisv_destroy()
+
+
+@pytest.mark.parametrize("first,second", [
+    (300, 177),        # one chunk of 300 rows, then one that starts in mid-cache, with a last block of 15 query tokens
+    (1300, 40),        # two chunks of 672 and 628 rows, then a chunk of few rows behind them
+])
+def test_long_prompts_at_default_precision(first, second):
+    """Prompts of hundreds of tokens on a context whose rounds exceed 16 rows, at the precision it comes with: gate/up, down
+    and LM head on one half-precision term in the many-rows kernels, attention in blocks of query rows.  Both prompts run
+    on the oracle too (float activations): every layer's cached keys and values, the greedy token and a following round are
+    compared.  Half-precision activations leave about 1.2e-3 of the cache's norm (bf16 steps where values straddle a
+    rounding boundary); 5e-3 is held, and one bf16 step of the plane's largest entry for every entry."""
+    dev = torch.device("cuda:0")
+    n, k = first + second, 4
+    w = replace(configs.get(3), model=MID128, batch=6, ctx=n, k=k, protos=(PROTO_FH,) * 6, name=f"mid128_prompts_{first}_{second}", index=53)
+    wd = gen.make_weights(w.model, w.seed, dev)
+    ctx = _ctx(w, wd)
+    assert ctx.wisv_get_option(binding.WISV_OPT_ONE_TERM_CLASSES) != 0
+    toks = gen.context_tokens(w, 0)
+    side = OracleSide(w, to_host_weights(wd))
+    c = side.cache[0] = side.orc.new_cache(n + k)
+    stats = {}
+    at = 0
+    for piece in (first, second):
+        ctx.wisv_prefill(0, toks[at:at + piece])
+        for c0 in range(at, at + piece, 64):
+            last = side.orc.forward_block(c, c0, toks[c0:min(c0 + 64, at + piece)])
+        at += piece
+        side.pred_next[0] = int(last["argmax"][-1])
+        assert ctx.wisv_get_state(0) == (at, side.pred_next[0])
+    for l in range(w.model.n_layers):
+        for plane, got in enumerate(ctx.wisv_kv_export(0, l, n)):
+            got, want = got.float().numpy(), c[l, plane, :, :n]
+            err = float(np.linalg.norm(got - want) / np.linalg.norm(want))
+            stats["kv_rel"] = max(stats.get("kv_rel", 0.0), err)
+            assert err <= 5e-3, (l, plane, err)
+            assert np.max(np.abs(got - want)) <= 2.0 ** -7 * np.max(np.abs(want)), (l, plane)
+    si = side.stream_inputs(0)
+    csi = gen.csi_features(w)
+    rows = np.arange(k)
+    g = ctx.wisv_verify_round([0], si.draft, [PROTO_FH], si.hd, rows, csi[:1], [0.5], k, binding.WISV_FLAG_NO_COMMIT | binding.WISV_FLAG_KEEP_LOGITS)
+    check_invariants(g, si.draft, k)
+    logits = ctx.wisv_debug_copy(binding.WISV_DBG_LOGITS, k)
+    o = side.round(0, si, PROTO_FH, si.hd, rows, csi[0], 0.5, want_logits=True)
+    stats["logit_rel"] = row_rel_err(logits, o["logits"])
+    assert stats["logit_rel"] <= TOL_BF16_MANY.logit_rel
+    compare_stream(g, 0, o, k, 0.5, TOL_BF16_MANY, stats, logits)
+    record(w.name, stats)
+    ctx.wisv_destroy()
