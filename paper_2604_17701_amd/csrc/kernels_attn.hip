@@ -525,7 +525,7 @@ static int attn_splits(const Ctx *c, const Fwd &f) {
     const int nw = g.n_heads / g.n_kv_heads * block <= 32 ? 8 : 4;
     const int n_steps = (f.max_len_ub + STEP - 1) / STEP, wgs = (f.rows + block - 1) / block * g.n_kv_heads;
     const int want = std::max(1, std::min(256 / wgs, (n_steps + nw - 1) / nw));
-    // 16: one batch of the combine kernel
+    // 16: one batch of the combine kernel; a round smaller than the ctx's largest finds room for more splits than that one
     return std::max(1, std::min(std::min(want, 16), (int)std::min<size_t>(64, c->att_cap / f.rows)));
 }
 

@@ -698,7 +698,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
     // WEAVE asks the scheduler to place those reads between the MFMAs instead (one read after every RP of them),
     // and reads the first group of the chunk's next k-tile the same way: the matrix pipe does not drain while
     // eight reads issue.  Measured gain only for the widest products without k-splits (512 rows: gate/up
-    // 142 -> 135 us; the down projection and 96-row gate/up lose 3 %).
+    // 142 -> 135 us; the down projection loses 3 %).
     // group og of k-tile lt: plane og % NPL, operand og / NPL
 #define WISV_MM_READ_B(lt, og, DST)                                                                                \
     _Pragma("unroll") for (int t = 0; t < NT; ++t)                                                                 \
@@ -833,11 +833,10 @@ __device__ __forceinline__ void lds_load_1k_nt(uint32_t lds_addr, uint32_t voff,
 }
 // at most `left` stages of N loads each may still be on their way; then meet the other waves
 template <int N, int NS> __device__ __forceinline__ void pipe_wait(int left) {
-    static_assert(NS >= 2 && N * (NS - 2) <= 63, "vmcnt holds six bits");
-    if (NS > 2 && left >= NS - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 2 ? N * (NS - 2) : 0) : "memory");
-    else if (NS > 5 && left >= 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 5 ? 3 * N : 0) : "memory");
-    else if (NS > 4 && left == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 4 ? 2 * N : 0) : "memory");
-    else if (NS > 3 && left == 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS > 3 ? N : 0) : "memory");
+    static_assert(NS == 3 || NS == 4, "one branch per count of stages left");
+    static_assert(N * (NS - 2) <= 63, "vmcnt holds six bits");
+    if (left >= NS - 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N * (NS - 2)) : "memory");
+    else if (NS == 4 && left == 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
@@ -1208,10 +1207,12 @@ template <int NT, int CH, int EPI, int NPL> static bool launch_pipe_nt(Ctx *c, G
 template <int EPI, int NPL> static bool launch_pipe(Ctx *c, GemmArgs &g, int splits) {
     // Four chains up to 64 rows, except for a product without k-splits over so many weight rows (>= 200 groups of 512: a
     // vocabulary of 100 thousand) that one chain per output always filled the chip
-    const bool four = g.M <= 64 && (EPI == EPI_PARTIAL || (g.nrb + 31) / 32 < 200);
+    if constexpr (EPI != EPI_PARTIAL)
+        if (g.M <= 64 && (g.nrb + 31) / 32 >= 200)
+            return g.M <= 32 ? launch_pipe_nt<1, 1, EPI, NPL>(c, g, splits) : launch_pipe_nt<2, 1, EPI, NPL>(c, g, splits);
     switch ((g.M + 31) / 32) {
-        case 1: return four ? launch_pipe_nt<1, 4, EPI, NPL>(c, g, splits) : launch_pipe_nt<1, 1, EPI, NPL>(c, g, splits);
-        case 2: return four ? launch_pipe_nt<2, 4, EPI, NPL>(c, g, splits) : launch_pipe_nt<2, 1, EPI, NPL>(c, g, splits);
+        case 1: return launch_pipe_nt<1, 4, EPI, NPL>(c, g, splits);
+        case 2: return launch_pipe_nt<2, 4, EPI, NPL>(c, g, splits);
         case 3: return launch_pipe_nt<3, 1, EPI, NPL>(c, g, splits);
         case 4: return launch_pipe_nt<4, 1, EPI, NPL>(c, g, splits);
         default: return launch_pipe_nt<5, 1, EPI, NPL>(c, g, splits);
@@ -1230,9 +1231,9 @@ static int mm_layout(int rows, int nrb, int nkt, bool can_split, int max_splits)
     const int base8 = ((nrb + 8 * MM_RB - 1) / (8 * MM_RB)) * tiles, base4 = ((nrb + 4 * MM_RB - 1) / (4 * MM_RB)) * tiles;
     if (!can_split) {
         // A workgroup takes about the same time however many of them run, so the cost is rounds of 256 workgroups
-        // times the time of one round, measured on gate/up at the 8B shape: wide 118 us (512 rows), 4 x 2 waves
-        // 88 us (256 rows), narrow 67 us (128 rows).  384 rows: 336 workgroups of 4 x 2 waves took 154 us where 168
-        // wide ones take one round.
+        // times the time of one round, measured on gate/up of 4096 x 5504 over 256 rows, one round in every shape: wide
+        // 108.6 us, 4 x 2 waves 81.6, narrow 62.6 (over 512 rows narrow needs two rounds: 106.4, 83.0 and 112.8).
+        // 14336 features over 384 rows: 336 workgroups of 4 x 2 waves 163.6 us, 168 wide ones 119.2.
         const int base2 = ((nrb + 2 * MM_RB - 1) / (2 * MM_RB)) * tiles;
         const double c8 = (base8 + 255) / 256 * 1.34, c4 = (base4 + 255) / 256 * 1.0, c2 = (base2 + 255) / 256 * 0.76;
         return c8 <= c4 && c8 <= c2 ? MM_WIDE : c4 <= c2 ? MM_NORMAL : MM_NARROW;
@@ -1255,7 +1256,8 @@ template <int EPI, int NPL> static bool launch_ws_many_t(Ctx *c, GemmArgs &g, in
     }
     if constexpr (EPI != EPI_PARTIAL) {   // products with k-splits never take it
         if (layout == MM_NARROW) {
-            // a ring of two chunks with the activations staged as deep pays for gate/up only (96 rows: 72.8 -> 65.8 us)
+            // gate/up: a ring of two chunks with the activations staged as deep (5504 features over 176 / 256 rows 58.5 / 63.0
+            // -> 53.9 / 62.1 us; the LM head of 16000 tokens 64.2 / 69.3 without it, 60.3 / 68.3 if it took it)
             if (EPI == EPI_SWIGLU) return launch_mm_t<2, 2, 4, 2, 4, EPI, NPL, true>(c, g, splits);
             return launch_mm_t<2, 2, 4, 2, 2, EPI, NPL>(c, g, splits);
         }

@@ -1,7 +1,7 @@
 // Generic kernels of the verify round: one straightforward kernel per step, templated on the
 // storage type (float or bf16) of weights / cache (WT) and of activations (AT; float in both paths).
 // They serve the fp32 configuration and are the fallback wherever no specialised bf16 kernel
-// applies (prefill chunks, unusual shapes).
+// applies (shapes the matrix-core kernels do not serve).
 #include "wisv_internal.h"
 
 namespace wisv {
