@@ -1083,43 +1083,6 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
     }
 }
 
-// final argmax over the per-group candidates of every row
-__global__ __launch_bounds__(1024) void k_argmax_cand(const float *__restrict__ val, const int32_t *__restrict__ idxs, int n_cand,
-                                                     int stride, int32_t *amax) {
-    __shared__ float bv[16];
-    __shared__ int bi[16];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    float best = -INFINITY;
-    int idx = 0x7fffffff;
-    // four candidates per pass, all loads first (slots past the end re-read the last one: same value, same index)
-    for (int i0 = tid; i0 < n_cand; i0 += 4096) {
-        float v[4];
-        int n[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = min(i0 + 1024 * u, n_cand - 1);
-            v[u] = val[(size_t)m * stride + i];
-            n[u] = idxs[(size_t)m * stride + i];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (v[u] > best || (v[u] == best && n[u] < idx)) { best = v[u]; idx = n[u]; }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(idx, o, 64);
-        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-    }
-    if ((tid & 63) == 0) { bv[tid >> 6] = best; bi[tid >> 6] = idx; }
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < 16; ++w)
-            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-        amax[m] = idx == 0x7fffffff ? 0 : idx;
-    }
-}
-
 // ------------------------------------------------------------------------------------------ launch
 // LDS bytes: activation chunk (two planes, WK slices; two buffers when a slice needs several chunks),
 // or the slice-reduction scratch if that is larger
@@ -1420,7 +1383,7 @@ bool launch_gemm_ws_swiglu(Ctx *c, const void *Wt, const ActBuf &X, const ActBuf
     return launch_ws_many<EPI_SWIGLU>(c, g, 1, mm_layout(rows, g.nrb, g.nkt, false, 1), Wh);
 }
 
-// LM head with the argmax fused: greedy token of every row in c->amax; logits kept only on request
+// LM head with the argmax fused: the candidates of every row's greedy token in c->cand; logits kept only on request
 bool launch_gemm_ws_argmax(Ctx *c, const void *Wt, const ActBuf &X, float *logits, int rows, int n, int kd, int kclass,
                            const void *Wh) {
     GemmArgs g{};
@@ -1430,17 +1393,10 @@ bool launch_gemm_ws_argmax(Ctx *c, const void *Wt, const ActBuf &X, float *logit
     g.Yp = logits;
     g.cand_val = c->cand_val; g.cand_idx = c->cand_idx;
     const int slots = rows <= 16 ? g.nrb : rows <= PIPE_MAX_ROWS ? g.nrb / 2 : (g.nrb + MM_RB - 1) / MM_RB;
-    {
-        ProfScope ps(c, kclass);
-        const bool ok = rows <= 16 ? launch_ws_t<1, 1, 8, 1, 16, EPI_ARGMAX>(c, g, 1, 70 * 1024)
-                                   : launch_ws_many<EPI_ARGMAX>(c, g, 1, mm_layout(rows, g.nrb, g.nkt, false, 1), Wh);
-        if (!ok) return false;
-    }
-    {
-        ProfScope ps(c, KC_ARGMAX);
-        hipLaunchKernelGGL(k_argmax_cand, dim3(rows), dim3(1024), 0, c->stream, c->cand_val, c->cand_idx, slots, g.n_cand, c->amax);
-    }
-    return true;
+    c->cand = Candidates{c->cand_val, c->cand_idx, slots, g.n_cand};
+    ProfScope ps(c, kclass);
+    return rows <= 16 ? launch_ws_t<1, 1, 8, 1, 16, EPI_ARGMAX>(c, g, 1, 70 * 1024)
+                      : launch_ws_many<EPI_ARGMAX>(c, g, 1, mm_layout(rows, g.nrb, g.nkt, false, 1), Wh);
 }
 
 }  // namespace wisv

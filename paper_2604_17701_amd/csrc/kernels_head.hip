@@ -1,10 +1,11 @@
 // Decision head, mismatch localisation and the first-reject scan (Sec. V-A eqs. feature_concat /
 // head_forward / mlp_form; eq. threshold; Alg. 1 last block).
 //
-//   1. head     one kernel: gather of [h^D ; h^T ; c] for the scored positions (FH: positions with an uploaded h^D
-//               row; SH: mismatch positions with one), first layer, activation, second-layer partial sums
-//   2. decide   per stream: accept probabilities from the partial sums, mismatch mask, earliest rejected position,
-//               accepted length, correction token, and the commit of the stream state
+//   1. head     one launch for two things that do not need each other: the greedy token of every row from the LM head's
+//               candidates, and the head's first layer over [h^D ; h^T ; c] for every position with an uploaded h^D row
+//   2. decide   per stream: localisation, second layer and accept probabilities of the scored positions (FH: positions
+//               with an h^D row; SH: mismatch positions with one), mismatch mask, earliest rejected position, accepted
+//               length, correction token, and the commit of the stream state
 #include <algorithm>
 
 #include "wisv_internal.h"
@@ -26,18 +27,67 @@ void launch_pad_cols(Ctx *c, const void *src, void *dst, int rows, int cols, int
         hipLaunchKernelGGL(k_pad_cols<float>, dim3(rows), dim3(256), 0, c->stream, (const float *)src, (float *)dst, cols, cols_pad);
 }
 
-// ------------------------------------------------------------------------------------------ the fused head
-// u = W1 [h^D ; h^T ; c] + b1, t = w2 . act(u) for every scored position, in one kernel and without ever writing the
-// concatenated vector: the three column slices of W1 meet h^D (read through hd_row from what the device uploaded),
-// h^T (the target's final hidden state) and c (the stream's CSI vector) where they lie.
+// ------------------------------------------------------------------------------------------ greedy tokens
+// lowest index among the largest of n candidates (index i of the logits row itself where idx is null); by a whole workgroup
+template <int NTH> __device__ __forceinline__ void argmax_row(const Candidates &cd, int m, int32_t *amax) {
+    __shared__ float bv[NTH / 64];
+    __shared__ int bi[NTH / 64];
+    const int tid = threadIdx.x;
+    const float *val = cd.val + (size_t)m * cd.stride;
+    const int32_t *idxs = cd.idx ? cd.idx + (size_t)m * cd.stride : nullptr;
+    float best = -INFINITY;
+    int idx = 0x7fffffff;
+    // four candidates per pass, all loads first (slots past the end re-read the last one: same value, same index)
+    for (int i0 = tid; i0 < cd.n; i0 += 4 * NTH) {
+        float v[4];
+        int n[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = min(i0 + NTH * u, cd.n - 1);
+            v[u] = val[i];
+            n[u] = idxs ? idxs[i] : i;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (v[u] > best || (v[u] == best && n[u] < idx)) { best = v[u]; idx = n[u]; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(best, o, 64);
+        const int oi = __shfl_xor(idx, o, 64);
+        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
+    }
+    if ((tid & 63) == 0) { bv[tid >> 6] = best; bi[tid >> 6] = idx; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < NTH / 64; ++w)
+            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
+        amax[m] = idx == 0x7fffffff ? 0 : idx;
+    }
+}
+
+__global__ __launch_bounds__(512) void k_argmax(Candidates cd, int32_t *amax) { argmax_row<512>(cd, blockIdx.x, amax); }
+
+void launch_argmax(Ctx *c, int rows) {
+    ProfScope ps(c, KC_ARGMAX);
+    hipLaunchKernelGGL(k_argmax, dim3(rows), dim3(512), 0, c->stream, c->cand, c->amax);
+}
+
+// ------------------------------------------------------------------------------------------ the head's first layer
+// u = W1 [h^D ; h^T ; c] for every position with an uploaded row, without ever writing the concatenated vector: the three
+// column slices of W1 meet h^D (read through hd_row from what the device uploaded), h^T (the target's final hidden state)
+// and c (the stream's CSI vector) where they lie.  Which of these positions count is localisation's business and is left
+// to k_decide, so that nothing here waits for the greedy tokens.
 //
-// bf16 weights: W1 is held re-tiled for the 16x16x32 MFMA (kernels_gemm.hip), one workgroup = (row-block of 16
-// hidden units, tile of 16 positions), its WK waves split the columns among them and each wave builds its own B
-// operands (16 positions x 32 columns, two bf16 terms) straight from global memory - no two waves of a workgroup
-// need the same columns, so nothing is staged in LDS.  The waves' accumulators are added through LDS in wave order;
-// wave 0 adds b1, applies the activation, multiplies by w2 and adds up its 16 hidden units: one partial sum per
-// (row-block, position), which k_decide adds up in row-block order.  Positions that are not scored (not uploaded,
-// or matching drafts of a selective-hidden stream) are never loaded; a tile without a scored position exits.
+// bf16 weights: W1 is held re-tiled for the 16x16x32 MFMA (kernels_gemm.hip).  One workgroup = RB row-blocks of 16 hidden
+// units x NT tiles of 16 positions x one split of the columns; its WK waves split those columns again and each wave builds
+// its own B operands (16 positions x 32 columns, two bf16 terms) straight from global memory - no two waves of a workgroup
+// need the same columns, so nothing is staged in LDS.  The waves' accumulators are added through LDS in wave order into
+// one partial sum per (split, position, hidden unit), which k_decide adds up in split order.  Positions without an
+// uploaded row are never loaded; a tile without one exits.
+//
+// Bound by what a workgroup reads, at some 50 GB/s per CU, behind two dependent loads (row map, operands): a row-block of W1
+// is 200 KB at the 8B shape, h^D and h^T of a tile 330 KB.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -50,28 +100,20 @@ struct HeadArgs {
     const int32_t *hd_row;     // [rows] or null (identity)
     int n_hd;
     const float *h_t, *csi;    // [rows][dT], [batch][dC]
-    const int32_t *stream_ids, *proto, *tokens, *amax, *pred_next;
-    int k, rows, max_batch, gate_all, act;
+    int k, rows, act;
     const void *b1, *w2;
-    float *sp;                 // [parts][rows] partial second-layer sums
-    int32_t *scored;           // [rows]
+    float *u;                  // bf16 path: first-layer partial sums [split][rows][16 nrb]; generic: second-layer sums [rows]
+    int gx, tiles, kt_per_split;   // bf16 path: workgroups along the hidden units and the positions; columns of a split
+    // the first argmax_rows workgroups find greedy tokens instead
+    Candidates cand;
+    int argmax_rows;
+    int32_t *amax;
 };
 
-// is position m scored, and from which row of hd: Alg. 1's localisation (mismatch against the target's greedy token)
-// and the upload protocol (Sec. III-B: full-hidden streams are scored everywhere, selective-hidden ones at mismatches)
-__device__ __forceinline__ bool head_scored(const HeadArgs &a, int m, int *hr_out) {
-    // every load is unconditional (one behind a branch is waited for on the spot): they go out together, pred_next after
-    // the slot id
-    const int b = m / a.k, j = m - b * a.k;
-    const int slot = min(max(a.stream_ids[b], 0), a.max_batch - 1);
-    const int before = a.amax[max(m - 1, 0)], token = a.tokens[m], proto = a.proto[b];
-    int hr = (a.hd_row ? a.hd_row : a.tokens)[m];
-    if (!a.hd_row) hr = m;
-    const int pending = a.pred_next[slot];
-    const bool mismatch = token != (j == 0 ? pending : before);
-    if (hr >= a.n_hd) hr = -1;
-    *hr_out = hr;
-    return (a.gate_all || proto == WISV_PROTO_FH || mismatch) && hr >= 0;
+// the uploaded row of position m, or -1
+__device__ __forceinline__ int head_row(const int32_t *hd_row, int n_hd, int m) {
+    const int hr = hd_row ? hd_row[m] : m;
+    return hr >= 0 && hr < n_hd ? hr : -1;
 }
 
 // element c < din of z = [h^D ; h^T ; c] of position m
@@ -85,49 +127,33 @@ template <typename WT> __device__ __forceinline__ float head_z(const HeadArgs &a
 
 __device__ __forceinline__ float head_act(int act, float v) { return act == WISV_ACT_RELU ? fmaxf(v, 0.f) : v / (1.0f + expf(-v)); }
 
-// WK waves split the columns; a wave multiplies RB row-blocks of hidden units with NT tiles of 16 positions (every A
-// operand meets NT B operands and every B operand RB A operands) and requests TB k-tiles at a time
+// WK waves split the columns of the split; a wave multiplies RB row-blocks of hidden units with NT tiles of 16 positions (every
+// A operand meets NT B operands and every B operand RB A operands) and requests TB k-tiles at a time
 template <int WK, int RB, int NT, int TB>
 __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
-    __shared__ floatx4 red[WK][RB * NT][64];
-    __shared__ int any_scored;
-    const int rb0 = blockIdx.x * RB, tile0 = blockIdx.y * NT;
+    if ((int)blockIdx.x < a.argmax_rows) {
+        argmax_row<64 * WK>(a.cand, blockIdx.x, a.amax);
+        return;
+    }
+    const int wg = blockIdx.x - a.argmax_rows, rb0 = wg % a.gx * RB, tile0 = wg / a.gx % a.tiles * NT, split = wg / (a.gx * a.tiles);
     const int tid = threadIdx.x, lane = tid & 63, wk = tid >> 6, bj = lane & 15, bg = lane >> 4;
     int m[NT], hr[NT];
-    bool sc[NT];
+    bool sc[NT], any = false;
     const bf16_t *hd_row[NT];
     const float *ht_row[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         m[t] = (tile0 + t) * 16 + bj;
-        hr[t] = -1;
-        sc[t] = m[t] < a.rows && head_scored(a, m[t], &hr[t]);
+        hr[t] = head_row(a.hd_row, a.n_hd, min(m[t], a.rows - 1));
+        sc[t] = m[t] < a.rows && hr[t] >= 0;
+        any = any || sc[t];
         hd_row[t] = (const bf16_t *)a.hd + (size_t)max(hr[t], 0) * a.dD;
         ht_row[t] = a.h_t + (size_t)min(m[t], a.rows - 1) * a.dT;
     }
-    // bias and second-layer weights of this lane's hidden units, for the end of the kernel (units past the last re-read it)
-    bf16_t b1v[RB][4], w2v[RB][4];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = min((rb0 + r) * 16 + bg * 4 + e, a.dJ - 1);
-            b1v[r][e] = ((const bf16_t *)a.b1)[j];
-            w2v[r][e] = ((const bf16_t *)a.w2)[j];
-        }
-    if (tid == 0) any_scored = 0;
-    __syncthreads();
-    if (wk == 0) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (blockIdx.x == 0 && bg == 0 && m[t] < a.rows) a.scored[m[t]] = sc[t] ? 1 : 0;
-            if (sc[t]) any_scored = 1;      // every writer stores the same value
-        }
-    }
-    __syncthreads();
-    if (!any_scored) return;         // the whole workgroup leaves together
+    if (!__any(any)) return;         // every wave sees the same positions: the whole workgroup leaves together
 
-    const int sub = (a.nkt + WK - 1) / WK, k_begin = wk * sub, k_end = min(a.nkt, k_begin + sub);
+    const int kt0 = split * a.kt_per_split, kt1 = min(a.nkt, kt0 + a.kt_per_split), sub = (kt1 - kt0 + WK - 1) / WK;
+    const int k_begin = min(kt1, kt0 + wk * sub), k_end = min(kt1, k_begin + sub);
     floatx4 acc[RB][NT];
 #pragma unroll
     for (int r = 0; r < RB; ++r)
@@ -238,46 +264,45 @@ __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
             mma(av, t, bh, bl, true);
         }
     }
-    // ---- the waves' column slices, added in wave order
+    // ---- the waves' column slices, added in wave order, an operand tile by one wave
+    constexpr int OPS = RB * NT, PART = OPS < 4 ? OPS : 4;   // operand tiles added at a time
+    static_assert(OPS % PART == 0, "");
+    __shared__ floatx4 red[WK][PART][64];
+    const int dJp = 16 * a.nrb;
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
+    for (int i0 = 0; i0 < OPS; i0 += PART) {
+        if (i0) __syncthreads();
 #pragma unroll
-        for (int t = 0; t < NT; ++t) red[wk][r * NT + t][lane] = acc[r][t];
-    __syncthreads();
-    if (wk != 0) return;
+        for (int i = 0; i < PART; ++i) red[wk][i][lane] = acc[(i0 + i) / NT][(i0 + i) % NT];
+        __syncthreads();
+        if (wk >= PART) continue;
+        const int r = (i0 + wk) / NT, t = (i0 + wk) % NT;
+        floatx4 u = red[0][wk][lane];
+        for (int w = 1; w < WK; ++w) u += red[w][wk][lane];
+        bool on = false;
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            floatx4 u = acc[r][t];
-            for (int w = 1; w < WK; ++w) u += red[w][r * NT + t][lane];
-            // lane (bj, bg) holds u[hidden 16 (rb0 + r) + 4 bg + e][position bj of tile t]
-            float s2 = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int j = (rb0 + r) * 16 + bg * 4 + e;
-                if (j < a.dJ)
-                    s2 = fmaf(bf16_to_f32(w2v[r][e]), head_act(a.act, u[e] + bf16_to_f32(b1v[r][e])), s2);
-            }
-            s2 += __shfl_xor(s2, 16, 64);
-            s2 += __shfl_xor(s2, 32, 64);
-            if (bg == 0 && sc[t] && rb0 + r < a.nrb) a.sp[(size_t)(rb0 + r) * a.rows + m[t]] = s2;
-        }
+        for (int q = 0; q < NT; ++q) on = q == t ? sc[q] : on;
+        // lane (bj, bg) holds u[hidden 16 (rb0 + r) + 4 bg + e][position bj of tile t]
+        if (on && rb0 + r < a.nrb)
+            *reinterpret_cast<floatx4 *>(a.u + ((size_t)split * a.rows + (tile0 + t) * 16 + bj) * dJp + (rb0 + r) * 16 + bg * 4) = u;
+    }
 }
 
-// Generic form (float weights, or shapes the re-tiled form does not serve): one workgroup of 16 waves per position; one
-// partial sum per position.  Bound by latency (4 rows of the tiny fp32 target: 18 us when four waves took one hidden unit
+// Generic form (float weights, or shapes the re-tiled form does not serve): one workgroup of 16 waves per position, both
+// layers at once.  Bound by latency (4 rows of the tiny fp32 target: 18 us when four waves took one hidden unit
 // after the other, 5 us now): a wave works on UJ hidden units at once, all loads of a step of columns before the first use.  The
 // units' products are then added by four threads, unit j by thread j % 4 in rising order, and the four sums in pairs.
 template <typename WT>
 __global__ __launch_bounds__(1024) void k_head_ref(HeadArgs a) {
     constexpr int UJ = 4, GROUP = 16 * UJ * 4;            // hidden units per wave at once; per pass over val
     __shared__ float val[GROUP], red[4];
-    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int hr;
-    const bool sc = head_scored(a, m, &hr);
-    if (tid == 0) a.scored[m] = sc ? 1 : 0;
-    if (!sc) return;
+    if ((int)blockIdx.x < a.argmax_rows) {
+        argmax_row<1024>(a.cand, blockIdx.x, a.amax);
+        return;
+    }
+    const int m = blockIdx.x - a.argmax_rows, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hr = head_row(a.hd_row, a.n_hd, m);
+    if (hr < 0) return;
     float t = 0.f;
     for (int g0 = 0; g0 < a.dJ; g0 += GROUP) {
         for (int j0 = g0 + wave * UJ; j0 < min(g0 + GROUP, a.dJ); j0 += 16 * UJ) {
@@ -307,112 +332,166 @@ __global__ __launch_bounds__(1024) void k_head_ref(HeadArgs a) {
     }
     if (tid < 4) red[tid] = t;
     __syncthreads();
-    if (tid == 0) a.sp[m] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0) a.u[m] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// one wave per stream: accept probabilities from the head's partial sums (lane q adds parts q, q + 64, ..; then a
-// fixed shuffle tree), threshold, earliest rejected position, correction token, commit
-__global__ __launch_bounds__(64) void k_decide(int batch, int k, int max_batch, const int32_t *__restrict__ stream_ids,
-                         const int32_t *__restrict__ tokens, const int32_t *__restrict__ amax,
-                         const float *__restrict__ sp, int parts, int rows, const void *__restrict__ b2, int b2_bf16,
-                         const int32_t *__restrict__ scored, const float *__restrict__ tau, int gate_all, int commit,
-                         int32_t *kv_len, int32_t *pred_next, float *p_acc, int32_t *alen, int32_t *ytok, int32_t *targ,
-                         uint32_t *mask_out, uint32_t *status_out) {
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const int slot = min(max(stream_ids[b], 0), max_batch - 1);
-    const int pn = pred_next[slot];
-    const float bias = b2_bf16 ? bf16_to_f32(*(const bf16_t *)b2) : *(const float *)b2;
-    // second-layer sums of the block's positions: every load first (positions past k re-read the last one)
-    float part[WISV_MAX_K];
+// One workgroup per stream, one wave per position: is it a mismatch (Alg. 1's localisation against the target's greedy token)
+// and does the upload protocol have it scored (Sec. III-B: full-hidden streams everywhere, selective-hidden ones at
+// mismatches); the second layer from the first layer's partial sums (lanes take four hidden units at a time, then a fixed
+// shuffle tree); threshold.  Then the first wave finds the earliest rejected position, and the commit.
+struct DecideArgs {
+    int batch, k, rows, max_batch, gate_all, commit, act;
+    const int32_t *stream_ids, *tokens, *proto, *amax, *hd_row;
+    int n_hd;
+    const float *tau;
+    const float *u;            // first-layer partial sums [splits][rows][16 nrb], or (splits == 0) second-layer sums [rows]
+    int splits, dJ, nrb;
+    const void *b1, *w2, *b2;
+    int bf16;
+    int32_t *kv_len, *pred_next;
+    float *p_acc;
+    int32_t *alen, *ytok, *targ;
+    uint32_t *mask_out, *status_out;
+};
+constexpr int HEAD_MAX_SPLITS = 8;
+__global__ __launch_bounds__(64 * WISV_MAX_K) void k_decide(DecideArgs a) {
+    __shared__ int flags[WISV_MAX_K];   // 1: mismatch, 2: rejected, 4: wanted for the decision but not uploaded
+    const int b = blockIdx.x, lane = threadIdx.x & 63, j = threadIdx.x >> 6, m = b * a.k + j;
+    const int slot = min(max(a.stream_ids[b], 0), a.max_batch - 1);
+    const int before = a.amax[max(m - 1, 0)], own = a.amax[m], token = a.tokens[m], proto = a.proto[b];
+    const int hr = head_row(a.hd_row, a.n_hd, m);
+    const float tau = a.tau[b];
+    const int pn = a.pred_next[slot];
+    const bool mismatch = token != (j == 0 ? pn : before);
+    const bool sc = (a.gate_all || proto == WISV_PROTO_FH || mismatch) && hr >= 0;
+    // second layer; a position that is not scored reads sums that nobody wrote (inside the buffer) and drops the result
+    float s2 = 0.f;
+    if (a.splits) {
+        const int dJp = 16 * a.nrb;
+        for (int j0 = lane * 4; j0 < dJp; j0 += 256) {
+            float4 part[HEAD_MAX_SPLITS];
 #pragma unroll
-    for (int j = 0; j < WISV_MAX_K; ++j) {
-        const int m = b * k + min(j, k - 1);
-        float v = 0.f;
-        for (int q = lane; q < parts; q += 64) v += sp[(size_t)q * rows + m];
-        part[j] = v;
+            for (int p = 0; p < HEAD_MAX_SPLITS; ++p)   // splits past the last re-read it and are not added
+                part[p] = *reinterpret_cast<const float4 *>(a.u + ((size_t)min(p, a.splits - 1) * a.rows + m) * dJp + j0);
+            float b1[4], w2[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                b1[e] = bf16_to_f32(((const bf16_t *)a.b1)[min(j0 + e, a.dJ - 1)]);
+                w2[e] = bf16_to_f32(((const bf16_t *)a.w2)[min(j0 + e, a.dJ - 1)]);
+            }
+            float u[4] = {part[0].x, part[0].y, part[0].z, part[0].w};
+#pragma unroll
+            for (int p = 1; p < HEAD_MAX_SPLITS; ++p) {
+                const bool on = p < a.splits;
+                u[0] += on ? part[p].x : 0.f; u[1] += on ? part[p].y : 0.f; u[2] += on ? part[p].z : 0.f; u[3] += on ? part[p].w : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j0 + e < a.dJ) s2 = fmaf(w2[e], head_act(a.act, u[e] + b1[e]), s2);
+        }
+        s2 = wave_sum(s2);
+    } else {
+        s2 = a.u[m];
     }
-    float s_j[WISV_MAX_K];
-#pragma unroll
-    for (int j = 0; j < WISV_MAX_K; ++j) s_j[j] = wave_sum(part[j]);
-    if (lane != 0) return;
-    uint32_t mask = 0, status = 0;
-    int first = k;
-#pragma unroll
-    for (int j = WISV_MAX_K - 1; j >= 0; --j) {
-        if (j >= k) continue;
-        const int m = b * k + j;
-        const int t = j == 0 ? pn : amax[m - 1];
-        const bool mismatch = tokens[m] != t;
-        if (mismatch) mask |= 1u << j;
-        const bool sc = scored[m] != 0;
-        const float p = sc ? 1.0f / (1.0f + expf(s_j[j] + bias)) : 1.0f;   // p_accept = 1 - sigmoid(s); 1 where not evaluated
-        p_acc[m] = p;
-        if (gate_all || mismatch) {
-            bool reject;
-            if (!sc) { reject = true; status |= WISV_STATUS_MISSING_HIDDEN; }
-            else reject = !(p >= tau[b]);
-            if (reject) first = j;
+    const float bias = a.bf16 ? bf16_to_f32(*(const bf16_t *)a.b2) : *(const float *)a.b2;
+    if (lane == 0) {
+        const float p = sc ? 1.0f / (1.0f + expf(s2 + bias)) : 1.0f;   // p_accept = 1 - sigmoid(s); 1 where not evaluated
+        a.p_acc[m] = p;
+        const bool decides = a.gate_all || mismatch, missing = decides && !sc;
+        flags[j] = (mismatch ? 1 : 0) | (missing || (decides && !(p >= tau)) ? 2 : 0) | (missing ? 4 : 0);
+        if (a.targ) {
+            a.targ[b * (a.k + 1) + j + 1] = own;
+            if (j == 0) a.targ[b * (a.k + 1)] = pn;
         }
     }
-    const int y = first == 0 ? pn : amax[b * k + first - 1];
-    alen[b] = first;
-    ytok[b] = y;
-    if (targ) {
-        targ[b * (k + 1)] = pn;
-        for (int j = 0; j < k; ++j) targ[b * (k + 1) + j + 1] = amax[b * k + j];
-    }
-    if (mask_out) mask_out[b] = mask;
-    if (status_out) status_out[b] = status;
-    if (commit) {
-        kv_len[slot] += first;
-        pred_next[slot] = y;
+    __syncthreads();
+    if (j != 0) return;
+    const int fl = flags[min(lane, a.k - 1)];
+    const bool live = lane < a.k;
+    const uint64_t mask = __ballot(live && (fl & 1)), rejected = __ballot(live && (fl & 2)), missing = __ballot(live && (fl & 4));
+    if (lane != 0) return;
+    const int first = rejected ? __ffsll((unsigned long long)rejected) - 1 : a.k;
+    const int y = first == 0 ? pn : a.amax[b * a.k + first - 1];
+    a.alen[b] = first;
+    a.ytok[b] = y;
+    if (a.mask_out) a.mask_out[b] = (uint32_t)mask;
+    if (a.status_out) a.status_out[b] = missing ? WISV_STATUS_MISSING_HIDDEN : 0;
+    if (a.commit) {
+        a.kv_len[slot] += first;
+        a.pred_next[slot] = y;
     }
 }
 
-void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in, const wisv_round_out &out) {
+// How the first layer is cut: tiles of RB x NT operands and as many splits of the columns (of at least eight k-tiles) as make one
+// round of 256 workgroups
+struct HeadCut { int rb, nt, gx, tiles, splits, kt_per_split; };
+static HeadCut head_cut(int rows, int nrb, int nkt) {
+    HeadCut h;
+    const int pos = (rows + 15) / 16;
+    h.rb = pos <= 16 ? 2 : 4;
+    h.nt = pos == 1 ? 1 : 2;
+    h.gx = (nrb + h.rb - 1) / h.rb;
+    h.tiles = (pos + h.nt - 1) / h.nt;
+    const int s = std::max(1, std::min(std::min(HEAD_MAX_SPLITS, 256 / (h.gx * h.tiles)), nkt / 8));
+    h.kt_per_split = (nkt + s - 1) / s;
+    h.splits = (nkt + h.kt_per_split - 1) / h.kt_per_split;
+    return h;
+}
+static bool head_tiled(const Ctx *c) { return c->head_w1_t && c->cfg.d_draft % 8 == 0; }
+size_t head_scratch_floats(const Ctx *c, int rows) {
+    const int nrb = (c->cfg.d_head_hidden + 15) / 16;
+    size_t most = rows;
+    for (int r = 16;; r += 16) {      // the cut depends on the number of tiles of 16 positions
+        const int n = std::min(r, rows);
+        most = std::max(most, (size_t)head_cut(n, nrb, c->din_pad / 32).splits * n * 16 * nrb);
+        if (n == rows) return most;
+    }
+}
+
+void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in, const wisv_round_out &out, bool find_tokens) {
     const wisv_config &g = c->cfg;
-    const int gate_all = (in.flags & WISV_FLAG_GATE_ALL) ? 1 : 0, commit = (in.flags & WISV_FLAG_NO_COMMIT) ? 0 : 1;
     HeadArgs a{};
     a.w1t = (const u32x4 *)c->head_w1_t; a.w1 = c->head_w1;
     a.dJ = g.d_head_hidden; a.dD = g.d_draft; a.dT = g.d_model; a.dC = g.d_csi; a.din = g.d_draft + g.d_model + g.d_csi;
     a.nkt = c->din_pad / 32; a.nrb = (g.d_head_hidden + 15) / 16;
-    // no uploaded rows: the kernels still form addresses inside hd (and never use what they read there)
-    a.hd = in.n_hd > 0 && in.hd ? in.hd : c->d_hd;
-    a.hd_row = in.hd_row; a.n_hd = in.n_hd;
+    a.hd = in.hd; a.hd_row = in.hd_row; a.n_hd = in.n_hd;
     a.h_t = c->h_t; a.csi = in.csi;
-    a.stream_ids = in.stream_ids; a.proto = in.proto; a.tokens = in.draft_tokens; a.amax = c->amax; a.pred_next = c->d_pred_next;
-    a.k = f.k; a.rows = f.rows; a.max_batch = g.max_batch; a.gate_all = gate_all; a.act = g.head_act;
+    a.k = f.k; a.rows = f.rows; a.act = g.head_act;
     a.b1 = c->head_b1; a.w2 = c->head_w2;
-    a.sp = c->hu; a.scored = c->scored;
-    int parts;
-    {
+    a.u = c->hu;
+    a.cand = c->cand; a.amax = c->amax;
+    a.argmax_rows = find_tokens ? f.rows : 0;
+    int splits = 0;
+    if (in.n_hd == 0) {          // nothing was uploaded: localisation only
+        if (find_tokens) launch_argmax(c, f.rows);
+    } else {
         ProfScope ps(c, KC_HEAD);
-        if (c->head_w1_t && g.d_draft % 8 == 0 && g.d_draft >= 8) {
-            // A workgroup's time is what it reads (a row-block of W1, 200 KB at the 8B shape, and 260 KB of h^T per tile), so
-            // the smallest tiles are taken that make at most one round of 256 workgroups: one row-block x one tile of 16
-            // positions (96 rows: 18.7 us against 31.3 with 2 x 2 tiles), then two row-blocks (143 rows: 21.3 against 29.8;
-            // as 288 workgroups of one 35.8), then 2 x 2 operand tiles per wave (512 rows: 32.3 us; two row-blocks 42.0).
-            const int tiles = (f.rows + 15) / 16;
-            parts = a.nrb;
-            if (a.nrb * tiles <= 256)
-                hipLaunchKernelGGL((k_head_fused<16, 1, 1, 8>), dim3(a.nrb, tiles), dim3(1024), 0, c->stream, a);
-            else if ((a.nrb + 1) / 2 * tiles <= 256)
-                hipLaunchKernelGGL((k_head_fused<16, 2, 1, 4>), dim3((a.nrb + 1) / 2, tiles), dim3(1024), 0, c->stream, a);
-            else
-                hipLaunchKernelGGL((k_head_fused<8, 2, 2, 4>), dim3((a.nrb + 1) / 2, (tiles + 1) / 2), dim3(512), 0, c->stream, a);
+        if (head_tiled(c)) {
+            const HeadCut h = head_cut(f.rows, a.nrb, a.nkt);
+            a.gx = h.gx; a.tiles = h.tiles; a.kt_per_split = h.kt_per_split;
+            splits = h.splits;
+            const dim3 grid(a.argmax_rows + h.gx * h.tiles * h.splits);
+            if (h.nt == 1) hipLaunchKernelGGL((k_head_fused<8, 2, 1, 6>), grid, dim3(512), 0, c->stream, a);
+            else if (h.rb == 2) hipLaunchKernelGGL((k_head_fused<8, 2, 2, 4>), grid, dim3(512), 0, c->stream, a);
+            else hipLaunchKernelGGL((k_head_fused<8, 4, 2, 3>), grid, dim3(512), 0, c->stream, a);
         } else {
-            parts = 1;
-            if (c->bf16) hipLaunchKernelGGL(k_head_ref<bf16_t>, dim3(f.rows), dim3(1024), 0, c->stream, a);
-            else hipLaunchKernelGGL(k_head_ref<float>, dim3(f.rows), dim3(1024), 0, c->stream, a);
+            const dim3 grid(a.argmax_rows + f.rows);
+            if (c->bf16) hipLaunchKernelGGL(k_head_ref<bf16_t>, grid, dim3(1024), 0, c->stream, a);
+            else hipLaunchKernelGGL(k_head_ref<float>, grid, dim3(1024), 0, c->stream, a);
         }
     }
-    {
-        ProfScope ps(c, KC_DECIDE);
-        hipLaunchKernelGGL(k_decide, dim3(f.batch), dim3(64), 0, c->stream, f.batch, f.k, g.max_batch,
-                           in.stream_ids, in.draft_tokens, c->amax, c->hu, parts, f.rows, c->head_b2, c->bf16 ? 1 : 0,
-                           c->scored, in.tau, gate_all, commit, c->d_kv_len, c->d_pred_next, out.p_accept,
-                           out.accepted_len, out.correction_token, out.target_argmax, out.mismatch_mask, out.status);
-    }
+    DecideArgs d{};
+    d.batch = f.batch; d.k = f.k; d.rows = f.rows; d.max_batch = g.max_batch; d.act = g.head_act;
+    d.gate_all = (in.flags & WISV_FLAG_GATE_ALL) ? 1 : 0; d.commit = (in.flags & WISV_FLAG_NO_COMMIT) ? 0 : 1;
+    d.stream_ids = in.stream_ids; d.tokens = in.draft_tokens; d.proto = in.proto; d.amax = c->amax;
+    d.hd_row = in.hd_row; d.n_hd = in.n_hd; d.tau = in.tau;
+    d.u = c->hu; d.splits = splits; d.dJ = g.d_head_hidden; d.nrb = a.nrb;
+    d.b1 = c->head_b1; d.w2 = c->head_w2; d.b2 = c->head_b2; d.bf16 = c->bf16 ? 1 : 0;
+    d.kv_len = c->d_kv_len; d.pred_next = c->d_pred_next;
+    d.p_acc = out.p_accept; d.alen = out.accepted_len; d.ytok = out.correction_token; d.targ = out.target_argmax;
+    d.mask_out = out.mismatch_mask; d.status_out = out.status;
+    ProfScope ps(c, KC_DECIDE);
+    hipLaunchKernelGGL(k_decide, dim3(f.batch), dim3(64 * f.k), 0, c->stream, d);
 }
 
 }  // namespace wisv

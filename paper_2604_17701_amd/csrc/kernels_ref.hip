@@ -44,24 +44,6 @@ template <int NT> __device__ __forceinline__ float block_max(float v, float *red
     return t;
 }
 
-// ------------------------------------------------------------------------------------------ rows
-// row m = (stream b = m / k, position j = m % k): slot and absolute position L_b + j
-__global__ void k_prep_rows(const int32_t *__restrict__ stream_ids, const int32_t *__restrict__ kv_len, int k,
-                            int rows, int max_batch, int max_ctx, int32_t *row_slot, int32_t *row_pos) {
-    int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= rows) return;
-    int b = m / k, j = m - b * k;
-    int s = min(max(stream_ids[b], 0), max_batch - 1);
-    row_slot[m] = s;
-    row_pos[m] = min(max(kv_len[s], 0) + j, max_ctx - 1);
-}
-
-void launch_prep_rows(Ctx *c, const Fwd &f) {
-    ProfScope ps(c, KC_PREP);
-    hipLaunchKernelGGL(k_prep_rows, dim3((f.rows + 63) / 64), dim3(64), 0, c->stream, f.stream_ids, c->d_kv_len, f.k,
-                       f.rows, c->cfg.max_batch, c->cfg.max_ctx, c->row_slot, c->row_pos);
-}
-
 // ------------------------------------------------------------------------------------------ inputs of a host-pointer round
 // Reads pinned host memory over the link: a kernel in the stream's own queue instead of one copy command per argument
 // (seven of about 10 us each for a small round).  Every load of a thread goes out before its first store.
@@ -81,42 +63,47 @@ void launch_unpack(Ctx *c, const void *host, void *dev, size_t bytes) {
     hipLaunchKernelGGL(k_unpack, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, c->stream, (const uint4 *)host, (uint4 *)dev, n);
 }
 
-// ------------------------------------------------------------------------------------------ embedding
-template <typename WT>
-__global__ void k_embed(const WT *__restrict__ E, const int32_t *__restrict__ tok, int d, int vocab, float *x) {
-    int m = blockIdx.x;
-    int t = min(max(tok[m], 0), vocab - 1);
-    for (int i = threadIdx.x; i < d; i += blockDim.x) x[(size_t)m * d + i] = Elem<WT>::load(E + (size_t)t * d + i);
-}
-
-void launch_embed(Ctx *c, const Fwd &f) {
-    ProfScope ps(c, KC_EMBED);
-    if (c->bf16)
-        hipLaunchKernelGGL(k_embed<bf16_t>, dim3(f.rows), dim3(256), 0, c->stream, (const bf16_t *)c->embed, f.tokens,
-                           c->cfg.d_model, c->cfg.vocab, c->x);
-    else
-        hipLaunchKernelGGL(k_embed<float>, dim3(f.rows), dim3(256), 0, c->stream, (const float *)c->embed, f.tokens,
-                           c->cfg.d_model, c->cfg.vocab, c->x);
-}
-
 // ------------------------------------------------------------------------------------------ RMSNorm
 // x[m] += y[0][m] + ... + y[n_partial-1][m] (fixed order), then out[m] = x[m] / sqrt(mean(x^2)+eps) * g
-// NP: the most slices a launch may hold (the loads of all NP are issued whatever n_partial is)
+// NP: the most slices a launch may hold (the loads of all NP are issued whatever n_partial is); 0: the first launch of a
+// forward, where x[m] is the embedding of row m's token and the rows' slots and positions are noted too: row m =
+// (stream b = m / k, position j = m % k) sits at L_b + j (one launch instead of three: 96 rows 4.2 + 9.1 + 4.7 us before)
 // ss_out != null: the 1 / rms is left to whoever adds up the product's slices (out = x * g, ss_out[m] = sum of x^2)
+struct FirstRows {
+    const int32_t *tokens, *stream_ids, *kv_len;
+    const void *embed;
+    int vocab, k, max_batch, max_ctx;
+    int32_t *row_slot, *row_pos;
+};
+template <typename WT> __device__ __forceinline__ float4 load4(const WT *p);
+template <> __device__ __forceinline__ float4 load4<float>(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+template <> __device__ __forceinline__ float4 load4<bf16_t>(const bf16_t *p) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
 template <typename WT, typename AT, int NP>
 __global__ __launch_bounds__(1024) void k_rmsnorm(float *x, const float *__restrict__ y, int n_partial, size_t partial_stride,
-                          const WT *__restrict__ g, int d, float eps, ActBuf out, float *out_f32, float *ss_out) {
+                          const WT *__restrict__ g, int d, float eps, ActBuf out, float *out_f32, float *ss_out, FirstRows first) {
     __shared__ float red[16];
     const int m = blockIdx.x;
     float *xr = x + (size_t)m * d;
+    const WT *er = nullptr;
+    if (NP == 0) {
+        const int b = m / first.k, s = min(max(first.stream_ids[b], 0), first.max_batch - 1);
+        er = (const WT *)first.embed + (size_t)min(max(first.tokens[m], 0), first.vocab - 1) * d;
+        if (threadIdx.x == 0) {
+            first.row_slot[m] = s;
+            first.row_pos[m] = min(max(first.kv_len[s], 0) + m - b * first.k, first.max_ctx - 1);
+        }
+    }
     float ss = 0.f;
     // 1024 threads, four consecutive elements each per pass.  Every slice is requested before the first is used
     // (no load sits behind a branch: slices past the last re-read it and count as zero) and added in slice order.
     // The first pass's elements stay in registers for the second phase.
     float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int i = threadIdx.x * 4; i < d; i += 4096) {
-        float4 v = *reinterpret_cast<const float4 *>(xr + i);
-        float4 part[NP];
+        float4 v = NP == 0 ? load4<WT>(er + i) : *reinterpret_cast<const float4 *>(xr + i);
+        float4 part[NP ? NP : 1];
         const int np = max(n_partial, 1);
 #pragma unroll
         for (int p = 0; p < NP; ++p)
@@ -126,10 +113,11 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float *x, const float *__restr
             const bool on = p < n_partial;   // a select, not a product: the unused re-read may hold anything
             v.x += on ? part[p].x : 0.f; v.y += on ? part[p].y : 0.f; v.z += on ? part[p].z : 0.f; v.w += on ? part[p].w : 0.f;
         }
-        if (n_partial) *reinterpret_cast<float4 *>(xr + i) = v;
+        if (NP == 0 || n_partial) *reinterpret_cast<float4 *>(xr + i) = v;
         if (i < 4096) v0 = v;
         ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     }
+    if (NP == 0 && !g) return;      // the norm is folded into the product that follows
     ss = block_sum<1024>(ss, red);
     const float inv = ss_out ? 1.0f : 1.0f / sqrtf(ss / (float)d + eps);
     if (ss_out && threadIdx.x == 0) ss_out[m] = ss;
@@ -159,16 +147,17 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float *x, const float *__restr
 }
 
 template <int NP>
-static void launch_rmsnorm_np(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32, int row0, float *ss_out) {
+static void launch_rmsnorm_np(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32, int row0, float *ss_out,
+                              const FirstRows &first = {}) {
     const int d = c->cfg.d_model;
     const size_t stride = (size_t)c->slice_rows * d;
     float *x = c->x + (size_t)row0 * d, *y = c->y + (size_t)row0 * d;
     if (c->bf16)
         hipLaunchKernelGGL((k_rmsnorm<bf16_t, float, NP>), dim3(rows), dim3(1024), 0, c->stream, x, y, n_partial,
-                           stride, (const bf16_t *)g, d, c->cfg.rms_eps, out, out_f32, ss_out);
+                           stride, (const bf16_t *)g, d, c->cfg.rms_eps, out, out_f32, ss_out, first);
     else
         hipLaunchKernelGGL((k_rmsnorm<float, float, NP>), dim3(rows), dim3(1024), 0, c->stream, x, y, n_partial,
-                           stride, (const float *)g, d, c->cfg.rms_eps, out, out_f32, ss_out);
+                           stride, (const float *)g, d, c->cfg.rms_eps, out, out_f32, ss_out, first);
 }
 
 void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf &out, float *out_f32, int row0, float *ss_out) {
@@ -178,6 +167,13 @@ void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf
     if (n_partial <= 4) launch_rmsnorm_np<4>(c, rows, n_partial, g, out, out_f32, row0, ss_out);
     else if (n_partial <= 8) launch_rmsnorm_np<8>(c, rows, n_partial, g, out, out_f32, row0, ss_out);
     else launch_rmsnorm_np<16>(c, rows, n_partial, g, out, out_f32, row0, ss_out);
+}
+
+void launch_embed(Ctx *c, const Fwd &f, const void *g, const ActBuf &out, float *ss_out) {
+    ProfScope ps(c, KC_EMBED);
+    launch_rmsnorm_np<0>(c, f.rows, 0, g, out, nullptr, 0, ss_out,
+                         FirstRows{f.tokens, f.stream_ids, c->d_kv_len, c->embed, c->cfg.vocab, f.k, c->cfg.max_batch, c->cfg.max_ctx,
+                                   c->row_slot, c->row_pos});
 }
 
 // ------------------------------------------------------------------------------------------ GEMM (fallback)
@@ -389,38 +385,6 @@ void launch_swiglu(Ctx *c, int rows) {
     const int F = c->cfg.d_ff;
     dim3 grid((F + 255) / 256, rows);
     hipLaunchKernelGGL(k_swiglu, grid, dim3(256), 0, c->stream, c->gu, F, c->h);
-}
-
-// ------------------------------------------------------------------------------------------ argmax over logits rows
-__global__ void k_argmax_rows(const float *__restrict__ z, int V, int32_t *amax) {
-    __shared__ float bv[4];
-    __shared__ int bi[4];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    const float *zr = z + (size_t)m * V;
-    float best = -INFINITY;
-    int idx = 0x7fffffff;
-    for (int i = tid; i < V; i += 256) {
-        float v = zr[i];
-        if (v > best || idx == 0x7fffffff) { best = v; idx = i; }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        float ov = __shfl_xor(best, o, 64);
-        int oi = __shfl_xor(idx, o, 64);
-        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-    }
-    if ((tid & 63) == 0) { bv[tid >> 6] = best; bi[tid >> 6] = idx; }
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < 4; ++w)
-            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-        amax[m] = idx == 0x7fffffff ? 0 : idx;
-    }
-}
-
-void launch_argmax(Ctx *c, int rows) {
-    ProfScope ps(c, KC_ARGMAX);
-    hipLaunchKernelGGL(k_argmax_rows, dim3(rows), dim3(256), 0, c->stream, c->logits, c->cfg.vocab, c->amax);
 }
 
 // after a prefill chunk: the slot's length grows by the chunk; after the last one pred_next = the last row's greedy token

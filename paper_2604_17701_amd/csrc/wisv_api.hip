@@ -438,7 +438,6 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
         CREATE_TRY(dalloc(c, &c->d_in, c->io_in_bytes));
     }
     CREATE_TRY(dalloc(c, &c->d_stream_ids, g.max_batch));
-    CREATE_TRY(dalloc(c, &c->d_hd_row, R));
     {
         char *p;
         CREATE_TRY(dalloc(c, &p, (size_t)R * g.d_draft * esz));
@@ -448,7 +447,6 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     CREATE_TRY(dalloc(c, &c->d_ytok, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_pacc, R));
     CREATE_TRY(dalloc(c, &c->amax, R));
-    CREATE_TRY(dalloc(c, &c->scored, R));
     {
         hipError_t e = hipSuccess;
         make_scratch(c, *c, R, [&](size_t bytes) -> void * {
@@ -466,7 +464,7 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
         CREATE_TRY(dalloc(c, &c->cand_idx, (size_t)R * n_cand));
     }
     CREATE_TRY(dalloc(c, &c->h_t, (size_t)R * d));
-    CREATE_TRY(dalloc(c, &c->hu, (size_t)((g.d_head_hidden + 15) / 16) * R));   // the head's partial sums [row-block][row]
+    CREATE_TRY(dalloc(c, &c->hu, head_scratch_floats(c, R)));
     {
         // split-KV attention partials: as many splits of the largest round as fit 64 MiB, at most 64
         const size_t per_split = (size_t)R * c->d_q;
@@ -499,8 +497,8 @@ extern "C" const char *wisv_last_error(const wisv_ctx *ctx) { return ctx ? ctx->
 
 // ------------------------------------------------------------------------------------------ the target forward
 
-// Enqueues the decoder over f.rows rows (Alg. 1 "Verify"): leaves h^T in c->h_t and the greedy token of
-// every row in c->amax.
+// Enqueues the decoder over f.rows rows (Alg. 1 "Verify"): leaves h^T in c->h_t and the candidates for every row's greedy
+// token in c->cand (a prompt's last chunk: that token in c->amax[0]).
 // The folded RMSNorms make every workgroup of the consuming product sum the slices (or stage the whole attention row)
 // itself, work that grows with the rows while the launch it saves does not.  At the 8B shape, one stream over 512
 // cached tokens: 4 rows 3.43 -> 3.38 ms per round with the folds; 8 rows 3.52 -> 3.72 ms, 16 rows 3.84 -> 4.14 ms.
@@ -512,8 +510,10 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
     c->slice_rows = f.rows;
     // a prompt's chunk ends with its last row, and only the last chunk needs that row's greedy token
     const int out_rows = f.prefill ? 1 : f.rows, out_row0 = f.rows - out_rows;
-    launch_prep_rows(c, f);
-    launch_embed(c, f);
+    auto generic_lm_head = [&] {
+        launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, out_rows, g.vocab, d, KC_LMHEAD);
+        c->cand = Candidates{c->logits, nullptr, g.vocab, g.vocab};
+    };
     c->o_planes = ACT_ALL;
     if (c->ws_ok) {
         // bf16 weight-streaming path: every product leaves k-split partial slices that the next
@@ -572,6 +572,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
             // prologue, which sums the QKV slices anyway, applies 1 / rms.  One launch less per layer.
             int nq = 0, n_ss = 0;
             if (fuse_rope && f.rows <= FOLD_MAX_ROWS) {
+                if (l == 0) launch_embed(c, f, nullptr, ActBuf{}, nullptr);
                 nq = n_ss = launch_gemm_ws_normfold(c, L.wqkv_t, c->x, c->x_alt, ny, L.attn_norm, c->qkv, qs, max_splits, f.rows,
                                                     c->d_qkv, d, c->ss, KC_GEMM_QKV);
                 if (nq) std::swap(c->x, c->x_alt);
@@ -583,8 +584,9 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
                 // the steps)
                 const bool defer_rms = f.prefill && !half(L.wqkv_h, TERM_QKV);
                 n_ss = defer_rms ? 1 : 0;
-                launch_rmsnorm(c, f.rows, ny, L.attn_norm, act_planes(c->a, planes_for(half(L.wqkv_h, TERM_QKV))), nullptr, 0,
-                               defer_rms ? c->ss : nullptr);
+                const ActBuf a = act_planes(c->a, planes_for(half(L.wqkv_h, TERM_QKV)));
+                if (l == 0) launch_embed(c, f, L.attn_norm, a, defer_rms ? c->ss : nullptr);
+                else launch_rmsnorm(c, f.rows, ny, L.attn_norm, a, nullptr, 0, defer_rms ? c->ss : nullptr);
                 nq = product(L.wqkv_t, L.wqkv, half(L.wqkv_h, TERM_QKV), c->a, c->qkv, qs, c->d_qkv, d, KC_GEMM_QKV, full);
             }
             // with few k-splits and few rows the O projection combines the attention partials while it stages them
@@ -632,14 +634,15 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
                 c->launch_err = "the LM head fell back to the generic kernel after its input was written without the float plane";
                 return;
             }
-            launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, out_rows, g.vocab, d, KC_LMHEAD);
-            launch_argmax(c, out_rows);
+            generic_lm_head();
         }
+        if (f.prefill) launch_argmax(c, 1);
         return;
     }
     for (int l = 0; l < g.n_layers; ++l) {
         const LayerW &L = c->layers[l];
-        launch_rmsnorm(c, f.rows, l == 0 ? 0 : 1, L.attn_norm, c->a, nullptr);     // + previous FFN update
+        if (l == 0) launch_embed(c, f, L.attn_norm, c->a, nullptr);
+        else launch_rmsnorm(c, f.rows, 1, L.attn_norm, c->a, nullptr);             // + previous FFN update
         launch_gemm_ref(c, c->a.f, L.wqkv, c->qkv, f.rows, c->d_qkv, d, KC_GEMM_QKV);
         launch_rope_append(c, f, l, 1);
         launch_attn_ref(c, f, l);
@@ -651,8 +654,8 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
     }
     if (f.prefill && !f.want_last) return;
     launch_rmsnorm(c, out_rows, 1, c->final_norm, c->a, c->h_t, out_row0);
-    launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, out_rows, g.vocab, d, KC_LMHEAD);
-    launch_argmax(c, out_rows);
+    generic_lm_head();
+    if (f.prefill) launch_argmax(c, 1);
 }
 
 // ------------------------------------------------------------------------------------------ verify round
@@ -801,12 +804,9 @@ extern "C" int wisv_verify_round(wisv_ctx *ctx, const wisv_round_in *in, wisv_ro
         if (verify_only) {
             // localisation only: no hidden state counts as uploaded, nothing is committed
             din.n_hd = 0;
-            din.hd_row = c->d_hd_row;
-            hipError_t e = hipMemsetAsync(c->d_hd_row, 0xff, (size_t)R * 4, c->stream);   // every row: -1, not uploaded
-            if (e != hipSuccess) return e;
             din.flags |= WISV_FLAG_NO_COMMIT;
         }
-        launch_head_decide(c, f, din, dout);
+        launch_head_decide(c, f, din, dout, !decide_only);
         return hipSuccess;
     };
     if (same_call && c->graph_exec) {
@@ -1316,7 +1316,7 @@ extern "C" int wisv_calibration_copy(wisv_ctx *ctx, void *dst, const void *src, 
     return WISV_OK;
 }
 
-static const char *kClassNames[KC_COUNT] = {"prep_rows", "embed", "rmsnorm", "gemm_qkv", "gemm_gate_up", "rope_append", "attention", "attention_combine",
+static const char *kClassNames[KC_COUNT] = {"embed", "rmsnorm", "gemm_qkv", "gemm_gate_up", "rope_append", "attention", "attention_combine",
                                             "swiglu", "lm_head", "argmax", "head", "decide", "spec_sampling", "event_pair_overhead",
                                             "gemm_o", "gemm_down"};
 

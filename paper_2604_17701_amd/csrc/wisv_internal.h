@@ -99,7 +99,7 @@ inline ActBuf act_planes(ActBuf a, int planes) {
 
 // ---------------------------------------------------------------- kernel classes (for per-kernel timing)
 enum KernelClass {
-    KC_PREP = 0, KC_EMBED, KC_NORM, KC_GEMM_QKV, KC_GEMM_GATEUP, KC_ROPE, KC_ATTN, KC_ATTN_COMBINE, KC_SWIGLU, KC_LMHEAD,
+    KC_EMBED = 0, KC_NORM, KC_GEMM_QKV, KC_GEMM_GATEUP, KC_ROPE, KC_ATTN, KC_ATTN_COMBINE, KC_SWIGLU, KC_LMHEAD,
     KC_ARGMAX, KC_HEAD, KC_DECIDE, KC_SS, KC_EMPTY, KC_GEMM_O, KC_GEMM_DOWN, KC_COUNT
 };
 
@@ -112,6 +112,13 @@ struct LayerW {
 
 // product classes whose many-rows kernel may take its activations as one half-precision term (wisv_set_option)
 enum { TERM_QKV = 1, TERM_O = 2, TERM_GATE_UP = 4, TERM_DOWN = 8, TERM_LM_HEAD = 16, TERM_ALL = 31 };
+
+// what the LM head left of every row: n candidates for its greedy token (value, index; idx null: the value's own place)
+struct Candidates {
+    const float *val;
+    const int32_t *idx;
+    int n, stride;
+};
 
 // The buffers a forward runs through.  The rounds of a ctx own one set, sized for the largest of them; a prompt's chunk
 // of more rows runs in another.
@@ -168,8 +175,8 @@ struct Ctx : Scratch {
     void *prompt_mem;
     int prompt_rows;              // rows they hold; 0: none
 
-    // a prompt's slot; the row map of a round without uploads; uploaded hidden states too large to be packed
-    int32_t *d_stream_ids, *d_hd_row;
+    // a prompt's slot; uploaded hidden states too large to be packed
+    int32_t *d_stream_ids;
     void *d_hd;
     // host-pointer mode: a round's inputs are packed into io_in (pinned host memory the GPU can read), which a kernel
     // copies to d_in as it is; the last kernel writes the results straight into io_out (pinned as well)
@@ -180,14 +187,15 @@ struct Ctx : Scratch {
     float *d_pacc;
 
     // scratch
-    int32_t *amax, *scored;
+    int32_t *amax;
+    Candidates cand;              // of the last forward
     float *h_t, *logits;
     float *ss2;                   // [d_model / 16][16]: those of the O projection that folds the FFN norm in
     bool graph_refused;           // a capture of the round failed once: later rounds run eagerly without trying again
     float *cand_val;
     int32_t *cand_idx;
     int o_planes;                 // ACT_*: the representations of o that this round's attention kernels write
-    float *hu;                    // decision head: second-layer partial sums [row-block of hidden units][row]
+    float *hu;                    // decision head: first-layer partial sums [split][row][hidden unit]
     float *att_o, *att_m, *att_l; // split-KV attention partials: [split][rows][heads][head_dim], [split][rows][heads]
     size_t logits_rows;
     size_t att_cap;               // query rows of width d_q that att_o holds
@@ -228,8 +236,8 @@ struct Fwd {
 };
 
 // ---------------------------------------------------------------- kernel launchers (kernels_ref.hip)
-void launch_prep_rows(Ctx *c, const Fwd &f);
-void launch_embed(Ctx *c, const Fwd &f);
+// the rows' slots and positions, x = the embeddings of their tokens, out = RMSNorm(x) * g (g null: no norm); ss_out as below
+void launch_embed(Ctx *c, const Fwd &f, const void *g, const ActBuf &out, float *ss_out);
 // bytes (a multiple of 16) from pinned host memory to the device
 void launch_unpack(Ctx *c, const void *host, void *dev, size_t bytes);
 void launch_v_reblock(Ctx *c, void *rows, void *plane, int len, bool to_plane);
@@ -244,12 +252,15 @@ void launch_gemm_ref(Ctx *c, const float *A, const void *W, float *Y, int rows, 
 void launch_rope_append(Ctx *c, const Fwd &f, int layer, int n_partial, int n_ss = 0);
 void launch_attn_ref(Ctx *c, const Fwd &f, int layer);
 void launch_swiglu(Ctx *c, int rows);
-void launch_argmax(Ctx *c, int rows);
 // kv_len[slot] = new_len; pred_next[slot] = amax[row] unless row is negative
 void launch_set_pred_next(Ctx *c, int slot, int row, int new_len);
 
 // ---------------------------------------------------------------- decision head + scan (kernels_head.hip)
-void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in_dev, const wisv_round_out &out_dev);
+// the greedy token of every row, from c->cand to c->amax
+void launch_argmax(Ctx *c, int rows);
+// find_tokens: c->amax is still to be made from c->cand
+void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in_dev, const wisv_round_out &out_dev, bool find_tokens);
+size_t head_scratch_floats(const Ctx *c, int rows);   // of c->hu
 void launch_pad_cols(Ctx *c, const void *src, void *dst, int rows, int cols, int cols_pad);
 
 // ---------------------------------------------------------------- speculative-sampling decision (kernels_ss.hip)

@@ -607,7 +607,10 @@ def test_row_tiles_of_the_many_rows_products(batch, k, one_term):
 
 @pytest.mark.parametrize("base,d_draft,d_head,act,batch,k", [
     (MID128, 200, 520, configs.ACT_SILU, 13, 10),     # 130 rows, 33 row-blocks: two per workgroup; h^D ends inside a 32-column tile
-    (MID128, 192, 520, configs.ACT_RELU, 30, 10),     # 300 rows: 2 x 2 tiles, an odd number of both
+    (MID128, 192, 520, configs.ACT_RELU, 30, 10),     # 300 rows: four row-blocks x two tiles, an odd number of both
+    (MID128, 1600, 520, configs.ACT_SILU, 1, 6),      # the columns in eight splits (67 k-tiles: the last one shorter), one tile
+    (MID128, 1608, 70, configs.ACT_RELU, 13, 4),      # 52 rows, eight splits, a row-block of six units; h^D ends inside a k-tile
+    (MID128, 1600, 200, configs.ACT_SILU, 17, 16),    # 272 rows, seven splits
     (MID128, 8, 40, configs.ACT_SILU, 2, 3),          # h^D of eight columns: its only tile straddles into h^T
     (MID128, 100, 300, configs.ACT_SILU, 2, 5),       # a width the tiled form does not serve: generic form on bf16 weights
     (W0.model, 131, 300, configs.ACT_RELU, 1, 4),     # generic form, fp32, more than one pass over the hidden units
