@@ -65,29 +65,64 @@ __device__ __forceinline__ void ss_load8(const float *__restrict__ row, int i0, 
     }
 }
 
+// e^d for d <= 0 (or NaN), to the bit what expf gives there: 2^(d log2 e) with the product in two floats, split into its nearest
+// integer and the rest.  expf also looks for overflow, and k_ss_stats is close to bound by what it issues per logit.
+__device__ __forceinline__ float exp_nonpos(float d) {
+#pragma clang fp contract(off)
+    const float L = 0x1.715476p+0f, Llo = 0x1.4ae0bep-26f;   // log2 e and what a float leaves of it
+    const float p = d * L, e = __builtin_rintf(p), lo = __builtin_fmaf(d, Llo, __builtin_fmaf(d, L, -p));
+    const float r = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((p - e) + lo), (int)e);
+    return d < -0x1.9d1da0p+6f ? 0.f : r;                   // (at minus infinity p - e is no number)
+}
+
+// One wave per chunk, nothing shared between waves: all its 8 KiB are requested at once, and waves in different phases keep the
+// memory busy (512 rows x 128256 logits: 54.6 us with a workgroup per chunk and its three barriers, 40.5 now; a stream
+// of 263 MB takes 42).  The sums are those of 256 threads with eight consecutive logits each, four such groups of 64 per lane.
 __global__ void __launch_bounds__(SS_THREADS)
-k_ss_stats(const float *__restrict__ logits, int V, int C, bool vec, float *__restrict__ pm, float *__restrict__ pz) {
-    __shared__ float red[SS_THREADS / 64];
-    const int c = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
-    float x[8];
-    ss_load8(logits + (size_t)r * V, (c * SS_THREADS + tid) * SS_PER_THREAD, V, vec, -INFINITY, x);
-    float m = x[0];
+k_ss_stats(const float *__restrict__ logits, int V, int C, int n_chunks, bool vec, float *__restrict__ pm, float *__restrict__ pz) {
+    const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * (SS_THREADS / 64) + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    if (i >= n_chunks) return;
+    const int r = i / C, c = i - r * C;
+    const float *row = logits + (size_t)r * V;
+    constexpr int G = SS_THREADS / 64;
+    float x[G][8];
+    if (vec && (c + 1) * SS_THREADS * SS_PER_THREAD <= V) {   // uniform: a whole chunk
+        const float *p = row + (size_t)c * SS_THREADS * SS_PER_THREAD + lane * 8;
+        float4 lo[G], hi[G];
 #pragma unroll
-    for (int e = 1; e < 8; ++e) m = fmaxf(m, x[e]);
+        for (int w = 0; w < G; ++w) {
+            lo[w] = *reinterpret_cast<const float4 *>(p + 512 * w);
+            hi[w] = *reinterpret_cast<const float4 *>(p + 512 * w + 4);
+        }
+#pragma unroll
+        for (int w = 0; w < G; ++w) {
+            x[w][0] = lo[w].x; x[w][1] = lo[w].y; x[w][2] = lo[w].z; x[w][3] = lo[w].w;
+            x[w][4] = hi[w].x; x[w][5] = hi[w].y; x[w][6] = hi[w].z; x[w][7] = hi[w].w;
+        }
+    } else {
+#pragma unroll
+        for (int w = 0; w < G; ++w) ss_load8(row, (c * SS_THREADS + 64 * w + lane) * SS_PER_THREAD, V, vec, -INFINITY, x[w]);
+    }
+    float m = x[0][0];
+#pragma unroll
+    for (int w = 0; w < G; ++w)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, x[w][e]);
     m = wave_max(m);
-    if ((tid & 63) == 0) red[tid >> 6] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    float z = 0.f;
+    float z[G];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) z += expf(x[e] - m);   // exp(-inf) = 0 beyond the row's end
-    z = wave_sum(z);
-    if ((tid & 63) == 0) red[tid >> 6] = z;
-    __syncthreads();
-    if (tid == 0) {
-        pm[(size_t)r * C + c] = m;
-        pz[(size_t)r * C + c] = (red[0] + red[1]) + (red[2] + red[3]);
+    for (int w = 0; w < G; ++w) {
+        z[w] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[w] += exp_nonpos(x[w][e] - m);   // 0 beyond the row's end
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int w = 0; w < G; ++w) z[w] += __shfl_xor(z[w], o, 64);
+    if (lane == 0) {
+        pm[i] = m;
+        pz[i] = (z[0] + z[1]) + (z[2] + z[3]);
     }
 }
 
@@ -249,7 +284,9 @@ static void enqueue_ss(hipStream_t stream, const SsArgs &a, void *ws, int max_ba
     float *row_m = (float *)p;    p += (size_t)rows * 4;
     int32_t *sel_row = (int32_t *)p;  p += (size_t)a.batch * 4;
     int32_t *sel_mode = (int32_t *)p;
-    hipLaunchKernelGGL(k_ss_stats, dim3(C, rows), dim3(SS_THREADS), 0, stream, a.logits, V, C, vec, pm, pz);
+    const int n_chunks = rows * C;   // at most 2^16 rows of 4000 chunks
+    hipLaunchKernelGGL(k_ss_stats, dim3((n_chunks + SS_THREADS / 64 - 1) / (SS_THREADS / 64)), dim3(SS_THREADS), 0, stream, a.logits, V, C,
+                       n_chunks, vec, pm, pz);
     hipLaunchKernelGGL(k_ss_accept, dim3(a.batch), dim3(64 * a.k), 0, stream, a.k, V, C, max_batch, a.logits, pm, pz,
                        a.stream_ids, d_pred_next, a.pending_tokens, a.tokens, a.draft_probs, a.u_accept, row_m, row_z,
                        sel_row, sel_mode, a.accepted_len, a.emitted_token, a.alpha);

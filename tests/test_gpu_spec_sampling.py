@@ -86,6 +86,12 @@ def test_ss_decide_full_vocabulary(wide_vocab_ctx, batch, k, scale):
     _decide_case(wide_vocab_ctx, 7 + batch, batch, k, 128256, scale)
 
 
+@pytest.mark.parametrize("vocab", [2047, 2048, 2052, 4099, 6144])
+def test_ss_decide_edges_of_the_chunks(wide_vocab_ctx, vocab):
+    """Vocabularies that end before, at and behind a chunk of 2048 tokens, with and without rows on 16-byte boundaries."""
+    _decide_case(wide_vocab_ctx, 31 + vocab, 3, 5, vocab, 2.5)
+
+
 def test_ss_decide_rejects_bad_arguments(tiny_ctx):
     z = torch.zeros(4 * 2048, device=DEV)
     zi = torch.zeros(4, dtype=torch.int32, device=DEV)
