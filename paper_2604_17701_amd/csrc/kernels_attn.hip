@@ -25,34 +25,43 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int HD = 128, STEP = 32;
 
 struct AttnArgs {
-    const float *q;           // rotated queries [rows][H * 128]
     const bf16_t *kv_layer;   // this layer's cache: [slot][K|V][G] planes of ctx_pad * 128
     size_t slot_stride;       // elements per slot
     int H, G, rep, K, max_ctx, ctx_pad, n_splits, rows;
     const int32_t *row_slot, *row_pos;
     float *po, *pm, *pl;      // partials [split][rows][H][128], [split][rows][H]  (n_splits > 1); pm in units of ln 2
     ActBuf o;                 // attention output [rows][H][128]                    (n_splits == 1)
-    // FUSE: the kernel sums the k-split slices of the QKV product itself, rotates q and k, appends k and v
+    // the kernel sums the k-split slices of the QKV product itself and rotates q (a round: and k, and appends k and v)
     const float *qkv;         // [n_partial][partial_stride] slices of [rows][H*128 + 2 G*128]
     int n_partial;
     size_t partial_stride;
     const float *cs, *sn;     // rotary tables [max_ctx][64]
-    // FUSE, n_ss > 0: the slices are products of x * gain; row m is scaled by 1 / sqrt(sum_p ss[p][m] / d_model + eps)
+    // n_ss > 0: the slices are products of x * gain; row m is scaled by 1 / sqrt(sum_p ss[p][m] / d_model + eps)
     const float *ss;          // [n_ss][rows]
     int n_ss, d_model;
     float eps;
     bf16_t *kv_write;         // == kv_layer
 };
 
-// NQ: 16-row query tiles; NW: waves per workgroup; FUSE: RoPE and the cache append happen here: every workgroup
-// rotates the queries it needs from the slices of the QKV product, and the workgroup of a (stream, KV head) whose
-// k-split ends the sequence writes the new k, v rows before any of its waves reads them (no other split reads them)
-// NP: the most slices of the QKV product a fused launch may hold (all NP are requested whatever n_partial is, slices past
-// the last re-read it); SS: the rows still want the 1 / rms of a folded RMSNorm
-template <int NQ, int NW, bool FUSE, int NP, bool SS>
-__global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
+// NQ: 16-row query tiles; NW: waves per workgroup.  Every workgroup rotates the queries it needs from the slices of the
+// QKV product.  A round (!PROMPT): the workgroup of a (stream, KV head) whose k-split ends the sequence also writes the
+// new k, v rows before any of its waves reads them (no other split reads them).  PROMPT: a block of a prompt's chunk, whose
+// k, v rows k_kv_append has written (a block reads those of the blocks before it).
+// NP: the most slices of the QKV product a launch may hold (all NP are requested whatever n_partial is, slices past
+// the last re-read it); NSS: the most partial sums of squares (0: the rows want no 1 / rms of a folded RMSNorm)
+//
+// PROMPT is bound by the vector and matrix instructions of its waves, about as many cycles of either per step: two waves per
+// SIMD overlap them, which takes at most 256 registers and 80 KB of LDS.  Three query tiles meet that (four spill), and the
+// waves' outputs are merged in two parts of the features (1999 tokens behind nothing, 16 x 6 ctx, per chunk and layer: four
+// tiles, one wave per SIMD 87.5 us; four capped with spills 77.1; three 67.0; two 92.0.  512 tokens: 26.7, 33.1, 23.7, 30.3).
+// Rounds of three and four tiles, one workgroup per CU at most, keep the registers of one wave (143 rows: 42.0 us, capped 42.7).
+constexpr int attn_merge_parts(int nq) { return nq > 2 ? 2 : 1; }
+template <int NQ, int NW, bool PROMPT, int NP, int NSS>
+__global__ __launch_bounds__(64 * NW, PROMPT && NQ < 4 ? 2 : 1) void k_attn_mfma(AttnArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+    constexpr int PARTS = attn_merge_parts(NQ);
+    // (a prompt's last blocks see the most keys: they start first)
+    const int split = blockIdx.x, g = blockIdx.y, b = PROMPT ? gridDim.z - 1 - blockIdx.z : blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, bj = lane & 15, bg = lane >> 4;
     const int m0 = b * a.K;
     const int L = a.row_pos[m0], slot = a.row_slot[m0];
@@ -62,10 +71,10 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
     const bf16_t *vc = kc + (size_t)a.G * a.ctx_pad * HD;
     const int n_steps = (n_keys + STEP - 1) / STEP, sps = (n_steps + a.n_splits - 1) / a.n_splits;
     int s_begin = split * sps, s_end = min(n_steps, s_begin + sps);
-    // FUSE with several k-splits: the last split appends the block's k, v rows, so it owns every step from the one
+    // A round with several k-splits: the last split appends the block's k, v rows, so it owns every step from the one
     // that holds position L on (at most two steps more than its share); the others stop there
-    const bool appends = FUSE && split == a.n_splits - 1;
-    if (FUSE && a.n_splits > 1) {
+    const bool appends = !PROMPT && split == a.n_splits - 1;
+    if (!PROMPT && a.n_splits > 1) {
         const int tail = L / STEP;
         if (appends) {
             s_begin = min(s_begin, tail);
@@ -94,18 +103,17 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
         const bf16_t *pv_ = vc + ((size_t)(s_) * HD + bj) * STEP + 8 * bg;                                \
         _Pragma("unroll") for (int dt = 0; dt < 8; ++dt) va[dt] = *reinterpret_cast<const u32x4 *>(pv_ + (size_t)dt * 16 * STEP); \
     }
-    constexpr bool Q_IN_LDS = NQ > 1 || FUSE;
     constexpr int QREG = NQ > 1 ? 1 : NQ;
     u32x4 qhi[QREG][4], qlo[QREG][4];
     u32x4 *qs = reinterpret_cast<u32x4 *>(lds);   // [NQ][4][2][64] query operands; the merge at the end re-uses the space
     int s = s_begin + wave;
-    if (FUSE) {
+    {
         // this wave's first step is requested now; if it holds appended rows it is requested again below
         const int s0 = min(s, n_steps - 1);
         WISV_ATTN_LOAD_K(s0)
         WISV_ATTN_LOAD_V(s0)
     }
-    if (FUSE) {
+    {
         // ---- RoPE + append.  Work item = (row, pair of features i, i + 64): q rows rho < R of this KV head's query
         //      heads go, rotated and split into two bf16 terms, straight into the operand layout in LDS; the K new
         //      rows of k (rotated) and v go to the cache.  Slices are added in slice order.
@@ -136,10 +144,10 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
                 xs[p] = *reinterpret_cast<const floatx4 *>(src + off);
                 ys[p] = *reinterpret_cast<const floatx4 *>(src + off + 64);
             }
-            float ssp[MAX_SPLITS];
-            if (SS) {
+            float ssp[NSS ? NSS : 1];
+            if (NSS) {
 #pragma unroll
-                for (int p = 0; p < MAX_SPLITS; ++p) ssp[p] = a.ss[(size_t)min(p, a.n_ss - 1) * a.rows + m0 + j];
+                for (int p = 0; p < NSS; ++p) ssp[p] = a.ss[(size_t)min(p, a.n_ss - 1) * a.rows + m0 + j];
             }
             const int pos = min(L + j, a.max_ctx - 1);
             const floatx4 co = *reinterpret_cast<const floatx4 *>(a.cs + (size_t)pos * 64 + i);
@@ -154,10 +162,10 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
                     y[c] += on ? ys[p][c] : 0.f;
                 }
             }
-            if (SS) {   // the deferred 1 / rms of the folded RMSNorm (sums of squares in slice order)
+            if (NSS) {   // the deferred 1 / rms of the folded RMSNorm (sums of squares in slice order)
                 float t = 0.f;
 #pragma unroll
-                for (int p = 0; p < MAX_SPLITS; ++p) t += p < a.n_ss ? ssp[p] : 0.f;
+                for (int p = 0; p < NSS; ++p) t += p < a.n_ss ? ssp[p] : 0.f;
                 const float inv = 1.0f / sqrtf(t / (float)a.d_model + a.eps);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) { x[c] *= inv; y[c] *= inv; }
@@ -172,17 +180,19 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
                 // element (rho, dim) of operand (nq, t = dim / 32, plane): lane 16 ((dim % 32) / 8) + rho % 16, slot dim % 8
                 const int nq = row >> 4, bjq = row & 15;
                 const int e = i & 7, ln = 16 * ((i & 31) >> 3) + bjq, t0 = i >> 5;
-                bf16_t h0[4], l0[4], h1[4], l1[4];
+                uint2 h0, l0, h1, l1;
+                if (row >= R) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    split2(row < R ? r0[c] : 0.f, h0[c], l0[c]);
-                    split2(row < R ? r1[c] : 0.f, h1[c], l1[c]);
+                    for (int c = 0; c < 4; ++c) r0[c] = r1[c] = 0.f;
                 }
-                auto pack = [](const bf16_t (&v)[4]) { return make_uint2(v[0] | ((unsigned)v[1] << 16), v[2] | ((unsigned)v[3] << 16)); };
-                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0) * 2 + 0) * 64 + ln) << 3) + e) = pack(h0);
-                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0) * 2 + 1) * 64 + ln) << 3) + e) = pack(l0);
-                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0 + 2) * 2 + 0) * 64 + ln) << 3) + e) = pack(h1);
-                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0 + 2) * 2 + 1) * 64 + ln) << 3) + e) = pack(l1);
+                split2x2(r0[0], r0[1], h0.x, l0.x);
+                split2x2(r0[2], r0[3], h0.y, l0.y);
+                split2x2(r1[0], r1[1], h1.x, l1.x);
+                split2x2(r1[2], r1[3], h1.y, l1.y);
+                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0) * 2 + 0) * 64 + ln) << 3) + e) = h0;
+                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0) * 2 + 1) * 64 + ln) << 3) + e) = l0;
+                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0 + 2) * 2 + 0) * 64 + ln) << 3) + e) = h1;
+                *reinterpret_cast<uint2 *>(q16 + ((((nq * 4 + t0 + 2) * 2 + 1) * 64 + ln) << 3) + e) = l1;
             } else if (row < 16 * NQ + K) {
                 bf16_t k0[4], k1[4];
 #pragma unroll
@@ -201,70 +211,17 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
     }
     // (no load below is conditional - a branch around a load makes the compiler wait for it on the spot: a wave
     // without a further step re-reads a step that exists and ignores it)
-    {
+    if (!PROMPT) {
         const int s0 = min(s, n_steps - 1);
-        if (!FUSE || (s0 + 1) * STEP > L) {
+        if ((s0 + 1) * STEP > L) {
             WISV_ATTN_LOAD_K(s0)
             WISV_ATTN_LOAD_V(s0)
         }
     }
 
     // ---- queries as MFMA B operands (two bf16 terms): lane (bj, bg) holds Q[rho = 16 nq + bj][32 t + 8 bg ..].
-    //      One query tile lives in registers; more would crowd out the accumulators, so they are parked in LDS
-    //      (built once, shared by the waves) and re-read at each use.
-    if (!FUSE) {
-        if (NQ > 1) {
-            // the NQ x 4 operand pairs are dealt to the waves; rows past R load row 0 (no branch around the loads)
-            // and become zero
-            for (int item = wave; item < NQ * 4; item += NW) {
-                const int nq = item >> 2, t = item & 3, rho = nq * 16 + bj;
-                const bool valid = rho < R;
-                const float *qp = a.q + ((size_t)(m0 + (valid ? rho / a.rep : 0)) * a.H + (size_t)g * a.rep + (valid ? rho % a.rep : 0)) * HD;
-                const float4 x0 = *reinterpret_cast<const float4 *>(qp + 32 * t + 8 * bg);
-                const float4 x1 = *reinterpret_cast<const float4 *>(qp + 32 * t + 8 * bg + 4);
-                const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                uint32_t h[4], l[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    bf16_t h0, l0, h1, l1;
-                    split2(valid ? xs[2 * e] : 0.f, h0, l0);
-                    split2(valid ? xs[2 * e + 1] : 0.f, h1, l1);
-                    h[e] = h0 | ((uint32_t)h1 << 16);
-                    l[e] = l0 | ((uint32_t)l1 << 16);
-                }
-                qs[(item * 2 + 0) * 64 + lane] = u32x4{h[0], h[1], h[2], h[3]};
-                qs[(item * 2 + 1) * 64 + lane] = u32x4{l[0], l[1], l[2], l[3]};
-            }
-            __syncthreads();
-        } else {
-            const bool valid = bj < R;
-            const float *qp = a.q + ((size_t)(m0 + (valid ? bj / a.rep : 0)) * a.H + (size_t)g * a.rep + (valid ? bj % a.rep : 0)) * HD;
-            // all eight loads first, then the arithmetic
-            float4 xq[4][2];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                xq[t][0] = *reinterpret_cast<const float4 *>(qp + 32 * t + 8 * bg);
-                xq[t][1] = *reinterpret_cast<const float4 *>(qp + 32 * t + 8 * bg + 4);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                uint32_t h[4], l[4];
-                const float4 x0 = xq[t][0], x1 = xq[t][1];
-                const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    bf16_t h0, l0, h1, l1;
-                    split2(valid ? xs[2 * e] : 0.f, h0, l0);
-                    split2(valid ? xs[2 * e + 1] : 0.f, h1, l1);
-                    h[e] = h0 | ((uint32_t)h1 << 16);
-                    l[e] = l0 | ((uint32_t)l1 << 16);
-                }
-                qhi[0][t] = u32x4{h[0], h[1], h[2], h[3]};
-                qlo[0][t] = u32x4{l[0], l[1], l[2], l[3]};
-            }
-        }
-    } else if (NQ == 1) {
+    //      One query tile lives in registers; more would crowd out the accumulators and are re-read from LDS at each use.
+    if (NQ == 1) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             qhi[0][t] = qs[(t * 2 + 0) * 64 + lane];
@@ -345,13 +302,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
             }
             uint32_t h[4], l[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                bf16_t h0, l0, h1, l1;
-                split2(p[2 * e], h0, l0);
-                split2(p[2 * e + 1], h1, l1);
-                h[e] = h0 | ((uint32_t)h1 << 16);
-                l[e] = l0 | ((uint32_t)l1 << 16);
-            }
+            for (int e = 0; e < 4; ++e) split2x2(p[2 * e], p[2 * e + 1], h[e], l[e]);
             phi[nq] = u32x4{h[0], h[1], h[2], h[3]};
             plo[nq] = u32x4{l[0], l[1], l[2], l[3]};
             __builtin_amdgcn_sched_barrier(0);   // one query tile at a time: their temporaries must not pile up
@@ -417,33 +368,132 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a) {
         }
         m_all[nq] = mx;
         l_all[nq] = ls;
-        const float mine = m_run[nq] == -INFINITY ? 0.f : exp2f(m_run[nq] - mx);
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) so[((wave * NQ + nq) * 8 + dt) * 64 + lane] = oacc[nq][dt] * mine;
+        m_run[nq] = m_run[nq] == -INFINITY ? 0.f : exp2f(m_run[nq] - mx);   // from here on: the weight of this wave's output
     }
-    __syncthreads();
-    for (int dt = wave; dt < 8; dt += NW) {
+    constexpr int DP = 8 / PARTS;   // feature tiles merged at a time
+    auto merge = [&](int part) {
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq) {
-            const int rho = nq * 16 + bj;
-            floatx4 acc = so[((0 * NQ + nq) * 8 + dt) * 64 + lane];
-            for (int w = 1; w < NW; ++w) acc += so[((w * NQ + nq) * 8 + dt) * 64 + lane];
-            if (rho >= R) continue;
-            // lane holds features 16 dt + 4 bg + r of query rho
-            const int m = m0 + rho / a.rep, h = g * a.rep + rho % a.rep;
-            if (a.n_splits == 1) {
-                const float inv = 1.0f / l_all[nq];
-                act_store4(a.o, ((size_t)m * a.H + h) * HD + 16 * dt + 4 * bg, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-            } else {
-                const size_t row = ((size_t)split * a.rows + m) * a.H + h;
-                *reinterpret_cast<floatx4 *>(a.po + row * HD + 16 * dt + 4 * bg) = acc;
-                if (dt == 0 && bg == 0) {
-                    a.pm[row] = m_all[nq];
-                    a.pl[row] = l_all[nq];
+        for (int nq = 0; nq < NQ; ++nq)
+#pragma unroll
+            for (int dt = 0; dt < DP; ++dt) so[((wave * NQ + nq) * DP + dt) * 64 + lane] = oacc[nq][part * DP + dt] * m_run[nq];
+        __syncthreads();
+        for (int dl = wave; dl < DP; dl += NW) {
+            const int dt = part * DP + dl;
+#pragma unroll
+            for (int nq = 0; nq < NQ; ++nq) {
+                const int rho = nq * 16 + bj;
+                floatx4 acc = so[((0 * NQ + nq) * DP + dl) * 64 + lane];
+                for (int w = 1; w < NW; ++w) acc += so[((w * NQ + nq) * DP + dl) * 64 + lane];
+                if (rho >= R) continue;
+                // lane holds features 16 dt + 4 bg + r of query rho
+                const int m = m0 + rho / a.rep, h = g * a.rep + rho % a.rep;
+                if (a.n_splits == 1) {
+                    const float inv = 1.0f / l_all[nq];
+                    act_store4(a.o, ((size_t)m * a.H + h) * HD + 16 * dt + 4 * bg, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+                } else {
+                    const size_t row = ((size_t)split * a.rows + m) * a.H + h;
+                    *reinterpret_cast<floatx4 *>(a.po + row * HD + 16 * dt + 4 * bg) = acc;
+                    if (dt == 0 && bg == 0) {
+                        a.pm[row] = m_all[nq];
+                        a.pl[row] = l_all[nq];
+                    }
                 }
             }
         }
+    };
+    merge(0);
+    if (PARTS == 2) {
+        __syncthreads();   // the first part has been read
+        merge(PARTS - 1);
     }
+}
+
+// ------------------------------------------------------------------------------------------ a prompt's keys and values
+// The chunk's rows lie at consecutive positions of one slot.  One workgroup = one block of 32 positions of the cache x one KV
+// head, k (blockIdx.z 0: rotated, 16-byte stores) or v (1: turned over in LDS, since the V plane keeps 32 positions of a feature
+// together).  Slices are added in slice order; n_ss as in AttnArgs (at most 1).  1024 rows of the 8B shape: 6 us; a
+// workgroup per row and head, which rotated the queries too, 26.2.
+struct AppendArgs {
+    const float *qkv;
+    int n_partial;
+    size_t partial_stride;
+    int rows, d_q, G, ctx_pad, d_model, n_ss;
+    const int32_t *row_slot, *row_pos;
+    const float *cs, *sn, *ss;
+    float eps;
+    bf16_t *kv_layer;
+    size_t slot_stride;
+};
+__global__ __launch_bounds__(256) void k_kv_append(AppendArgs a) {
+    __shared__ float vt[HD][STEP + 1];
+    const int g = blockIdx.y, tid = threadIdx.x, r = tid >> 3, c0 = (tid & 7) * 8;   // row of the block; features c0 .. + 7 and c0 + 64 ..
+    const int pos0 = a.row_pos[0], slot = a.row_slot[0], pb = pos0 / STEP + blockIdx.x;
+    const int m = pb * STEP - pos0 + r, mc = min(max(m, 0), a.rows - 1), pos = pos0 + mc;   // rows outside the chunk re-read one inside
+    const bool is_v = blockIdx.z != 0;
+    const float *src = a.qkv + (size_t)mc * (a.d_q + 2 * a.G * HD) + a.d_q + (is_v ? a.G * HD : 0) + g * HD + c0;
+    floatx4 x[4];   // features c0, c0 + 4, c0 + 64, c0 + 68
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const floatx4 *>(src + (i >> 1) * 64 + (i & 1) * 4);
+    const float ssm = a.ss[mc];
+    for (int p = 1; p < a.n_partial; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] += *reinterpret_cast<const floatx4 *>(src + p * a.partial_stride + (i >> 1) * 64 + (i & 1) * 4);
+    if (a.n_ss) {
+        const float inv = 1.0f / sqrtf(ssm / (float)a.d_model + a.eps);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] *= inv;
+    }
+    const bool live = m >= 0 && m < a.rows;
+    bf16_t *kc = a.kv_layer + (size_t)slot * a.slot_stride + (size_t)g * a.ctx_pad * HD;
+    if (!is_v) {
+        uint32_t lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const floatx4 co = *reinterpret_cast<const floatx4 *>(a.cs + (size_t)pos * 64 + c0 + 4 * i);
+            const floatx4 si = *reinterpret_cast<const floatx4 *>(a.sn + (size_t)pos * 64 + c0 + 4 * i);
+            float f0[4], f1[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                f0[e] = x[i][e] * co[e] - x[2 + i][e] * si[e];
+                f1[e] = x[2 + i][e] * co[e] + x[i][e] * si[e];
+            }
+            lo[2 * i] = f32x2_to_bf16x2(f0[0], f0[1]); lo[2 * i + 1] = f32x2_to_bf16x2(f0[2], f0[3]);
+            hi[2 * i] = f32x2_to_bf16x2(f1[0], f1[1]); hi[2 * i + 1] = f32x2_to_bf16x2(f1[2], f1[3]);
+        }
+        if (live) {
+            *reinterpret_cast<uint4 *>(kc + (size_t)pos * HD + c0) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            *reinterpret_cast<uint4 *>(kc + (size_t)pos * HD + c0 + 64) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vt[c0 + (i >> 1) * 64 + (i & 1) * 4 + e][r] = x[i][e];
+    __syncthreads();
+    // thread: sixteen positions of one feature
+    const int dim = tid >> 1, p0 = (tid & 1) * 16, m_first = pb * STEP - pos0 + p0;
+    bf16_t *vp = kc + (size_t)a.G * a.ctx_pad * HD + ((size_t)pb * HD + dim) * STEP + p0;
+    uint32_t w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = f32x2_to_bf16x2(vt[dim][p0 + 2 * i], vt[dim][p0 + 2 * i + 1]);
+    if (m_first >= 0 && m_first + 16 <= a.rows) {
+        *reinterpret_cast<uint4 *>(vp) = make_uint4(w[0], w[1], w[2], w[3]);
+        *reinterpret_cast<uint4 *>(vp + 8) = make_uint4(w[4], w[5], w[6], w[7]);
+    } else {   // the chunk begins or ends inside: the other positions keep what they hold
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (m_first + i >= 0 && m_first + i < a.rows) vp[i] = (bf16_t)(w[i >> 1] >> (16 * (i & 1)));
+    }
+}
+static void launch_kv_append(Ctx *c, const Fwd &f, int layer, int n_partial, int n_ss) {
+    const wisv_config &g = c->cfg;
+    ProfScope ps(c, KC_ROPE);
+    const AppendArgs a{c->qkv, n_partial, (size_t)c->slice_rows * c->d_qkv, f.rows, c->d_q, g.n_kv_heads, c->ctx_pad, g.d_model, n_ss,
+                       c->row_slot, c->row_pos, c->rope_cos, c->rope_sin, c->ss, g.rms_eps, (bf16_t *)kv_ptr(c, layer, 0, 0),
+                       (size_t)2 * g.n_kv_heads * c->ctx_pad * g.head_dim};
+    // the first row may lie anywhere in its block of positions
+    hipLaunchKernelGGL(k_kv_append, dim3((f.rows + STEP - 2) / STEP + 1, g.n_kv_heads, 2), dim3(256), 0, c->stream, a);
 }
 
 // o[m][h][:] = sum_s 2^(m_s - m*) O_s / sum_s 2^(m_s - m*) l_s (the maxima are kept in units of ln 2), splits in index
@@ -483,22 +533,26 @@ __global__ void k_attn_combine(const float *__restrict__ po, const float *__rest
     act_store(o, ((size_t)m * H + h) * HD + d, num / den);
 }
 
-template <int NQ, int NW, bool FUSE, int NP, bool SS> static bool launch_nq_t(Ctx *c, const AttnArgs &a, dim3 grid) {
+template <int NQ, int NW, bool PROMPT, int NP, int NSS> static bool launch_nq_t(Ctx *c, const AttnArgs &a, dim3 grid) {
     // the merge area at the end of the kernel, which also holds the parked query operands before that
-    const size_t lds = std::max((size_t)NW * NQ * (2 * 16 * 4 + 8 * 64 * 16), (size_t)NQ * 8 * 1024);
+    const size_t lds = std::max((size_t)NW * NQ * (2 * 16 * 4 + 8 / attn_merge_parts(NQ) * 64 * 16), (size_t)NQ * 8 * 1024);
     static bool allowed[MAX_DEVICES];
-    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_attn_mfma<NQ, NW, FUSE, NP, SS>), allowed)) return false;
-    hipLaunchKernelGGL((k_attn_mfma<NQ, NW, FUSE, NP, SS>), grid, dim3(64 * NW), lds, c->stream, a);
+    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_attn_mfma<NQ, NW, PROMPT, NP, NSS>), allowed)) return false;
+    hipLaunchKernelGGL((k_attn_mfma<NQ, NW, PROMPT, NP, NSS>), grid, dim3(64 * NW), lds, c->stream, a);
     return true;
 }
-// The fused prologue requests as many slices as its instantiation holds, 32 bytes of each per item: the smallest one that
-// covers the count (rounds of more than 16 rows leave 2 to 10)
+// The prologue requests as many slices as its instantiation holds, 32 bytes of each per item: the smallest one that
+// covers the count (rounds of more than 16 rows leave 2 to 10, a prompt's chunk 1 to 4, or more when it is short)
 template <int NQ, int NW> static bool launch_nq(Ctx *c, const AttnArgs &a, dim3 grid) {
-    if (a.n_partial == 0) return launch_nq_t<NQ, NW, false, 1, false>(c, a, grid);
-    if (a.n_ss > 0) return launch_nq_t<NQ, NW, true, MAX_SPLITS, true>(c, a, grid);
-    if (a.n_partial <= 2) return launch_nq_t<NQ, NW, true, 2, false>(c, a, grid);
-    if (a.n_partial <= 5) return launch_nq_t<NQ, NW, true, 5, false>(c, a, grid);
-    return launch_nq_t<NQ, NW, true, MAX_SPLITS, false>(c, a, grid);
+    if (a.n_ss > 0) return launch_nq_t<NQ, NW, false, MAX_SPLITS, MAX_SPLITS>(c, a, grid);
+    if (a.n_partial <= 2) return launch_nq_t<NQ, NW, false, 2, 0>(c, a, grid);
+    if (a.n_partial <= 5) return launch_nq_t<NQ, NW, false, 5, 0>(c, a, grid);
+    return launch_nq_t<NQ, NW, false, MAX_SPLITS, 0>(c, a, grid);
+}
+template <int NQ, int NW> static bool launch_prompt_nq(Ctx *c, const AttnArgs &a, dim3 grid) {
+    if (a.n_partial <= 2) return a.n_ss ? launch_nq_t<NQ, NW, true, 2, 1>(c, a, grid) : launch_nq_t<NQ, NW, true, 2, 0>(c, a, grid);
+    if (a.n_partial <= 4) return a.n_ss ? launch_nq_t<NQ, NW, true, 4, 1>(c, a, grid) : launch_nq_t<NQ, NW, true, 4, 0>(c, a, grid);
+    return a.n_ss ? launch_nq_t<NQ, NW, true, MAX_SPLITS, 1>(c, a, grid) : launch_nq_t<NQ, NW, true, MAX_SPLITS, 0>(c, a, grid);
 }
 
 // One workgroup per (stream, KV head) when that fills the chip (then the workgroup writes the output itself);
@@ -508,15 +562,15 @@ template <int NQ, int NW> static bool launch_nq(Ctx *c, const AttnArgs &a, dim3 
 // (one stream over 512: the round takes 3.51 ms with 3 splits and their combine kernel, 3.55 ms with one).
 // 0: the shape is not served.
 //
-// A prompt's chunk has more rows than the 64 query rows one workgroup meets: it is cut into blocks of 64 / rep rows,
-// each treated as a stream of its own whose cached length is its first row's position (k_rope_append has written the
+// A prompt's chunk has more rows than the 64 query rows one workgroup meets: it is cut into blocks of about 48 query rows,
+// each treated as a stream of its own whose cached length is its first row's position (k_kv_append has written the
 // whole chunk's k, v rows before, and a block's causal limit is its own last position).
 static int attn_block(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
     const int rep = g.n_heads / g.n_kv_heads;
     if (!c->bf16 || g.head_dim != HD || rep > 64 || f.rows != f.batch * f.k) return 0;
     if (rep * f.k <= 64) return f.k;
-    return f.prefill ? 64 / rep : 0;   // a round's larger block goes to the generic kernel
+    return f.prefill ? std::max(1, 48 / rep) : 0;   // a round's larger block goes to the generic kernel
 }
 static int attn_splits(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
@@ -534,8 +588,7 @@ static int attn_splits(const Ctx *c, const Fwd &f) {
 // for RoPE and the append: 8 rows over 4096 cached tokens 4.04 -> 3.92 ms per round; 96 rows, 2 splits 6.34 -> 6.15;
 // 72 rows, 3 splits 6.25 -> 6.09; 32 rows over 4096 tokens, 8 splits 4.98 -> 4.86; 24 rows over 8192 tokens, 16
 // splits 4.88 -> 4.89.  k_rope_append serves the shapes this kernel does not take.
-// A chunk cut into blocks cannot fuse it: a block reads the k, v rows of the blocks before it.
-bool attn_mfma_fuses_rope(const Ctx *c, const Fwd &f) { return attn_block(c, f) == f.k; }
+bool attn_one_block(const Ctx *c, const Fwd &f) { return attn_block(c, f) == f.k; }
 
 // c->o from the k-split partials in c->att_o / att_m / att_l
 void launch_attn_combine(Ctx *c, const Fwd &f, int n_splits) {
@@ -549,15 +602,14 @@ void launch_attn_combine(Ctx *c, const Fwd &f, int n_splits) {
                            n_splits, f.rows, g.n_heads, act_planes(c->o, c->o_planes));
 }
 
-// n_partial > 0: the k-split slices of the QKV product are in c->qkv and the kernel does RoPE and the append
-// itself; n_partial == 0: launch_rope_append has run
+// c->qkv holds the n_partial k-split slices of the QKV product
 bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_combine, int *n_splits, int n_ss) {
     const wisv_config &g = c->cfg;
     const int block = attn_block(c, f), rep = g.n_heads / g.n_kv_heads, R = rep * block;
+    const bool prompt = block != f.k;
     AttnArgs a;
     a.n_splits = attn_splits(c, f);
-    if (!a.n_splits || (n_partial > 0 && !attn_mfma_fuses_rope(c, f))) return false;
-    a.q = c->q;
+    if (!a.n_splits || (prompt && n_ss > 1)) return false;
     a.kv_layer = (const bf16_t *)kv_ptr(c, layer, 0, 0);
     a.kv_write = (bf16_t *)kv_ptr(c, layer, 0, 0);
     a.slot_stride = (size_t)2 * g.n_kv_heads * c->ctx_pad * g.head_dim;
@@ -568,16 +620,16 @@ bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_
     a.qkv = c->qkv; a.n_partial = n_partial; a.partial_stride = (size_t)c->slice_rows * c->d_qkv;
     a.cs = c->rope_cos; a.sn = c->rope_sin;
     a.ss = c->ss; a.n_ss = n_ss; a.d_model = g.d_model; a.eps = g.rms_eps;
-    if (n_ss > 0 && n_partial == 0) return false;   // only the fused prologue applies the scale
+    if (prompt) launch_kv_append(c, f, layer, n_partial, n_ss);
     dim3 grid(a.n_splits, g.n_kv_heads, (f.rows + block - 1) / block);
     {
         ProfScope ps(c, KC_ATTN);
         bool ok;
         switch ((R + 15) / 16) {
-            case 1: ok = launch_nq<1, 8>(c, a, grid); break;
-            case 2: ok = launch_nq<2, 8>(c, a, grid); break;
-            case 3: ok = launch_nq<3, 4>(c, a, grid); break;
-            default: ok = launch_nq<4, 4>(c, a, grid); break;
+            case 1: ok = prompt ? launch_prompt_nq<2, 8>(c, a, grid) : launch_nq<1, 8>(c, a, grid); break;
+            case 2: ok = prompt ? launch_prompt_nq<2, 8>(c, a, grid) : launch_nq<2, 8>(c, a, grid); break;
+            case 3: ok = prompt ? launch_prompt_nq<3, 4>(c, a, grid) : launch_nq<3, 4>(c, a, grid); break;
+            default: ok = prompt ? launch_prompt_nq<4, 4>(c, a, grid) : launch_nq<4, 4>(c, a, grid); break;
         }
         if (!ok) return false;
     }

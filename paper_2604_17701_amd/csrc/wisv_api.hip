@@ -564,14 +564,14 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
             }
         };
         int ny = 0;
-        const bool fuse_rope = attn_mfma_fuses_rope(c, f);
+        const bool one_block = attn_one_block(c, f);
         for (int l = 0; l < g.n_layers; ++l) {
             const LayerW &L = c->layers[l];
             // Few rows, attention with the fused prologue: the attention norm is folded into the QKV product
             // (it sums the previous slices into the residual stream itself and is fed x * gain) and the attention
             // prologue, which sums the QKV slices anyway, applies 1 / rms.  One launch less per layer.
             int nq = 0, n_ss = 0;
-            if (fuse_rope && f.rows <= FOLD_MAX_ROWS) {
+            if (one_block && f.rows <= FOLD_MAX_ROWS) {
                 if (l == 0) launch_embed(c, f, nullptr, ActBuf{}, nullptr);
                 nq = n_ss = launch_gemm_ws_normfold(c, L.wqkv_t, c->x, c->x_alt, ny, L.attn_norm, c->qkv, qs, max_splits, f.rows,
                                                     c->d_qkv, d, c->ss, KC_GEMM_QKV);
@@ -590,12 +590,12 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
                 nq = product(L.wqkv_t, L.wqkv, half(L.wqkv_h, TERM_QKV), c->a, c->qkv, qs, c->d_qkv, d, KC_GEMM_QKV, full);
             }
             // with few k-splits and few rows the O projection combines the attention partials while it stages them
-            const bool defer = fuse_rope && f.rows <= 16 && g.head_dim == 128;
+            const bool defer = one_block && f.rows <= 16 && g.head_dim == 128;
             int att_splits = 1;
-            if (!(fuse_rope && launch_attn_mfma(c, f, l, nq, !defer, &att_splits, n_ss))) {
+            if (!launch_attn_mfma(c, f, l, nq, !defer, &att_splits, n_ss)) {
                 att_splits = 1;
                 launch_rope_append(c, f, l, nq, n_ss);
-                if (!launch_attn_mfma(c, f, l, 0)) launch_attn_ref(c, f, l);
+                launch_attn_ref(c, f, l);
             }
             ny = 0;
             // Few rows: the O projection keeps its k-split inside the workgroup, adds the residual stream itself

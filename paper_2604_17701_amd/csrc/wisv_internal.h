@@ -57,6 +57,17 @@ __device__ __forceinline__ void split2(float v, bf16_t &hi, bf16_t &lo) {
     hi = f32_to_bf16(v);
     lo = f32_to_bf16(v - bf16_to_f32(hi));
 }
+// two values at once, each pair one word (low half first): the compiler converts what split2 is given one value at a time and
+// puts the halves together afterwards
+__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float a, float b) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
+}
+__device__ __forceinline__ void split2x2(float a, float b, uint32_t &hi, uint32_t &lo) {
+    hi = f32x2_to_bf16x2(a, b);
+    lo = f32x2_to_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
 // A plane whose pointer is null is not written (f; hi and lo together; h16): a producer whose only consumer reads
 // one representation leaves the others out.
 __device__ __forceinline__ void act_store(const ActBuf &a, size_t i, float v) {
@@ -74,13 +85,11 @@ __device__ __forceinline__ void act_store(const ActBuf &a, size_t i, float v) {
 __device__ __forceinline__ void act_store4(const ActBuf &a, size_t i, float v0, float v1, float v2, float v3) {
     if (a.f) *reinterpret_cast<float4 *>(a.f + i) = make_float4(v0, v1, v2, v3);
     if (a.hi) {
-        bf16_t h[4], l[4];
-        split2(v0, h[0], l[0]);
-        split2(v1, h[1], l[1]);
-        split2(v2, h[2], l[2]);
-        split2(v3, h[3], l[3]);
-        *reinterpret_cast<uint2 *>(a.hi + i) = make_uint2(h[0] | ((unsigned)h[1] << 16), h[2] | ((unsigned)h[3] << 16));
-        *reinterpret_cast<uint2 *>(a.lo + i) = make_uint2(l[0] | ((unsigned)l[1] << 16), l[2] | ((unsigned)l[3] << 16));
+        uint2 h, l;
+        split2x2(v0, v1, h.x, l.x);
+        split2x2(v2, v3, h.y, l.y);
+        *reinterpret_cast<uint2 *>(a.hi + i) = h;
+        *reinterpret_cast<uint2 *>(a.lo + i) = l;
     }
     if (a.h16)
         *reinterpret_cast<uint2 *>(a.h16 + i) = make_uint2(f32_to_f16(v0) | ((unsigned)f32_to_f16(v1) << 16),
@@ -318,18 +327,17 @@ bool launch_gemm_ws_argmax(Ctx *c, const void *Wt, const ActBuf &X, float *logit
                            const void *Wh = nullptr);
 
 // ---------------------------------------------------------------- split-KV MFMA attention (kernels_attn.hip)
-// true if the shape is served (bf16 cache, head_dim 128, at most 64 query rows per KV head); then c->o holds
-// the attention output of every row
+// RoPE, the cache append and the attention of every row from the n_partial k-split slices of the QKV product in c->qkv.
+// true if the shape is served (bf16 cache, head_dim 128, at most 64 query rows per KV head or a prompt's chunk); then c->o
+// holds the attention output of every row
 // with_combine false leaves the k-split partials in c->att_o / att_m / att_l for a consumer that combines them
 // itself (*n_splits tells how many; 1 means c->o is complete all the same)
 // n_ss > 0: the QKV product was fed x * gain instead of RMSNorm(x); its slices are scaled by 1 / rms from the n_ss
-// partial sums of squares in c->ss (fused RoPE path only)
-bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_combine = true, int *n_splits = nullptr,
-                      int n_ss = 0);
+// partial sums of squares in c->ss
+bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_combine, int *n_splits, int n_ss);
 void launch_attn_combine(Ctx *c, const Fwd &f, int n_splits);
-// true if launch_attn_mfma(.., n_partial > 0) will do RoPE and the cache append itself from the k-split slices of
-// the QKV product (then launch_rope_append must not run)
-bool attn_mfma_fuses_rope(const Ctx *c, const Fwd &f);
+// true if each stream's rows are one block of that kernel
+bool attn_one_block(const Ctx *c, const Fwd &f);
 
 // A kernel that wants more than 64 KiB of dynamic LDS must be allowed to once per device.  `done` is the caller's
 // per-kernel table (one flag per device): a cache of an idempotent call, not state that results depend on.

@@ -548,7 +548,9 @@ def test_mixed_context_lengths_in_one_round(lengths, k):
 
 
 @pytest.mark.parametrize("model,batch,k,lens", [
-    (MID128, 1, 4, (15, 16, 17, 31, 33, 64, 65, 130)),       # two bf16 terms; 16-row blocks of query tokens, short last one
+    (MID128, 1, 4, (15, 16, 17, 31, 33, 64, 65, 130)),       # two bf16 terms; up to 16 tokens are one block
+    (MID128, 1, 4, (24, 25, 36, 95)),                        # blocks of 12 tokens: whole ones, a last one of one and of eleven
+    (replace(MID128, n_heads=28, n_kv_heads=1), 1, 2, (6, 35)),   # 28 query heads per KV head: blocks of one token
     (MID128, 1, 1, (3, 20)),                                 # more rows in a prompt's chunk than the largest round has
     (MID128, 6, 4, (24, 40, 97, 1061)),                      # rounds beyond 16 rows exist: a leftover of 1, 16, 1, 5 tokens
     (replace(MID128, n_heads=12, n_kv_heads=4), 1, 4, (21, 43, 150)),   # three query heads per KV head: blocks of 21 tokens
