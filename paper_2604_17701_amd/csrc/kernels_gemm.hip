@@ -91,9 +91,7 @@ struct GemmArgs {
     float *Yp;                 // EPI_PARTIAL: [S][split_stride];  EPI_ARGMAX with logits != null: [M][N]
     size_t split_stride;
     ActBuf H;                  // EPI_SWIGLU: [M][N] float + planes (N = features)
-    float *cand_val;           // EPI_ARGMAX: [M][n_cand]
-    int32_t *cand_idx;
-    int n_cand;
+    uint2 *cand;               // EPI_ARGMAX: (value, index) [slot][M]
     int gx, gz, gs;            // k_gemm_mm, k_gemm_pipe: row-block groups, row tiles and k-splits the 1-D grid decodes into
     int per;                   // k_gemm_pipe: consecutive k-splits a workgroup takes one after the other
     // PRO: the activations are the attention output, still in k-split partials (up to WS_PRO_SPLITS of them):
@@ -222,10 +220,7 @@ __device__ __forceinline__ void ws_epilogue(const GemmArgs &g, floatx4 (&acc)[RB
                 const int oi = __shfl_xor(idx, o, 64);
                 if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
             }
-            if (bg == 0 && m < g.M) {
-                g.cand_val[(size_t)m * g.n_cand + slot] = best;
-                g.cand_idx[(size_t)m * g.n_cand + slot] = idx;
-            }
+            if (bg == 0 && m < g.M) g.cand[(size_t)slot * g.M + m] = make_uint2(__float_as_uint(best), (uint32_t)idx);
         }
     }
 }
@@ -522,31 +517,51 @@ __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_
 // tiles sharing a slice of W run on the same XCD at the same time (workgroup ids are dealt round-robin to the
 // 8 XCDs): W then comes from HBM once and from that L2 afterwards.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+// Plain results: a lane's four consecutive floats stored as they stand would put 16 bytes into each of 32 rows twice per store,
+// and the four stores of a tile a quarter each into the same lines.  So a tile is turned over in 4 KiB of LDS that belong to
+// the wave (the 16-byte pieces of a row permuted, so that neither side meets a bank twice) and leaves as 128-byte runs of eight
+// rows per store.  us per launch, before and after: down over 512 rows 66.1 -> 62.0, over 143 rows 34.5 -> 33.4; QKV over 1000
+// rows 108.5 -> 104.5; O over 143 rows 16.7 -> 16.0; 32 and 96 rows the same.  What an epilogue still costs is its bytes: 143 rows
+// leave 18 MB of QKV slices, 4 us.  SwiGLU's 2-byte results gain nothing this way (512 rows 115.2 -> 116, 1000 rows 225 -> 228).
+// Candidates for the greedy token lie [slot][row]: a wave's 32 rows fill whole lines, where [row][slot] put 4 bytes of every
+// XCD into each (LM head of 32000 tokens over 143 rows 60.8 -> 57.8 us).
+// one 32 x 32 tile of plain results to rows m0 .., columns n0 ..
+__device__ __forceinline__ void store_tile(const GemmArgs &g, float *out, floatx4 *turn, const floatx16 &a, int m0, int n0, int lane) {
+    const int mj = lane & 31, h = lane >> 5;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's LDS accesses stay in this order
+#pragma unroll
+    for (int v = 0; v < 4; ++v) turn[mj * 8 + ((2 * v + h) ^ ((mj >> 1) & 7))] = floatx4{a[4 * v], a[4 * v + 1], a[4 * v + 2], a[4 * v + 3]};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    floatx4 o[4];   // row 8 i + lane / 8, columns 4 (lane % 8) .. + 3
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        o[i] = turn[r * 8 + ((lane & 7) ^ ((r >> 1) & 7))];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int m = m0 + 8 * i + (lane >> 3), n = n0 + 4 * (lane & 7);
+        if (m >= g.M) continue;
+        if (n + 3 < g.N && (g.N & 3) == 0) *reinterpret_cast<floatx4 *>(out + (size_t)m * g.N + n) = o[i];
+        else
+            for (int e = 0; e < 4; ++e)
+                if (n + e < g.N) out[(size_t)m * g.N + n + e] = o[i][e];
+    }
+}
 // acc[p][t][e] = Y[m = m_base + 32 t + lane % 32][row 8 (e / 4) + 4 (lane / 32) + e % 4 of the 32 rows that
 // row-blocks rb0 + 2 p and rb0 + 2 p + 1 make]
 // rb_end: row-blocks from here on belong to another workgroup (SwiGLU only)
+// turn: 4 KiB of the wave's own
 template <int NT, int RP, int EPI>
 __device__ __forceinline__ void mm_epilogue(const GemmArgs &g, floatx16 (&acc)[RP][NT], int m_base, int rb0, int split,
-                                            int slot, int lane, int rb_end = 0x7fffffff) {
+                                            int slot, int lane, floatx4 *turn, int rb_end = 0x7fffffff) {
     const int mj = lane & 31, h = lane >> 5;
     if (EPI == EPI_PARTIAL) {
         float *out = g.Yp + (size_t)split * g.split_stride;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int m = m_base + 32 * t + mj;
-            if (m >= g.M) continue;
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int p = 0; p < RP; ++p)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int n = (rb0 + 2 * p) * 16 + 8 * v + 4 * h;
-                    const floatx4 val = {acc[p][t][4 * v], acc[p][t][4 * v + 1], acc[p][t][4 * v + 2], acc[p][t][4 * v + 3]};
-                    if (n + 3 < g.N && (g.N & 3) == 0) *reinterpret_cast<floatx4 *>(out + (size_t)m * g.N + n) = val;
-                    else
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < g.N) out[(size_t)m * g.N + n + e] = val[e];
-                }
-        }
+            for (int p = 0; p < RP; ++p) store_tile(g, out, turn, acc[p][t], m_base + 32 * t, (rb0 + 2 * p) * 16, lane);
     } else if (EPI == EPI_SWIGLU) {
         // a row-block holds 8 gate rows over 8 up rows of the same features: this lane's registers 8 b + c and
         // 8 b + 4 + c are gate and up of feature 8 (rb0 + 2 p + b) + 4 h + c
@@ -579,23 +594,19 @@ __device__ __forceinline__ void mm_epilogue(const GemmArgs &g, floatx16 (&acc)[R
             float best = -INFINITY;
             int idx = 0x7fffffff;
 #pragma unroll
-            for (int p = 0; p < RP; ++p)
+            for (int p = 0; p < RP; ++p) {
+                if (g.Yp) store_tile(g, g.Yp, turn, acc[p][t], m_base + 32 * t, (rb0 + 2 * p) * 16, lane);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int n = (rb0 + 2 * p) * 16 + 8 * (e / 4) + 4 * h + (e % 4);
                     const float v = acc[p][t][e];
-                    if (n < g.N) {
-                        if (g.Yp && m < g.M) g.Yp[(size_t)m * g.N + n] = v;
-                        if (v > best || (v == best && n < idx)) { best = v; idx = n; }
-                    }
+                    if (n < g.N && (v > best || (v == best && n < idx))) { best = v; idx = n; }
                 }
+            }
             const float ov = __shfl_xor(best, 32, 64);
             const int oi = __shfl_xor(idx, 32, 64);
             if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-            if (h == 0 && m < g.M) {
-                g.cand_val[(size_t)m * g.n_cand + slot] = best;
-                g.cand_idx[(size_t)m * g.n_cand + slot] = idx;
-            }
+            if (h == 0 && m < g.M) g.cand[(size_t)slot * g.M + m] = make_uint2(__float_as_uint(best), (uint32_t)idx);
         }
     }
 }
@@ -781,14 +792,16 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 #undef WISV_MM_STAGE_STORE
 #undef WISV_MM_READ_B
 #undef WISV_MM_GROUP
+    __syncthreads();   // every wave is done with the staged operands: the epilogue turns its tiles over there
     if (!active) return;
+    static_assert(2 * BUF >= NW * 4096, "4 KiB of LDS per wave");
     if (SHORT) {
 #pragma unroll
         for (int p = 0; p < RP; ++p)
 #pragma unroll
             for (int t = 0; t < NT; ++t) acc[p][t] = sum[p][t] + acc[p][t];
     }
-    mm_epilogue<NT, RP, EPI>(g, acc, m_base + wm * (32 * NT), rb0, by, bx * WN + wn, lane);
+    mm_epilogue<NT, RP, EPI>(g, acc, m_base + wm * (32 * NT), rb0, by, bx * WN + wn, lane, reinterpret_cast<floatx4 *>(lds) + wave * 256);
 }
 
 // ------------------------------------------------------------------------------------------ tens of rows
@@ -990,6 +1003,7 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
         }
     };
     const int rb0 = bx * RBW + wn * 2 * P + wk * 2, rb_end = min(g.nrb, (bx + 1) * RBW);
+    floatx4 *turn = reinterpret_cast<floatx4 *>(lds + (size_t)NS * STAGE) + wave * 256;   // (the ring may still be filling for the next split)
     Ops o0, o1;
     int st = 0;
     static_assert(NT < 5 || !AHEAD, "several splits per workgroup: the plain loop only");
@@ -1017,7 +1031,7 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
             }
             fetch(st++, o0);
             last(o0, acc[0], whole);
-            if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], 0, rb0, split0 + sp, rb0 >> 1, lane, rb_end);
+            if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], 0, rb0, split0 + sp, rb0 >> 1, lane, turn, rb_end);
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -1077,9 +1091,9 @@ __global__ __launch_bounds__(512) void k_gemm_pipe(GemmArgs g) {
                     out[0][t][4 * e + i] = wk ? ((p0[i] + m0) + p1[i]) + m1 : ((m0 + p0[i]) + m1) + p1[i];
                 }
             }
-        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, out, 0, rb0, split, rb0 >> 1, lane, rb_end);
+        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, out, 0, rb0, split, rb0 >> 1, lane, turn, rb_end);
     } else {
-        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], 0, rb0, split, rb0 >> 1, lane, rb_end);
+        if (rb0 < rb_end) mm_epilogue<NT, 1, EPI>(g, acc[0], 0, rb0, split, rb0 >> 1, lane, turn, rb_end);
     }
 }
 
@@ -1143,8 +1157,9 @@ constexpr int PIPE_RB = 8, PIPE_MAX_ROWS = 160;
 template <int NT, int KC, int RBW, int CH, int EPI, int NPL, bool SHORT = false> static bool launch_pipe_t(Ctx *c, GemmArgs &g, int splits) {
     constexpr int NS = KC == 2 ? 3 : 4;                        // see the kernel: deeper rings measure the same
     constexpr int STAGE = KC * (8 + NPL * NT * 2);             // KiB
-    constexpr size_t lds = (size_t)std::max(NS * STAGE, CH == 4 ? 32 * NT : 0) * 1024;
+    constexpr size_t lds = (size_t)(NS * STAGE + 16) * 1024;   // the ring, and 4 KiB per multiplying wave for the epilogue
     static_assert(lds <= 150 * 1024, "what allow_big_lds asks for");
+    static_assert(CH != 4 || NS * STAGE >= 32 * NT, "the four chains are added up in the ring");
     g.gx = (g.nrb + RBW - 1) / RBW;
     g.gz = 1;
     g.gs = splits;
@@ -1389,11 +1404,10 @@ bool launch_gemm_ws_argmax(Ctx *c, const void *Wt, const ActBuf &X, float *logit
     GemmArgs g{};
     fill_args(g, Wt, X, rows, n, kd);
     g.kt_per_split = g.nkt;
-    g.n_cand = g.nrb;                     // at most one candidate slot per row-block
     g.Yp = logits;
-    g.cand_val = c->cand_val; g.cand_idx = c->cand_idx;
+    g.cand = c->cand_pairs;               // at most one slot per row-block
     const int slots = rows <= 16 ? g.nrb : rows <= PIPE_MAX_ROWS ? g.nrb / 2 : (g.nrb + MM_RB - 1) / MM_RB;
-    c->cand = Candidates{c->cand_val, c->cand_idx, slots, g.n_cand};
+    c->cand = Candidates{c->cand_pairs, nullptr, slots, rows};
     ProfScope ps(c, kclass);
     return rows <= 16 ? launch_ws_t<1, 1, 8, 1, 16, EPI_ARGMAX>(c, g, 1, 70 * 1024)
                       : launch_ws_many<EPI_ARGMAX>(c, g, 1, mm_layout(rows, g.nrb, g.nkt, false, 1), Wh);

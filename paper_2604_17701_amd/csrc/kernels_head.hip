@@ -28,13 +28,12 @@ void launch_pad_cols(Ctx *c, const void *src, void *dst, int rows, int cols, int
 }
 
 // ------------------------------------------------------------------------------------------ greedy tokens
-// lowest index among the largest of n candidates (index i of the logits row itself where idx is null); by a whole workgroup
+// lowest index among the largest of row m's candidates; by a whole workgroup
 template <int NTH> __device__ __forceinline__ void argmax_row(const Candidates &cd, int m, int32_t *amax) {
     __shared__ float bv[NTH / 64];
     __shared__ int bi[NTH / 64];
     const int tid = threadIdx.x;
-    const float *val = cd.val + (size_t)m * cd.stride;
-    const int32_t *idxs = cd.idx ? cd.idx + (size_t)m * cd.stride : nullptr;
+    const float *logits = cd.logits + (size_t)m * cd.n;
     float best = -INFINITY;
     int idx = 0x7fffffff;
     // four candidates per pass, all loads first (slots past the end re-read the last one: same value, same index)
@@ -44,8 +43,14 @@ template <int NTH> __device__ __forceinline__ void argmax_row(const Candidates &
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = min(i0 + NTH * u, cd.n - 1);
-            v[u] = val[i];
-            n[u] = idxs ? idxs[i] : i;
+            if (cd.pairs) {
+                const uint2 p = cd.pairs[(size_t)i * cd.rows + m];
+                v[u] = __uint_as_float(p.x);
+                n[u] = (int)p.y;
+            } else {
+                v[u] = logits[i];
+                n[u] = i;
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)

@@ -460,8 +460,7 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     c->graph_refused = false;
     {
         const size_t n_cand = ws_padded_row_blocks(V);
-        CREATE_TRY(dalloc(c, &c->cand_val, (size_t)R * n_cand));
-        CREATE_TRY(dalloc(c, &c->cand_idx, (size_t)R * n_cand));
+        CREATE_TRY(dalloc(c, &c->cand_pairs, (size_t)R * n_cand));
     }
     CREATE_TRY(dalloc(c, &c->h_t, (size_t)R * d));
     CREATE_TRY(dalloc(c, &c->hu, head_scratch_floats(c, R)));
@@ -512,7 +511,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
     const int out_rows = f.prefill ? 1 : f.rows, out_row0 = f.rows - out_rows;
     auto generic_lm_head = [&] {
         launch_gemm_ref(c, c->a.f, c->lm_head, c->logits, out_rows, g.vocab, d, KC_LMHEAD);
-        c->cand = Candidates{c->logits, nullptr, g.vocab, g.vocab};
+        c->cand = Candidates{nullptr, c->logits, g.vocab, out_rows};
     };
     c->o_planes = ACT_ALL;
     if (c->ws_ok) {

@@ -122,11 +122,12 @@ struct LayerW {
 // product classes whose many-rows kernel may take its activations as one half-precision term (wisv_set_option)
 enum { TERM_QKV = 1, TERM_O = 2, TERM_GATE_UP = 4, TERM_DOWN = 8, TERM_LM_HEAD = 16, TERM_ALL = 31 };
 
-// what the LM head left of every row: n candidates for its greedy token (value, index; idx null: the value's own place)
+// what the LM head left of every row: n candidates for its greedy token, (value, index) [candidate][rows], or (pairs null)
+// its logits [rows][n]
 struct Candidates {
-    const float *val;
-    const int32_t *idx;
-    int n, stride;
+    const uint2 *pairs;
+    const float *logits;
+    int n, rows;
 };
 
 // The buffers a forward runs through.  The rounds of a ctx own one set, sized for the largest of them; a prompt's chunk
@@ -201,8 +202,7 @@ struct Ctx : Scratch {
     float *h_t, *logits;
     float *ss2;                   // [d_model / 16][16]: those of the O projection that folds the FFN norm in
     bool graph_refused;           // a capture of the round failed once: later rounds run eagerly without trying again
-    float *cand_val;
-    int32_t *cand_idx;
+    uint2 *cand_pairs;
     int o_planes;                 // ACT_*: the representations of o that this round's attention kernels write
     float *hu;                    // decision head: first-layer partial sums [split][row][hidden unit]
     float *att_o, *att_m, *att_l; // split-KV attention partials: [split][rows][heads][head_dim], [split][rows][heads]
