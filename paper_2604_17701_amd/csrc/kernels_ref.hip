@@ -178,44 +178,62 @@ void launch_embed(Ctx *c, const Fwd &f, const void *g, const ActBuf &out, float 
 
 // ------------------------------------------------------------------------------------------ GEMM (fallback)
 // Y[r, o] = sum_i A[r, i] W[o, i]; one wave per output feature, MT rows per pass, kd % 8 == 0
-template <typename WT, typename AT, int MT>
-__global__ void k_gemm_ref(const AT *__restrict__ A, const WT *__restrict__ W, float *__restrict__ Y, int rows, int n,
-                           int kd) {
+// SWIGLU: W stacks gate over up; the wave of feature o takes both of its rows and H[r, o] = silu(gate) * up
+// Bound by latency at the small shapes it serves: every row of a pass is requested before the first is used (rows past the last
+// re-read it).  The tiny fp32 target, four rows: 1.5 to 2 us per launch, 1.5 to 2.6 with each row's loads behind a branch, and
+// SwiGLU needs no launch of its own (2 us and a gap); the whole call 178 -> 155 us.
+template <typename WT, typename AT, int MT, bool SWIGLU>
+__global__ void k_gemm_ref(const AT *__restrict__ A, const WT *__restrict__ W, float *__restrict__ Y, ActBuf H, int rows, int n, int kd) {
+    constexpr int NW = SWIGLU ? 2 : 1;
     const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6), r0 = blockIdx.y * MT;
     if (o >= n) return;
-    float acc[MT];
+    float acc[NW][MT];
 #pragma unroll
-    for (int t = 0; t < MT; ++t) acc[t] = 0.f;
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[w][t] = 0.f;
     const WT *wr = W + (size_t)o * kd;
     for (int i = lane * 8; i < kd; i += 512) {
-        float wv[8], av[8];
-        load8<WT>(wr + i, wv);
+        float wv[NW][8], av[MT][8];
 #pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            if (r0 + t < rows) {
-                load8<AT>(A + (size_t)(r0 + t) * kd + i, av);
+        for (int w = 0; w < NW; ++w) load8<WT>(wr + (size_t)w * n * kd + i, wv[w]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[t] = fmaf(av[e], wv[e], acc[t]);
-            }
-        }
+        for (int t = 0; t < MT; ++t) load8<AT>(A + (size_t)min(r0 + t, rows - 1) * kd + i, av[t]);
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[w][t] = fmaf(av[t][e], wv[w][e], acc[w][t]);
     }
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-        float s = wave_sum(acc[t]);
-        if (lane == 0 && r0 + t < rows) Y[(size_t)(r0 + t) * n + o] = s;
+        float s[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s[w] = wave_sum(acc[w][t]);
+        if (lane != 0 || r0 + t >= rows) continue;
+        if (SWIGLU) act_store(H, (size_t)(r0 + t) * n + o, s[0] / (1.0f + expf(-s[0])) * s[NW - 1]);
+        else Y[(size_t)(r0 + t) * n + o] = s[0];
     }
+}
+
+template <int MT, bool SWIGLU> static void launch_gemm_ref_t(Ctx *c, const float *A, const void *W, float *Y, const ActBuf &H, int rows, int n, int kd) {
+    const dim3 grid((n + 3) / 4, (rows + MT - 1) / MT);
+    if (c->bf16)
+        hipLaunchKernelGGL((k_gemm_ref<bf16_t, float, MT, SWIGLU>), grid, dim3(256), 0, c->stream, A, (const bf16_t *)W, Y, H, rows, n, kd);
+    else
+        hipLaunchKernelGGL((k_gemm_ref<float, float, MT, SWIGLU>), grid, dim3(256), 0, c->stream, A, (const float *)W, Y, H, rows, n, kd);
 }
 
 void launch_gemm_ref(Ctx *c, const float *A, const void *W, float *Y, int rows, int n, int kd, int kclass) {
     ProfScope ps(c, kclass);
-    constexpr int MT = 8;
-    dim3 grid((n + 3) / 4, (rows + MT - 1) / MT);
-    if (c->bf16)
-        hipLaunchKernelGGL((k_gemm_ref<bf16_t, float, MT>), grid, dim3(256), 0, c->stream, A,
-                           (const bf16_t *)W, Y, rows, n, kd);
-    else
-        hipLaunchKernelGGL((k_gemm_ref<float, float, MT>), grid, dim3(256), 0, c->stream, A,
-                           (const float *)W, Y, rows, n, kd);
+    if (rows <= 4) launch_gemm_ref_t<4, false>(c, A, W, Y, ActBuf{}, rows, n, kd);
+    else launch_gemm_ref_t<8, false>(c, A, W, Y, ActBuf{}, rows, n, kd);
+}
+
+void launch_gemm_ref_swiglu(Ctx *c, const float *A, const void *W, const ActBuf &H, int rows, int features, int kd) {
+    ProfScope ps(c, KC_GEMM_GATEUP);
+    launch_gemm_ref_t<4, true>(c, A, W, nullptr, H, rows, features, kd);
 }
 
 // ------------------------------------------------------------------------------------------ RoPE + KV append
@@ -369,22 +387,6 @@ void launch_v_reblock(Ctx *c, void *rows, void *plane, int len, bool to_plane) {
     else
         hipLaunchKernelGGL(k_v_reblock<float>, grid, dim3(256), 0, c->stream, (float *)rows, (float *)plane, len, g.head_dim,
                            c->ctx_pad, to_plane);
-}
-
-// ------------------------------------------------------------------------------------------ SwiGLU
-__global__ void k_swiglu(const float *__restrict__ gu, int F, ActBuf h) {
-    const int m = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= F) return;
-    const float g = gu[(size_t)m * 2 * F + i], u = gu[(size_t)m * 2 * F + F + i];
-    act_store(h, (size_t)m * F + i, g / (1.0f + expf(-g)) * u);
-}
-
-void launch_swiglu(Ctx *c, int rows) {
-    ProfScope ps(c, KC_SWIGLU);
-    const int F = c->cfg.d_ff;
-    dim3 grid((F + 255) / 256, rows);
-    hipLaunchKernelGGL(k_swiglu, grid, dim3(256), 0, c->stream, c->gu, F, c->h);
 }
 
 // after a prefill chunk: the slot's length grows by the chunk; after the last one pred_next = the last row's greedy token

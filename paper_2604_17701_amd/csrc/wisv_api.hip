@@ -187,7 +187,6 @@ template <typename Alloc> static bool make_scratch(const Ctx *c, Scratch &s, int
     put(s.x_alt, R * d);
     put(s.y, s.slice_cap * d);
     put(s.qkv, (size_t)s.slice_cap * c->d_qkv);
-    put(s.gu, float_rows * 2 * F);
     put(s.q, R * c->d_q);
     put(s.ss, MAX_SPLITS * std::max<size_t>(R, 16));
     auto act = [&](ActBuf &b, size_t width) {
@@ -558,8 +557,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
                     c->launch_err = "gate/up: the streaming kernel does not serve this shape after a folded RMSNorm";
                     return;
                 }
-                launch_gemm_ref(c, c->a.f, L.wgu, c->gu, f.rows, 2 * F, d, KC_GEMM_GATEUP);
-                launch_swiglu(c, f.rows);
+                launch_gemm_ref_swiglu(c, c->a.f, L.wgu, c->h, f.rows, F, d);
             }
         };
         int ny = 0;
@@ -647,8 +645,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
         launch_attn_ref(c, f, l);
         launch_gemm_ref(c, c->o.f, L.wo, c->y, f.rows, d, c->d_q, KC_GEMM_O);
         launch_rmsnorm(c, f.rows, 1, L.ffn_norm, c->a, nullptr);                   // + attention update
-        launch_gemm_ref(c, c->a.f, L.wgu, c->gu, f.rows, 2 * F, d, KC_GEMM_GATEUP);
-        launch_swiglu(c, f.rows);
+        launch_gemm_ref_swiglu(c, c->a.f, L.wgu, c->h, f.rows, F, d);
         launch_gemm_ref(c, c->h.f, L.wdown, c->y, f.rows, d, F, KC_GEMM_DOWN);
     }
     if (f.prefill && !f.want_last) return;
@@ -1316,7 +1313,7 @@ extern "C" int wisv_calibration_copy(wisv_ctx *ctx, void *dst, const void *src, 
 }
 
 static const char *kClassNames[KC_COUNT] = {"embed", "rmsnorm", "gemm_qkv", "gemm_gate_up", "rope_append", "attention", "attention_combine",
-                                            "swiglu", "lm_head", "argmax", "head", "decide", "spec_sampling", "event_pair_overhead",
+                                            "lm_head", "argmax", "head", "decide", "spec_sampling", "event_pair_overhead",
                                             "gemm_o", "gemm_down"};
 
 extern "C" int wisv_profile_enable(wisv_ctx *ctx, int32_t on) {

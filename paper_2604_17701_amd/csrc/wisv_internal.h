@@ -108,7 +108,7 @@ inline ActBuf act_planes(ActBuf a, int planes) {
 
 // ---------------------------------------------------------------- kernel classes (for per-kernel timing)
 enum KernelClass {
-    KC_EMBED = 0, KC_NORM, KC_GEMM_QKV, KC_GEMM_GATEUP, KC_ROPE, KC_ATTN, KC_ATTN_COMBINE, KC_SWIGLU, KC_LMHEAD,
+    KC_EMBED = 0, KC_NORM, KC_GEMM_QKV, KC_GEMM_GATEUP, KC_ROPE, KC_ATTN, KC_ATTN_COMBINE, KC_LMHEAD,
     KC_ARGMAX, KC_HEAD, KC_DECIDE, KC_SS, KC_EMPTY, KC_GEMM_O, KC_GEMM_DOWN, KC_COUNT
 };
 
@@ -138,7 +138,7 @@ struct Scratch {
     float *x, *x_alt;             // residual stream; a product that folds the norm in reads x and writes x_alt
     float *y, *qkv;               // slice_cap rows of partial slices each
     int slice_cap;                // k-split slices x rows that y and qkv hold
-    float *gu, *q;                // generic kernels: gate and up; rotated queries [rows][d_q]
+    float *q;                     // generic kernels: rotated queries [rows][d_q]
     float *ss;                    // [MAX_SPLITS][max(rows, 16)]: sums of squares left by a product that folds the norm in
     ActBuf a, o, h;               // normalised activations, attention output, SwiGLU output
 };
@@ -257,10 +257,11 @@ void launch_rmsnorm(Ctx *c, int rows, int n_partial, const void *g, const ActBuf
                     float *ss_out = nullptr);
 // Y[rows, n] = A[rows, kd] * W[n, kd]^T (float accumulate, float out)
 void launch_gemm_ref(Ctx *c, const float *A, const void *W, float *Y, int rows, int n, int kd, int kclass);
+// H = silu(gate) * up with W = gate over up [2 features, kd]
+void launch_gemm_ref_swiglu(Ctx *c, const float *A, const void *W, const ActBuf &H, int rows, int features, int kd);
 // n_ss > 0: the slices are scaled by 1 / rms from the n_ss partial sums of squares in c->ss (folded RMSNorm)
 void launch_rope_append(Ctx *c, const Fwd &f, int layer, int n_partial, int n_ss = 0);
 void launch_attn_ref(Ctx *c, const Fwd &f, int layer);
-void launch_swiglu(Ctx *c, int rows);
 // kv_len[slot] = new_len; pred_next[slot] = amax[row] unless row is negative
 void launch_set_pred_next(Ctx *c, int slot, int row, int new_len);
 
