@@ -427,20 +427,28 @@ __global__ __launch_bounds__(64 * WISV_MAX_K) void k_decide(DecideArgs a) {
     }
 }
 
-// How the first layer is cut: tiles of RB x NT operands and as many splits of the columns (of at least eight k-tiles) as make one
-// round of 256 workgroups
+// How the first layer is cut: two or four row-blocks x one or two tiles of 16 positions, and as many splits of the columns (of at
+// least eight k-tiles) as make one round of 256 workgroups; of the two the one whose workgroups read less (a row-block of W1
+// costs a KiB per k-tile, 16 positions two KiB)
 struct HeadCut { int rb, nt, gx, tiles, splits, kt_per_split; };
 static HeadCut head_cut(int rows, int nrb, int nkt) {
-    HeadCut h;
     const int pos = (rows + 15) / 16;
-    h.rb = pos <= 16 ? 2 : 4;
-    h.nt = pos == 1 ? 1 : 2;
-    h.gx = (nrb + h.rb - 1) / h.rb;
-    h.tiles = (pos + h.nt - 1) / h.nt;
-    const int s = std::max(1, std::min(std::min(HEAD_MAX_SPLITS, 256 / (h.gx * h.tiles)), nkt / 8));
-    h.kt_per_split = (nkt + s - 1) / s;
-    h.splits = (nkt + h.kt_per_split - 1) / h.kt_per_split;
-    return h;
+    HeadCut best{};
+    double least = 0;
+    for (int rb : {2, 4}) {
+        HeadCut h;
+        h.rb = rb;
+        h.nt = pos == 1 ? 1 : 2;
+        if (h.nt == 1 && rb == 4) break;
+        h.gx = (nrb + h.rb - 1) / h.rb;
+        h.tiles = (pos + h.nt - 1) / h.nt;
+        const int s = std::max(1, std::min(std::min(HEAD_MAX_SPLITS, 256 / (h.gx * h.tiles)), nkt / 8));
+        h.kt_per_split = (nkt + s - 1) / s;
+        h.splits = (nkt + h.kt_per_split - 1) / h.kt_per_split;
+        const double reads = (double)(h.rb + 2 * h.nt) * h.kt_per_split * ((h.gx * h.tiles * h.splits + 255) / 256);
+        if (!best.rb || reads < least) best = h, least = reads;
+    }
+    return best;
 }
 static bool head_tiled(const Ctx *c) { return c->head_w1_t && c->cfg.d_draft % 8 == 0; }
 size_t head_scratch_floats(const Ctx *c, int rows) {
