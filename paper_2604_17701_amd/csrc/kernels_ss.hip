@@ -211,6 +211,8 @@ k_ss_sample(int V, int C, int rows, int max_batch, bool vec, int commit, const f
     __shared__ int s_chunk, s_lastc, s_first, s_last;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int rs = sel_row[b], mode = sel_mode[b];
+    const float M = row_m[rs], vb = v[b];   // requested before anything waits
+    const double Z = row_z[rs];
     if (mode != 0) {   // the whole block takes the same side
         double *cw = s_chunks, *cex = s_chunks + C;
         if (tid == 0) { s_chunk = 0x7fffffff; s_lastc = 0; s_first = 0x7fffffff; s_last = -1; }
@@ -223,7 +225,7 @@ k_ss_sample(int V, int C, int rows, int max_batch, bool vec, int commit, const f
             if (c < C) { cw[c] = m; cex[c] = ex; }
             carry += tile_total;
         }
-        const double target = (double)v[b] * carry;
+        const double target = (double)vb * carry;
         __syncthreads();
         for (int c = tid; c < C; c += SS_THREADS)
             if (cw[c] > 0.0) {
@@ -237,8 +239,6 @@ k_ss_sample(int V, int C, int rows, int max_batch, bool vec, int commit, const f
         float x[8], qv[8];
         ss_load8(logits + (size_t)rs * V, i0, V, vec, -INFINITY, x);
         ss_load8(q + (size_t)min(rs + 1, rows - 1) * V, i0, V, vec, 0.f, qv);
-        const float M = row_m[rs];
-        const double Z = row_z[rs];
         double w[8], ts = 0.0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) { w[e] = ss_weight(x[e], qv[e], M, Z, mode == 1); ts += w[e]; }
