@@ -230,7 +230,10 @@ __device__ __forceinline__ void ws_epilogue(const GemmArgs &g, floatx4 (&acc)[RB
 // of k_attn_combine: weights e^(m_s - max m), splits in index order), so that no kernel of its own has to do it.
 // PRO_NORM: the activations are the residual stream plus the previous product's slices, times the norm gain (see
 // GemmArgs); WK == 1 and a single activation chunk
-template <int NT, int RB, int WR, int WK, int U, int PRO, int EPI>
+// WHOLE: every wave has a whole number of ring turns (the launcher checks), so no load and no product is guarded: the guarded
+// last turn waits for each of its loads in turn.  us per launch over 4 / 15 rows: gate/up 38.6 / 41.9 -> 37.9 / 40.5, down
+// 18.8 / 19.9 -> 18.1 / 19.1, O with the residual inside (eight k-tiles per wave, all requested at once) 12.1 -> 11.7.
+template <int NT, int RB, int WR, int WK, int U, int PRO, int EPI, bool WHOLE>
 __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_ws(GemmArgs g) {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int NTH = 64 * WR * WK;
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int r = 0; r < RB; ++r)
-                if (u < myn) abuf[u][r] = __builtin_nontemporal_load(wp[r] + (size_t)u * 64);
+                if (WHOLE || u < myn) abuf[u][r] = __builtin_nontemporal_load(wp[r] + (size_t)u * 64);
     }
 
     floatx4 acc[RB][NT];
@@ -457,6 +460,12 @@ __global__ __launch_bounds__(64 * WR * WK, PRO == PRO_NORM ? 6 : 1) void k_gemm_
                 for (int r = 0; r < RB; ++r) abuf[u][r] = __builtin_nontemporal_load(wp[r] + (size_t)(kt + u + U) * 64);
                 __builtin_amdgcn_sched_barrier(0);
             }
+        }
+        if (WHOLE) {   // the last turn
+            if (kt < kend)
+#pragma unroll
+                for (int u = 0; u < U; ++u) mfma_tile(buf, kt + u - ch * kcw, abuf[u]);
+            continue;
         }
         // the last tiles of the slice (and slices shorter than 2 U): guarded
         for (; kt < kend; kt += U) {
@@ -1106,8 +1115,8 @@ static size_t ws_lds(int Mt, int kcw, int sub, int NT, int RB, int WR, int WK) {
     return std::max(x, red);
 }
 
-template <int NT, int RB, int WR, int WK, int U, int EPI, int PRO = PRO_NONE>
-static bool launch_ws_t(Ctx *c, GemmArgs &g, int splits, size_t soft_budget) {
+template <int NT, int RB, int WR, int WK, int U, int EPI, int PRO, bool WHOLE>
+static bool launch_ws_u(Ctx *c, GemmArgs &g, int splits, size_t soft_budget) {
     const int sub = (g.kt_per_split + WK - 1) / WK, Mt = std::min(g.M, 16 * NT);
     // largest chunk (a multiple of U) within the soft budget, else within what a CU has
     int kcw = (sub + U - 1) / U * U;
@@ -1126,11 +1135,19 @@ static bool launch_ws_t(Ctx *c, GemmArgs &g, int splits, size_t soft_budget) {
     if (lds > 150 * 1024) return false;
     g.kcw = kcw;
     static bool allowed[MAX_DEVICES];     // per instantiation
-    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_ws<NT, RB, WR, WK, U, PRO, EPI>), allowed))
+    if (lds > 64 * 1024 && !allow_big_lds(c, reinterpret_cast<const void *>(&k_gemm_ws<NT, RB, WR, WK, U, PRO, EPI, WHOLE>), allowed))
         return false;
     dim3 grid((g.nrb / RB + WR - 1) / WR, splits, (g.M + 16 * NT - 1) / (16 * NT));
-    hipLaunchKernelGGL((k_gemm_ws<NT, RB, WR, WK, U, PRO, EPI>), grid, dim3(64 * WR * WK), lds, c->stream, g);
+    hipLaunchKernelGGL((k_gemm_ws<NT, RB, WR, WK, U, PRO, EPI, WHOLE>), grid, dim3(64 * WR * WK), lds, c->stream, g);
     return true;
+}
+// U: ring slots of the guarded form; UW: of the form for slices of whole turns, taken where the shape has them (every matrix of
+// the 8B shape does)
+template <int NT, int RB, int WR, int WK, int U, int UW, int EPI, int PRO = PRO_NONE>
+static bool launch_ws_t(Ctx *c, GemmArgs &g, int splits, size_t soft_budget) {
+    const bool whole = g.nkt == splits * g.kt_per_split && g.kt_per_split % (WK * UW) == 0 && g.nrb % (RB * WR) == 0;
+    if (whole) return launch_ws_u<NT, RB, WR, WK, UW, EPI, PRO, true>(c, g, splits, soft_budget);
+    return launch_ws_u<NT, RB, WR, WK, U, EPI, PRO, false>(c, g, splits, soft_budget);
 }
 
 constexpr int MM_RP = 2;            // pairs of row-blocks per wave of k_gemm_mm
@@ -1281,6 +1298,13 @@ static void fill_args(GemmArgs &g, const void *Wt, const ActBuf &X, int rows, in
     g.nrb = ws_padded_row_blocks(n); g.nkt = kd / 32;
 }
 
+// Slices of 8 k-tiles (QKV and O at the 8B shape) stay at a ring of four (of eight: QKV 9.4 -> 9.9 us, O 6.3 -> 6.8), slices of
+// 28 (down) take four turns of seven (18.8 -> 18.1)
+static bool launch_ws_partial_t(Ctx *c, GemmArgs &g, int splits) {
+    if (g.kt_per_split % 7) return launch_ws_t<1, 1, 8, 1, 4, 4, EPI_PARTIAL>(c, g, splits, 40 * 1024);
+    return launch_ws_t<1, 1, 8, 1, 4, 7, EPI_PARTIAL>(c, g, splits, 40 * 1024);
+}
+
 // Y partial slices: returns the number of slices written to `Yp` ([S][split_stride]), 0 if the shape cannot
 // be served (nothing was launched)
 int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, size_t split_stride, int max_splits,
@@ -1322,9 +1346,9 @@ int launch_gemm_ws_partial(Ctx *c, const void *Wt, const ActBuf &X, float *Yp, s
         if (rows > 16 || ap->splits < 1 || ap->splits > WS_PRO_SPLITS || kd != ap->heads * 128) return 0;
         g.att_o = ap->o; g.att_m = ap->m; g.att_l = ap->l;
         g.att_splits = ap->splits; g.att_rows = ap->rows; g.att_H = ap->heads;
-        return launch_ws_t<1, 1, 8, 1, 4, EPI_PARTIAL, PRO_ATTN>(c, g, splits, 40 * 1024) ? splits : 0;
+        return launch_ws_t<1, 1, 8, 1, 4, 4, EPI_PARTIAL, PRO_ATTN>(c, g, splits, 40 * 1024) ? splits : 0;
     }
-    const bool ok = rows <= 16 ? launch_ws_t<1, 1, 8, 1, 4, EPI_PARTIAL>(c, g, splits, 40 * 1024)
+    const bool ok = rows <= 16 ? launch_ws_partial_t(c, g, splits)
                                : launch_ws_many<EPI_PARTIAL>(c, g, splits, layout, Wh, short_chains);
     return ok ? splits : 0;
 }
@@ -1347,7 +1371,7 @@ int launch_gemm_ws_normfold(Ctx *c, const void *Wt, const float *x_in, float *x_
     const int splits = (g.nkt + g.kt_per_split - 1) / g.kt_per_split;
     g.xin = x_in; g.xout = x_out; g.ys = c->y; g.ys_stride = (size_t)c->slice_rows * kd; g.n_partial = n_partial;
     g.gain = (const bf16_t *)gain; g.ss_out = ss;
-    return launch_ws_t<1, 1, 8, 1, 4, EPI_PARTIAL, PRO_NORM>(c, g, splits, 40 * 1024) ? splits : 0;
+    return launch_ws_t<1, 1, 8, 1, 4, 4, EPI_PARTIAL, PRO_NORM>(c, g, splits, 40 * 1024) ? splits : 0;
 }
 
 // A product that closes a residual branch, complete inside one kernel (at most 16 rows): one row-block per
@@ -1366,9 +1390,9 @@ int launch_gemm_ws_resid(Ctx *c, const void *Wt, const ActBuf &X, const AttnPart
     if (ap) {
         g.att_o = ap->o; g.att_m = ap->m; g.att_l = ap->l;
         g.att_splits = ap->splits; g.att_rows = ap->rows; g.att_H = ap->heads;
-        return launch_ws_t<1, 1, 1, 16, 4, EPI_RESID, PRO_ATTN>(c, g, 1, 150 * 1024) ? n / 16 : 0;
+        return launch_ws_t<1, 1, 1, 16, 4, 8, EPI_RESID, PRO_ATTN>(c, g, 1, 150 * 1024) ? n / 16 : 0;
     }
-    return launch_ws_t<1, 1, 1, 16, 4, EPI_RESID>(c, g, 1, 150 * 1024) ? n / 16 : 0;
+    return launch_ws_t<1, 1, 1, 16, 4, 8, EPI_RESID>(c, g, 1, 150 * 1024) ? n / 16 : 0;
 }
 
 // gate/up with the SwiGLU fused (single split): H[rows][F] = silu(gate) * up.  Every row-block of the
@@ -1389,8 +1413,8 @@ bool launch_gemm_ws_swiglu(Ctx *c, const void *Wt, const ActBuf &X, const ActBuf
         // no k-split here, so the workgroup count is fixed by the shape: seven waves per workgroup when that fills
         // whole rounds of 256 CUs better than eight (14336 features: 256 workgroups instead of 224)
         auto fill = [&](int wr) { const int wgs = (g.nrb + wr - 1) / wr; return (double)wgs / ((wgs + 255) / 256 * 256); };
-        if (fill(7) > fill(8)) return launch_ws_t<1, 1, 7, 1, 16, EPI_SWIGLU>(c, g, 1, 36 * 1024);
-        return launch_ws_t<1, 1, 8, 1, 16, EPI_SWIGLU>(c, g, 1, 36 * 1024);
+        if (fill(7) > fill(8)) return launch_ws_t<1, 1, 7, 1, 16, 16, EPI_SWIGLU>(c, g, 1, 36 * 1024);
+        return launch_ws_t<1, 1, 8, 1, 16, 16, EPI_SWIGLU>(c, g, 1, 36 * 1024);
     }
     // more than 16 rows: H has one consumer, the down projection, and `planes` names the representation it reads;
     // the others (at 512 rows 59 of 73 MB) are not written
@@ -1409,7 +1433,7 @@ bool launch_gemm_ws_argmax(Ctx *c, const void *Wt, const ActBuf &X, float *logit
     const int slots = rows <= 16 ? g.nrb : rows <= PIPE_MAX_ROWS ? g.nrb / 2 : (g.nrb + MM_RB - 1) / MM_RB;
     c->cand = Candidates{c->cand_pairs, nullptr, slots, rows};
     ProfScope ps(c, kclass);
-    return rows <= 16 ? launch_ws_t<1, 1, 8, 1, 16, EPI_ARGMAX>(c, g, 1, 70 * 1024)
+    return rows <= 16 ? launch_ws_t<1, 1, 8, 1, 16, 16, EPI_ARGMAX>(c, g, 1, 70 * 1024)
                       : launch_ws_many<EPI_ARGMAX>(c, g, 1, mm_layout(rows, g.nrb, g.nkt, false, 1), Wh);
 }
 

@@ -450,6 +450,17 @@ def test_small_bf16_decoder_folded_norms(batch, k):
     _run_workload(w, TOL_BF16, kv="prefill")
 
 
+@pytest.mark.parametrize("batch,k,d_ff", [(1, 4, 14336), (1, 9, 14336), (4, 4, 14336), (1, 4, 14304), (3, 5, 14304)])
+def test_streaming_products_of_whole_turns_and_with_remainders(batch, k, d_ff):
+    """At most 16 rows, products whose waves have whole turns of their weight ring (gate/up and LM head two of 16 k-tiles, down four
+    of seven, O two of four or one of eight) and, with 14304 features, a last slice one k-tile short of them."""
+    model = replace(MID128, n_layers=1, d_model=1024, n_heads=32, n_kv_heads=8, d_ff=d_ff, vocab=2003)
+    protos = tuple(PROTO_FH if b % 2 == 0 else PROTO_SH for b in range(batch))
+    w = replace(configs.get(1), model=model, batch=batch, ctx=70, k=k, protos=protos, kv_source="synthetic",
+                name=f"turns_b{batch}_k{k}_f{d_ff}", index=51, match_rate=(0.5, 0.5))
+    _run_workload(w, TOL_BF16, kv="synthetic")
+
+
 def test_small_bf16_decoder_synthetic_kv():
     w = replace(configs.get(2), model=replace(MID, head_dim=128, n_heads=4, n_kv_heads=1), batch=2, ctx=1100, k=8,
                 protos=(PROTO_SH, PROTO_FH), name="mid_bf16_synthkv", index=8)
