@@ -192,6 +192,11 @@ struct Ctx : Scratch {
     // copies to d_in as it is; the last kernel writes the results straight into io_out (pinned as well)
     unsigned char *io_in, *io_out, *d_in;
     size_t io_in_bytes;
+    // pinned memory behind io_out that wisv_debug_copy reads results through, and when each piece of it has been written
+    static constexpr int READ_PIECES = 3;
+    static constexpr size_t READ_PIECE = (size_t)256 << 10;
+    unsigned char *read_stage;
+    hipEvent_t read_done[READ_PIECES];
     // outputs of a host-pointer sampling round
     int32_t *d_alen, *d_ytok;
     float *d_pacc;

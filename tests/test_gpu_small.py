@@ -461,6 +461,30 @@ def test_streaming_products_of_whole_turns_and_with_remainders(batch, k, d_ff):
     _run_workload(w, TOL_BF16, kv="synthetic")
 
 
+def test_kept_logits_in_one_piece_in_many_and_by_the_runtime_s_copy_agree():
+    """wisv_debug_copy: a multiple of 16 bytes comes through pinned pieces of 256 KiB, three of them ahead of the host, other sizes
+    by the runtime's copy.  The same bytes whichever way, at the edges of a piece, of the three and of the whole."""
+    w = replace(W0, model=replace(W0.model, vocab=50003), batch=1, k=8, name="tiny_read_back", index=52)
+    dev = torch.device("cuda:0")
+    ctx = _ctx(w, gen.make_weights(w.model, w.seed, dev))
+    ctx.wisv_prefill(0, gen.context_tokens(w, 0))
+    rows = np.arange(w.k)
+    csi = gen.csi_features(w)
+    g = ctx.wisv_verify_round([0], np.arange(w.k), [PROTO_FH], gen.draft_hidden(w, 0), rows, csi[:1], [0.5], w.k,
+                              binding.WISV_FLAG_NO_COMMIT | binding.WISV_FLAG_KEEP_LOGITS)
+    whole = ctx.wisv_debug_copy(binding.WISV_DBG_LOGITS, w.k)
+    assert np.array_equal(whole.argmax(1), np.asarray(g["target_argmax"]).reshape(-1)[1:w.k + 1])
+    whole = whole.reshape(-1).view(np.uint32)
+    assert whole.nbytes % 16 == 0 and len(set(whole[::101].tolist())) > 1000
+    piece = (256 << 10) // 4
+    for n in (4, 8, piece - 4, piece, piece + 4, 3 * piece - 4, 3 * piece, 3 * piece + 4, 4 * piece, whole.size):
+        for m in (n, n - 1):
+            part = np.full(n + 4, 0x7fc01234, np.uint32)
+            ctx._check(ctx._lib.wisv_debug_copy(ctx._h, binding.WISV_DBG_LOGITS, part.ctypes.data, 4 * m))
+            assert np.array_equal(part[:m], whole[:m]) and (part[m:] == 0x7fc01234).all(), (n, m)
+    ctx.wisv_destroy()
+
+
 def test_small_bf16_decoder_synthetic_kv():
     w = replace(configs.get(2), model=replace(MID, head_dim=128, n_heads=4, n_kv_heads=1), batch=2, ctx=1100, k=8,
                 protos=(PROTO_SH, PROTO_FH), name="mid_bf16_synthkv", index=8)
