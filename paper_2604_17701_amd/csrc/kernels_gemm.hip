@@ -838,7 +838,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs g) {
 // activations every workgroup re-reads from L2.  Against the workgroups it replaced, us per launch at the 8B shape, 32 /
 // 96 / 143 rows: gate/up 49.0 / 61.8 / 76.3 -> 38.0 / 42.8 / 49.2, down 23.6 / 33.3 / 40.9 -> 19.6 / 24.6 / 34.6,
 // QKV (two terms) 14.1 / 20.4 / 27.3 -> 10.3 / 18.4 / 23.1, O (two terms) 10.9 / 14.8 / 20.4 -> 8.3 / 12.4 / 16.8, LM head of
-// 32000 tokens 53.3 / 70.0 / 82.8 -> 45.4 / 49.4 / 55.1, of 128256 tokens over 28 rows 207 -> 188.
+// 32000 tokens 53.3 / 70.0 / 82.8 -> 45.4 / 49.4 / 55.1, of 128256 tokens over 28 rows 207 -> 188 (results still leaving in
+// 16-byte pieces; what whole lines took off stands at store_tile).
 
 // a wave-uniform pointer, in scalar registers
 __device__ __forceinline__ const unsigned char *scalar_ptr(const void *p) {
