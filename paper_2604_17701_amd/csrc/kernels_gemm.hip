@@ -533,7 +533,8 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // rows 108.5 -> 104.5; O over 143 rows 16.7 -> 16.0; 32 and 96 rows the same.  What an epilogue still costs is its bytes: 143 rows
 // leave 18 MB of QKV slices, 4 us.  SwiGLU's 2-byte results gain nothing this way (512 rows 115.2 -> 116, 1000 rows 225 -> 228).
 // Candidates for the greedy token lie [slot][row]: a wave's 32 rows fill whole lines, where [row][slot] put 4 bytes of every
-// XCD into each (LM head of 32000 tokens over 143 rows 60.8 -> 57.8 us).
+// XCD into each (LM head of 32000 tokens over 143 rows 60.8 -> 57.8 us, of 128256 tokens over 96 rows 213 -> 190, over 143 rows
+// 245 -> 222; the search that reads them is search_candidates, 7.0 us over either before and 6.4 and 6.8 now).
 // one 32 x 32 tile of plain results to rows m0 .., columns n0 ..
 __device__ __forceinline__ void store_tile(const GemmArgs &g, float *out, floatx4 *turn, const floatx16 &a, int m0, int n0, int lane) {
     const int mj = lane & 31, h = lane >> 5;

@@ -28,54 +28,47 @@ void launch_pad_cols(Ctx *c, const void *src, void *dst, int rows, int cols, int
 }
 
 // ------------------------------------------------------------------------------------------ greedy tokens
-// lowest index among the largest of row m's candidates; by a whole workgroup
-template <int NTH> __device__ __forceinline__ void argmax_row(const Candidates &cd, int m, int32_t *amax) {
-    __shared__ float bv[NTH / 64];
-    __shared__ int bi[NTH / 64];
-    const int tid = threadIdx.x;
-    const float *logits = cd.logits + (size_t)m * cd.n;
-    float best = -INFINITY;
+// Bound by latency: a round trip of eight loads per thread and the merge.  Candidates lie [slot][row] (see store_tile), so lanes
+// run along the rows of a line first and along the slots after that; with a workgroup for each row, which uses 8 bytes of a line,
+// and one part the search took, us per launch of its own at 128256 tokens over 4 / 15 / 96 / 143 / 512 rows, 7.5 / 12.5 / 9.4 / 9.3
+// / 13.7, now 2.1 / 2.7 / 1.9 / 2.3 / 3.0 (event pairs less the 4.5 of an empty one).
+template <int NTH> __device__ __forceinline__ void search_candidates(const Candidates &cd, const GreedyCut &cut, int wg, uint2 *best) {
+    __shared__ float bv[NTH / 64][16];
+    __shared__ int bi[NTH / 64][16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, width = 1 << cut.shift, step = NTH >> cut.shift;
+    const int part = wg % cut.parts, r = tid & (width - 1), m = (wg / cut.parts << cut.shift) + r, mc = min(m, cd.rows - 1);
+    const int end = min(cd.n, (part + 1) * cut.per);
+    float v = -INFINITY;
     int idx = 0x7fffffff;
-    // four candidates per pass, all loads first (slots past the end re-read the last one: same value, same index)
-    for (int i0 = tid; i0 < cd.n; i0 += 4 * NTH) {
-        float v[4];
-        int n[4];
+    for (int i0 = part * cut.per + (tid >> cut.shift); i0 < end; i0 += 8 * step) {
+        uint2 p[8];   // candidates past the end re-read the last one: same value, same index
+        if (cd.pairs) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = min(i0 + NTH * u, cd.n - 1);
-            if (cd.pairs) {
-                const uint2 p = cd.pairs[(size_t)i * cd.rows + m];
-                v[u] = __uint_as_float(p.x);
-                n[u] = (int)p.y;
-            } else {
-                v[u] = logits[i];
-                n[u] = i;
+            for (int u = 0; u < 8; ++u) p[u] = cd.pairs[(size_t)min(i0 + step * u, end - 1) * cd.rows + mc];
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = min(i0 + step * u, end - 1);
+                p[u] = make_uint2(__float_as_uint(cd.logits[(size_t)mc * cd.n + i]), i);
             }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (v[u] > best || (v[u] == best && n[u] < idx)) { best = v[u]; idx = n[u]; }
+        for (int u = 0; u < 8; ++u) keep_better(v, idx, __uint_as_float(p[u].x), (int)p[u].y);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(idx, o, 64);
-        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-    }
-    if ((tid & 63) == 0) { bv[tid >> 6] = best; bi[tid >> 6] = idx; }
+    for (int o = 32; o >= width; o >>= 1) keep_better(v, idx, __shfl_xor(v, o, 64), __shfl_xor(idx, o, 64));
+    if (lane < width) { bv[wave][lane] = v; bi[wave][lane] = idx; }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < NTH / 64; ++w)
-            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) { best = bv[w]; idx = bi[w]; }
-        amax[m] = idx == 0x7fffffff ? 0 : idx;
-    }
+    if (tid >= width || m >= cd.rows) return;
+    for (int w = 1; w < NTH / 64; ++w) keep_better(v, idx, bv[w][tid], bi[w][tid]);
+    best[(size_t)m * GREEDY_PARTS + part] = make_uint2(__float_as_uint(v), (uint32_t)idx);
 }
 
-__global__ __launch_bounds__(512) void k_argmax(Candidates cd, int32_t *amax) { argmax_row<512>(cd, blockIdx.x, amax); }
+__global__ __launch_bounds__(512) void k_argmax(Candidates cd, GreedyCut cut, uint2 *best) { search_candidates<512>(cd, cut, blockIdx.x, best); }
 
-void launch_argmax(Ctx *c, int rows) {
+void launch_argmax(Ctx *c) {
     ProfScope ps(c, KC_ARGMAX);
-    hipLaunchKernelGGL(k_argmax, dim3(rows), dim3(512), 0, c->stream, c->cand, c->amax);
+    const GreedyCut cut = greedy_cut(c->cand);
+    hipLaunchKernelGGL(k_argmax, dim3(cut.wgs), dim3(512), 0, c->stream, c->cand, cut, c->best);
 }
 
 // ------------------------------------------------------------------------------------------ the head's first layer
@@ -109,10 +102,11 @@ struct HeadArgs {
     const void *b1, *w2;
     float *u;                  // bf16 path: first-layer partial sums [split][rows][16 nrb]; generic: second-layer sums [rows]
     int gx, tiles, kt_per_split;   // bf16 path: workgroups along the hidden units and the positions; columns of a split
-    // the first argmax_rows workgroups find greedy tokens instead
+    // workgroups from search0 on look for greedy tokens instead
     Candidates cand;
-    int argmax_rows;
-    int32_t *amax;
+    GreedyCut cut;
+    int search0;
+    uint2 *best;
 };
 
 // the uploaded row of position m, or -1
@@ -136,11 +130,11 @@ __device__ __forceinline__ float head_act(int act, float v) { return act == WISV
 // A operand meets NT B operands and every B operand RB A operands) and requests TB k-tiles at a time
 template <int WK, int RB, int NT, int TB>
 __global__ __launch_bounds__(64 * WK) void k_head_fused(HeadArgs a) {
-    if ((int)blockIdx.x < a.argmax_rows) {
-        argmax_row<64 * WK>(a.cand, blockIdx.x, a.amax);
+    if ((int)blockIdx.x >= a.search0) {
+        search_candidates<64 * WK>(a.cand, a.cut, blockIdx.x - a.search0, a.best);
         return;
     }
-    const int wg = blockIdx.x - a.argmax_rows, rb0 = wg % a.gx * RB, tile0 = wg / a.gx % a.tiles * NT, split = wg / (a.gx * a.tiles);
+    const int wg = blockIdx.x, rb0 = wg % a.gx * RB, tile0 = wg / a.gx % a.tiles * NT, split = wg / (a.gx * a.tiles);
     const int tid = threadIdx.x, lane = tid & 63, wk = tid >> 6, bj = lane & 15, bg = lane >> 4;
     int m[NT], hr[NT];
     bool sc[NT], any = false;
@@ -301,11 +295,11 @@ template <typename WT>
 __global__ __launch_bounds__(1024) void k_head_ref(HeadArgs a) {
     constexpr int UJ = 4, GROUP = 16 * UJ * 4;            // hidden units per wave at once; per pass over val
     __shared__ float val[GROUP], red[4];
-    if ((int)blockIdx.x < a.argmax_rows) {
-        argmax_row<1024>(a.cand, blockIdx.x, a.amax);
+    if ((int)blockIdx.x >= a.search0) {
+        search_candidates<1024>(a.cand, a.cut, blockIdx.x - a.search0, a.best);
         return;
     }
-    const int m = blockIdx.x - a.argmax_rows, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hr = head_row(a.hd_row, a.n_hd, m);
     if (hr < 0) return;
     float t = 0.f;
@@ -346,8 +340,9 @@ __global__ __launch_bounds__(1024) void k_head_ref(HeadArgs a) {
 // shuffle tree); threshold.  Then the first wave finds the earliest rejected position, and the commit.
 struct DecideArgs {
     int batch, k, rows, max_batch, gate_all, commit, act;
-    const int32_t *stream_ids, *tokens, *proto, *amax, *hd_row;
-    int n_hd;
+    const int32_t *stream_ids, *tokens, *proto, *hd_row;
+    const uint2 *best;         // the rows' greedy tokens, in parts
+    int parts, n_hd;
     const float *tau;
     const float *u;            // first-layer partial sums [splits][rows][16 nrb], or (splits == 0) second-layer sums [rows]
     int splits, dJ, nrb;
@@ -361,14 +356,14 @@ struct DecideArgs {
 constexpr int HEAD_MAX_SPLITS = 8;
 __global__ __launch_bounds__(64 * WISV_MAX_K) void k_decide(DecideArgs a) {
     __shared__ int flags[WISV_MAX_K];   // 1: mismatch, 2: rejected, 4: wanted for the decision but not uploaded
+    __shared__ int greedy[WISV_MAX_K];
     const int b = blockIdx.x, lane = threadIdx.x & 63, j = threadIdx.x >> 6, m = b * a.k + j;
     const int slot = min(max(a.stream_ids[b], 0), a.max_batch - 1);
-    const int before = a.amax[max(m - 1, 0)], own = a.amax[m], token = a.tokens[m], proto = a.proto[b];
+    const int token = a.tokens[m], proto = a.proto[b];
     const int hr = head_row(a.hd_row, a.n_hd, m);
     const float tau = a.tau[b];
     const int pn = a.pred_next[slot];
-    const bool mismatch = token != (j == 0 ? pn : before);
-    const bool sc = (a.gate_all || proto == WISV_PROTO_FH || mismatch) && hr >= 0;
+    const uint2 part = greedy_part(a.best, a.parts, lane & 16 ? max(m - 1, 0) : m, lane);
     // second layer; a position that is not scored reads sums that nobody wrote (inside the buffer) and drops the result
     float s2 = 0.f;
     if (a.splits) {
@@ -398,8 +393,12 @@ __global__ __launch_bounds__(64 * WISV_MAX_K) void k_decide(DecideArgs a) {
     } else {
         s2 = a.u[m];
     }
+    const int merged = greedy_token(part), own = __builtin_amdgcn_readlane(merged, 0), before = __builtin_amdgcn_readlane(merged, 16);
+    const bool mismatch = token != (j == 0 ? pn : before);
+    const bool sc = (a.gate_all || proto == WISV_PROTO_FH || mismatch) && hr >= 0;
     const float bias = a.bf16 ? bf16_to_f32(*(const bf16_t *)a.b2) : *(const float *)a.b2;
     if (lane == 0) {
+        greedy[j] = own;
         const float p = sc ? 1.0f / (1.0f + expf(s2 + bias)) : 1.0f;   // p_accept = 1 - sigmoid(s); 1 where not evaluated
         a.p_acc[m] = p;
         const bool decides = a.gate_all || mismatch, missing = decides && !sc;
@@ -416,7 +415,7 @@ __global__ __launch_bounds__(64 * WISV_MAX_K) void k_decide(DecideArgs a) {
     const uint64_t mask = __ballot(live && (fl & 1)), rejected = __ballot(live && (fl & 2)), missing = __ballot(live && (fl & 4));
     if (lane != 0) return;
     const int first = rejected ? __ffsll((unsigned long long)rejected) - 1 : a.k;
-    const int y = first == 0 ? pn : a.amax[b * a.k + first - 1];
+    const int y = first == 0 ? pn : greedy[first - 1];
     a.alen[b] = first;
     a.ytok[b] = y;
     if (a.mask_out) a.mask_out[b] = (uint32_t)mask;
@@ -429,7 +428,9 @@ __global__ __launch_bounds__(64 * WISV_MAX_K) void k_decide(DecideArgs a) {
 
 // How the first layer is cut: two or four row-blocks x one or two tiles of 16 positions, and as many splits of the columns (of at
 // least eight k-tiles) as make one round of 256 workgroups; of the two the one whose workgroups read less (a row-block of W1
-// costs a KiB per k-tile, 16 positions two KiB)
+// costs a KiB per k-tile, 16 positions two KiB).  The search's workgroups (4 to 256 of them) come last in the grid and share CUs
+// with these: first in it 96 rows take 14.6 us instead of 12.2; counted as part of the round 143 rows 24.2 instead of 16.2
+// and 256 rows 26.3 instead of 20.6, 512 rows the same (128256 tokens, event pairs).
 struct HeadCut { int rb, nt, gx, tiles, splits, kt_per_split; };
 static HeadCut head_cut(int rows, int nrb, int nkt) {
     const int pos = (rows + 15) / 16;
@@ -472,23 +473,26 @@ void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in, const wis
     a.k = f.k; a.rows = f.rows; a.act = g.head_act;
     a.b1 = c->head_b1; a.w2 = c->head_w2;
     a.u = c->hu;
-    a.cand = c->cand; a.amax = c->amax;
-    a.argmax_rows = find_tokens ? f.rows : 0;
+    a.cand = c->cand; a.best = c->best;
+    a.cut = greedy_cut(c->cand);
+    const int search = find_tokens ? a.cut.wgs : 0;
     int splits = 0;
     if (in.n_hd == 0) {          // nothing was uploaded: localisation only
-        if (find_tokens) launch_argmax(c, f.rows);
+        if (find_tokens) launch_argmax(c);
     } else {
         ProfScope ps(c, KC_HEAD);
         if (head_tiled(c)) {
             const HeadCut h = head_cut(f.rows, a.nrb, a.nkt);
             a.gx = h.gx; a.tiles = h.tiles; a.kt_per_split = h.kt_per_split;
             splits = h.splits;
-            const dim3 grid(a.argmax_rows + h.gx * h.tiles * h.splits);
+            a.search0 = h.gx * h.tiles * h.splits;
+            const dim3 grid(a.search0 + search);
             if (h.nt == 1) hipLaunchKernelGGL((k_head_fused<8, 2, 1, 6>), grid, dim3(512), 0, c->stream, a);
             else if (h.rb == 2) hipLaunchKernelGGL((k_head_fused<8, 2, 2, 4>), grid, dim3(512), 0, c->stream, a);
             else hipLaunchKernelGGL((k_head_fused<8, 4, 2, 3>), grid, dim3(512), 0, c->stream, a);
         } else {
-            const dim3 grid(a.argmax_rows + f.rows);
+            a.search0 = f.rows;
+            const dim3 grid(a.search0 + search);
             if (c->bf16) hipLaunchKernelGGL(k_head_ref<bf16_t>, grid, dim3(1024), 0, c->stream, a);
             else hipLaunchKernelGGL(k_head_ref<float>, grid, dim3(1024), 0, c->stream, a);
         }
@@ -496,7 +500,7 @@ void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in, const wis
     DecideArgs d{};
     d.batch = f.batch; d.k = f.k; d.rows = f.rows; d.max_batch = g.max_batch; d.act = g.head_act;
     d.gate_all = (in.flags & WISV_FLAG_GATE_ALL) ? 1 : 0; d.commit = (in.flags & WISV_FLAG_NO_COMMIT) ? 0 : 1;
-    d.stream_ids = in.stream_ids; d.tokens = in.draft_tokens; d.proto = in.proto; d.amax = c->amax;
+    d.stream_ids = in.stream_ids; d.tokens = in.draft_tokens; d.proto = in.proto; d.best = c->best; d.parts = a.cut.parts;
     d.hd_row = in.hd_row; d.n_hd = in.n_hd; d.tau = in.tau;
     d.u = c->hu; d.splits = splits; d.dJ = g.d_head_hidden; d.nrb = a.nrb;
     d.b1 = c->head_b1; d.w2 = c->head_w2; d.b2 = c->head_b2; d.bf16 = c->bf16 ? 1 : 0;

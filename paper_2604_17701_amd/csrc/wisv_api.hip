@@ -450,7 +450,7 @@ extern "C" int wisv_ctx_create(const wisv_config *config, const wisv_weights *we
     CREATE_TRY(dalloc(c, &c->d_alen, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_ytok, g.max_batch));
     CREATE_TRY(dalloc(c, &c->d_pacc, R));
-    CREATE_TRY(dalloc(c, &c->amax, R));
+    CREATE_TRY(dalloc(c, &c->best, (size_t)R * GREEDY_PARTS));
     {
         hipError_t e = hipSuccess;
         make_scratch(c, *c, R, [&](size_t bytes) -> void * {
@@ -501,7 +501,7 @@ extern "C" const char *wisv_last_error(const wisv_ctx *ctx) { return ctx ? ctx->
 // ------------------------------------------------------------------------------------------ the target forward
 
 // Enqueues the decoder over f.rows rows (Alg. 1 "Verify"): leaves h^T in c->h_t and the candidates for every row's greedy
-// token in c->cand (a prompt's last chunk: that token in c->amax[0]).
+// token in c->cand (a prompt's last chunk: the parts of that token in c->best).
 // The folded RMSNorms make every workgroup of the consuming product sum the slices (or stage the whole attention row)
 // itself, work that grows with the rows while the launch it saves does not.  At the 8B shape, one stream over 512
 // cached tokens: 4 rows 3.43 -> 3.38 ms per round with the folds; 8 rows 3.52 -> 3.72 ms, 16 rows 3.84 -> 4.14 ms.
@@ -638,7 +638,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
             }
             generic_lm_head();
         }
-        if (f.prefill) launch_argmax(c, 1);
+        if (f.prefill) launch_argmax(c);
         return;
     }
     for (int l = 0; l < g.n_layers; ++l) {
@@ -656,7 +656,7 @@ static void enqueue_forward(Ctx *c, const Fwd &f) {
     if (f.prefill && !f.want_last) return;
     launch_rmsnorm(c, out_rows, 1, c->final_norm, c->a, c->h_t, out_row0);
     generic_lm_head();
-    if (f.prefill) launch_argmax(c, 1);
+    if (f.prefill) launch_argmax(c);
 }
 
 // ------------------------------------------------------------------------------------------ verify round

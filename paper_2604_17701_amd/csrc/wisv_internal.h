@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -129,6 +130,43 @@ struct Candidates {
     const float *logits;
     int n, rows;
 };
+// How the search for the greedy tokens is cut: a workgroup looks through one of `parts` runs of the candidates of 2^shift
+// neighbouring rows (one row's logits) and leaves a (value, index) pair per row and part; whoever needs a token merges its
+// row's parts (greedy_token).  About 4096 candidates per workgroup, eight loads per thread, all on their way at once.
+constexpr int GREEDY_PARTS = 16;
+struct GreedyCut { int shift, parts, per, wgs; };
+inline GreedyCut greedy_cut(const Candidates &cd) {
+    GreedyCut g;
+    g.shift = 0;
+    while (cd.pairs && g.shift < 4 && 1 << g.shift < cd.rows) ++g.shift;
+    g.parts = std::min<int64_t>(GREEDY_PARTS, (((int64_t)cd.n << g.shift) + 4095) / 4096);
+    g.per = (cd.n + g.parts - 1) / g.parts;
+    g.parts = (cd.n + g.per - 1) / g.per;      // none of them is empty
+    g.wgs = (((cd.rows - 1) >> g.shift) + 1) * g.parts;
+    return g;
+}
+// the larger value wins, of equal ones the lower index; what is no number never does
+__device__ __forceinline__ void keep_better(float &v, int &i, float ov, int oi) {
+    if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
+}
+// a lane's part of row `row`, and the token that the sixteen parts of a group of sixteen lanes make (each group has its row)
+__device__ __forceinline__ uint2 greedy_part(const uint2 *best, int parts, int row, int lane) {
+    return best[(size_t)row * GREEDY_PARTS + min(lane & 15, parts - 1)];
+}
+// (exchanges inside a row of sixteen lanes: the other of a pair, the other pair of four, then the row's halves mirrored and the row)
+template <int CTRL> __device__ __forceinline__ void greedy_step(float &v, int &i) {
+    const float ov = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+    keep_better(v, i, ov, __builtin_amdgcn_mov_dpp(i, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ int greedy_token(uint2 part) {
+    float v = __uint_as_float(part.x);
+    int i = (int)part.y;
+    greedy_step<0xb1>(v, i);    // quad_perm 1 0 3 2
+    greedy_step<0x4e>(v, i);    // quad_perm 2 3 0 1
+    greedy_step<0x141>(v, i);   // row_half_mirror
+    greedy_step<0x140>(v, i);   // row_mirror
+    return i == 0x7fffffff ? 0 : i;
+}
 
 // The buffers a forward runs through.  The rounds of a ctx own one set, sized for the largest of them; a prompt's chunk
 // of more rows runs in another.
@@ -202,7 +240,7 @@ struct Ctx : Scratch {
     float *d_pacc;
 
     // scratch
-    int32_t *amax;
+    uint2 *best;                  // [rows][GREEDY_PARTS]: the best candidates of a row's greedy token, part by part
     Candidates cand;              // of the last forward
     float *h_t, *logits;
     float *ss2;                   // [d_model / 16][16]: those of the O projection that folds the FFN norm in
@@ -246,7 +284,7 @@ struct Fwd {
     bool keep_logits;
     int max_len_ub;              // upper bound of kv_len + k over the streams of this forward
     bool prefill = false;        // a chunk of a prompt (batch 1): only its last row's greedy token matters, ...
-    bool want_last = false;      // ... and that only in the last chunk; it is left in c->amax[0]
+    bool want_last = false;      // ... and that only in the last chunk; its parts are left in c->best
 };
 
 // ---------------------------------------------------------------- kernel launchers (kernels_ref.hip)
@@ -267,13 +305,13 @@ void launch_gemm_ref_swiglu(Ctx *c, const float *A, const void *W, const ActBuf 
 // n_ss > 0: the slices are scaled by 1 / rms from the n_ss partial sums of squares in c->ss (folded RMSNorm)
 void launch_rope_append(Ctx *c, const Fwd &f, int layer, int n_partial, int n_ss = 0);
 void launch_attn_ref(Ctx *c, const Fwd &f, int layer);
-// kv_len[slot] = new_len; pred_next[slot] = amax[row] unless row is negative
+// kv_len[slot] = new_len; pred_next[slot] = the greedy token of row `row` unless that is negative
 void launch_set_pred_next(Ctx *c, int slot, int row, int new_len);
 
 // ---------------------------------------------------------------- decision head + scan (kernels_head.hip)
-// the greedy token of every row, from c->cand to c->amax
-void launch_argmax(Ctx *c, int rows);
-// find_tokens: c->amax is still to be made from c->cand
+// the parts of every row's greedy token, from c->cand to c->best
+void launch_argmax(Ctx *c);
+// find_tokens: c->best is still to be made from c->cand
 void launch_head_decide(Ctx *c, const Fwd &f, const wisv_round_in &in_dev, const wisv_round_out &out_dev, bool find_tokens);
 size_t head_scratch_floats(const Ctx *c, int rows);   // of c->hu
 void launch_pad_cols(Ctx *c, const void *src, void *dst, int rows, int cols, int cols_pad);

@@ -485,6 +485,47 @@ def test_kept_logits_in_one_piece_in_many_and_by_the_runtime_s_copy_agree():
     ctx.wisv_destroy()
 
 
+@pytest.mark.parametrize("base,vocab,batch,k", [
+    ("bf16", 2003, 1, 1), ("bf16", 40003, 1, 2), ("bf16", 40003, 1, 5), ("bf16", 9001, 3, 3), ("bf16", 70001, 2, 8),   # a candidate per 16 tokens
+    ("bf16", 70001, 17, 1), ("bf16", 2003, 11, 3), ("bf16", 70001, 13, 11),                                            # per 32 tokens
+    ("bf16", 9001, 23, 7), ("bf16", 70001, 20, 15),                                                                    # per 64 tokens
+    ("f32", 70001, 1, 4), ("f32", 203, 3, 3)])                                                                         # whole rows of logits
+def test_greedy_tokens_of_ties_and_of_all_cuts_of_the_search(base, vocab, batch, k):
+    """Every row's greedy token against its own logits, where each token of the first half has a twin of equal logits in the second
+    and one token's logits are no numbers: the search inside the decision head's launch, by itself (VERIFY_ONLY) and of a prompt."""
+    model = replace(MID128, n_layers=1, d_model=256, n_heads=2, n_kv_heads=1, d_ff=256, vocab=vocab) if base == "bf16" else \
+        replace(W0.model, n_layers=1, vocab=vocab)
+    w = replace(W0, model=model, batch=batch, ctx=5, k=k, protos=(PROTO_FH,) * batch, name=f"greedy_{base}_{vocab}_b{batch}_k{k}", index=53)
+    dev, half, rows = torch.device("cuda:0"), vocab // 2, batch * k
+    wd = gen.make_weights(w.model, w.seed, dev)
+    wd["lm_head"][half:2 * half] = wd["lm_head"][:half].clone()
+    wd["lm_head"][7] = wd["lm_head"][half + 7] = float("nan")
+    ctx = _ctx(w, wd, extra_ctx=2)
+    rng = np.random.default_rng(vocab + rows)
+    for s in range(batch):
+        ctx.wisv_prefill(s, rng.integers(0, vocab, 5).astype(np.int32))
+        ln, pred = ctx.wisv_get_state(s)
+        assert ln == 5 and 0 <= pred < half and pred != 7
+    drafts, sid, nc = rng.integers(0, vocab, rows).astype(np.int32), np.arange(batch), binding.WISV_FLAG_NO_COMMIT
+    csi, tau = np.zeros((batch, model.d_csi), np.float32), np.full(batch, 0.45, np.float32)
+    hd = torch.randn(rows, model.d_draft).to(torch.bfloat16 if base == "bf16" else torch.float32)
+    g = ctx.wisv_verify_round(sid, drafts, [PROTO_FH] * batch, hd, np.arange(rows), csi, tau, k, nc | binding.WISV_FLAG_KEEP_LOGITS)
+    z = ctx.wisv_debug_copy(binding.WISV_DBG_LOGITS, rows)
+    want = np.nanargmax(z, 1).reshape(batch, k)          # the first of equal ones
+    assert (want < half).all() and np.isnan(z[:, 7]).all()
+    np.testing.assert_array_equal(np.asarray(g["target_argmax"]).reshape(batch, k + 1)[:, 1:], want)
+    first = ctx.wisv_verify_round(sid, drafts, [PROTO_FH] * batch, None, np.full(rows, -1), csi, tau, k, binding.WISV_FLAG_VERIFY_ONLY)
+    np.testing.assert_array_equal(first["target_argmax"], g["target_argmax"])
+    second = ctx.wisv_verify_round(sid, drafts, [PROTO_FH] * batch, hd, np.arange(rows), csi, tau, k, binding.WISV_FLAG_DECIDE_ONLY | nc)
+    for key in g:
+        np.testing.assert_array_equal(second[key], g[key])
+    # the prompt's last row is the round's first one
+    ctx.wisv_set_state(0, 5, 0)
+    ctx.wisv_prefill(0, drafts[:1])
+    assert z[0, ctx.wisv_get_state(0)[1]] >= np.nanmax(z[0]) - 1e-2 * np.nanstd(z[0])
+    ctx.wisv_destroy()
+
+
 def test_small_bf16_decoder_synthetic_kv():
     w = replace(configs.get(2), model=replace(MID, head_dim=128, n_heads=4, n_kv_heads=1), batch=2, ctx=1100, k=8,
                 protos=(PROTO_SH, PROTO_FH), name="mid_bf16_synthkv", index=8)
