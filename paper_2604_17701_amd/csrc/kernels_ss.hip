@@ -109,12 +109,13 @@ k_ss_stats(const float *__restrict__ logits, int V, int C, int n_chunks, bool ve
 #pragma unroll
         for (int e = 0; e < 8; ++e) m = fmaxf(m, x[w][e]);
     m = wave_max(m);
+    const float ref = m == -INFINITY ? 0.f : m;   // a chunk without a finite logit weighs nothing: -inf less -inf would be no number
     float z[G];
 #pragma unroll
     for (int w = 0; w < G; ++w) {
         z[w] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) z[w] += exp_nonpos(x[w][e] - m);   // 0 beyond the row's end
+        for (int e = 0; e < 8; ++e) z[w] += exp_nonpos(x[w][e] - ref);   // 0 beyond the row's end
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)

@@ -38,10 +38,12 @@ def wide_vocab_ctx():
     ctx.wisv_destroy()
 
 
-def _decide_case(ctx, seed, batch, k, vocab, scale, tol=2e-6):
+def _decide_case(ctx, seed, batch, k, vocab, scale, tol=2e-6, masked=()):
     rows = batch * k
     rng = np.random.default_rng(seed)                     # test-side choices only (which rows get which recipe)
     logits = gen.target_logits(seed, rows, vocab, scale)
+    for lo, hi in masked:
+        logits[:, lo:hi] = -np.inf
     tokens = gen.randint(seed, "ss_tok", (rows,), vocab).numpy().astype(np.int32)
     top = np.argmax(logits, axis=1).astype(np.int32)      # drafts that hit a likely token: rows shifted by one position
     likely = rng.random(rows) < 0.6
@@ -90,6 +92,13 @@ def test_ss_decide_full_vocabulary(wide_vocab_ctx, batch, k, scale):
 def test_ss_decide_edges_of_the_chunks(wide_vocab_ctx, vocab):
     """Vocabularies that end before, at and behind a chunk of 2048 tokens, with and without rows on 16-byte boundaries."""
     _decide_case(wide_vocab_ctx, 31 + vocab, 3, 5, vocab, 2.5)
+
+
+@pytest.mark.parametrize("vocab,masked", [(6144, [(0, 2048)]), (6144, [(2048, 6144)]), (4099, [(4096, 4099)]), (6145, [(100, 5000), (6144, 6145)]),
+                                          (128256, [(0, 60000), (64000, 128256)])])
+def test_ss_decide_masked_logits(wide_vocab_ctx, vocab, masked):
+    """Logits of minus infinity, whole chunks of 2048 tokens of them: those tokens have no probability and the others keep theirs."""
+    _decide_case(wide_vocab_ctx, 57 + vocab, 4, 5, vocab, 2.5, masked=masked)
 
 
 def test_ss_decide_rejects_bad_arguments(tiny_ctx):
