@@ -65,16 +65,6 @@ __device__ __forceinline__ void ss_load8(const float *__restrict__ row, int i0, 
     }
 }
 
-// e^d for d <= 0 (or NaN), to the bit what expf gives there: 2^(d log2 e) with the product in two floats, split into its nearest
-// integer and the rest.  expf also looks for overflow, and k_ss_stats is close to bound by what it issues per logit.
-__device__ __forceinline__ float exp_nonpos(float d) {
-#pragma clang fp contract(off)
-    const float L = 0x1.715476p+0f, Llo = 0x1.4ae0bep-26f;   // log2 e and what a float leaves of it
-    const float p = d * L, e = __builtin_rintf(p), lo = __builtin_fmaf(d, Llo, __builtin_fmaf(d, L, -p));
-    const float r = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((p - e) + lo), (int)e);
-    return d < -0x1.9d1da0p+6f ? 0.f : r;                   // (at minus infinity p - e is no number)
-}
-
 // One wave per chunk, nothing shared between waves: all its 8 KiB are requested at once, and waves in different phases keep the
 // memory busy (512 rows x 128256 logits: 54.6 us with a workgroup per chunk and its three barriers, 40.5 now; a stream
 // of 263 MB takes 42).  The sums are those of 256 threads with eight consecutive logits each, four such groups of 64 per lane.
@@ -115,7 +105,7 @@ k_ss_stats(const float *__restrict__ logits, int V, int C, int n_chunks, bool ve
     for (int w = 0; w < G; ++w) {
         z[w] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) z[w] += exp_nonpos(x[w][e] - ref);   // 0 beyond the row's end
+        for (int e = 0; e < 8; ++e) z[w] += expf(x[w][e] - ref);   // 0 beyond the row's end
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
