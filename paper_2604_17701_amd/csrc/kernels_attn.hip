@@ -626,7 +626,7 @@ bool launch_attn_mfma(Ctx *c, const Fwd &f, int layer, int n_partial, bool with_
         ProfScope ps(c, KC_ATTN);
         bool ok;
         switch ((R + 15) / 16) {
-            case 1: ok = prompt ? launch_prompt_nq<2, 8>(c, a, grid) : launch_nq<1, 8>(c, a, grid); break;
+            case 1: ok = launch_nq<1, 8>(c, a, grid); break;   // (a prompt's blocks have at least 25 query rows)
             case 2: ok = prompt ? launch_prompt_nq<2, 8>(c, a, grid) : launch_nq<2, 8>(c, a, grid); break;
             case 3: ok = prompt ? launch_prompt_nq<3, 4>(c, a, grid) : launch_nq<3, 4>(c, a, grid); break;
             default: ok = prompt ? launch_prompt_nq<4, 4>(c, a, grid) : launch_nq<4, 4>(c, a, grid); break;
