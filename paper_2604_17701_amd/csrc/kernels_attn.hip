@@ -52,8 +52,11 @@ struct AttnArgs {
 //
 // PROMPT is bound by the vector and matrix instructions of its waves, about as many cycles of either per step: two waves per
 // SIMD overlap them, which takes at most 256 registers and 80 KB of LDS.  Three query tiles meet that (four spill), and the
-// waves' outputs are merged in two parts of the features (1999 tokens behind nothing, 16 x 6 ctx, per chunk and layer: four
-// tiles, one wave per SIMD 87.5 us; four capped with spills 77.1; three 67.0; two 92.0.  512 tokens: 26.7, 33.1, 23.7, 30.3).
+// waves' outputs are merged in two parts of the features.  us per layer, event pairs (4.5 of bracketing), mean of the two chunks of a
+// prompt of 1999 tokens / the one of 512, four query heads per KV head, the queries still rotated by a kernel before this one: four
+// tiles, one wave per SIMD 87.5 / 26.7; four capped with spills 77.1 / 33.1; three 67.0 / 23.7; two 92.0 / 30.3.  That
+// kernel, which rotated the queries and appended k and v, and this one together: 117.6 / 42.1 with four tiles, 86.1 / 30.3
+// with three and the rotation inside.
 // Rounds of three and four tiles, one workgroup per CU at most, keep the registers of one wave (143 rows: 42.0 us, capped 42.7).
 constexpr int attn_merge_parts(int nq) { return nq > 2 ? 2 : 1; }
 template <int NQ, int NW, bool PROMPT, int NP, int NSS>
@@ -411,8 +414,8 @@ __global__ __launch_bounds__(64 * NW, PROMPT && NQ < 4 ? 2 : 1) void k_attn_mfma
 // ------------------------------------------------------------------------------------------ a prompt's keys and values
 // The chunk's rows lie at consecutive positions of one slot.  One workgroup = one block of 32 positions of the cache x one KV
 // head, k (blockIdx.z 0: rotated, 16-byte stores) or v (1: turned over in LDS, since the V plane keeps 32 positions of a feature
-// together).  Slices are added in slice order; n_ss as in AttnArgs (at most 1).  1024 rows of the 8B shape: 6 us; a
-// workgroup per row and head, which rotated the queries too, 26.2.
+// together).  Slices are added in slice order; n_ss as in AttnArgs (at most 1).  Event pairs, chunks of 1000 / 512 rows of the 8B
+// shape: 10.6 / 6.6 us; a workgroup per row and head, which rotated the queries too, 27.5 / 14.4.
 struct AppendArgs {
     const float *qkv;
     int n_partial;
@@ -564,7 +567,9 @@ template <int NQ, int NW> static bool launch_prompt_nq(Ctx *c, const AttnArgs &a
 //
 // A prompt's chunk has more rows than the 64 query rows one workgroup meets: it is cut into blocks of about 48 query rows,
 // each treated as a stream of its own whose cached length is its first row's position (k_kv_append has written the
-// whole chunk's k, v rows before, and a block's causal limit is its own last position).
+// whole chunk's k, v rows before, and a block's causal limit is its own last position).  With 25 to 32 query heads per KV head
+// that is one token, so that keys are read twice as often as by blocks of two (four query tiles): 1000 tokens, 28 / 1 heads
+// 60 us per layer against 52, 64 / 2 heads 117 against 107; but 256 tokens, 28 / 1 heads 18 against 25, half as many workgroups.
 static int attn_block(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
     const int rep = g.n_heads / g.n_kv_heads;

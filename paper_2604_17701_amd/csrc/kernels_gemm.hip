@@ -1301,7 +1301,9 @@ static void fill_args(GemmArgs &g, const void *Wt, const ActBuf &X, int rows, in
 }
 
 // Slices of 8 k-tiles (QKV and O at the 8B shape) stay at a ring of four (of eight: QKV 9.4 -> 9.9 us, O 6.3 -> 6.8), slices of
-// 28 (down) take four turns of seven (18.8 -> 18.1)
+// 28 (down) take four turns of seven (18.8 -> 18.1).  So do all lengths that seven divides, whether four does or not: down from as
+// many features as make slices of 14 / 21 / 28 / 35 / 42 / 56 k-tiles, 4 rows, event pairs, with the ring of four 14.8 / 19.7 / 23.0
+// / 31.3 / 33.3 / 41.7 us, of seven 13.5 / 18.0 / 22.5 / 28.1 / 31.2 / 40.5; 15 rows alike.
 static bool launch_ws_partial_t(Ctx *c, GemmArgs &g, int splits) {
     if (g.kt_per_split % 7) return launch_ws_t<1, 1, 8, 1, 4, 4, EPI_PARTIAL>(c, g, splits, 40 * 1024);
     return launch_ws_t<1, 1, 8, 1, 4, 7, EPI_PARTIAL>(c, g, splits, 40 * 1024);

@@ -1,11 +1,11 @@
 // Decision head, mismatch localisation and the first-reject scan (Sec. V-A eqs. feature_concat /
 // head_forward / mlp_form; eq. threshold; Alg. 1 last block).
 //
-//   1. head     one launch for two things that do not need each other: the greedy token of every row from the LM head's
-//               candidates, and the head's first layer over [h^D ; h^T ; c] for every position with an uploaded h^D row
-//   2. decide   per stream: localisation, second layer and accept probabilities of the scored positions (FH: positions
-//               with an h^D row; SH: mismatch positions with one), mismatch mask, earliest rejected position, accepted
-//               length, correction token, and the commit of the stream state
+//   1. head     one launch for two things that do not need each other: the head's first layer over [h^D ; h^T ; c] for every
+//               position with an uploaded h^D row, and the search for every row's greedy token among the LM head's candidates
+//   2. decide   per stream: the parts of that search merged, localisation, second layer and accept probabilities of the scored
+//               positions (FH: positions with an h^D row; SH: mismatch positions with one), mismatch mask, earliest rejected
+//               position, accepted length, correction token, and the commit of the stream state
 #include <algorithm>
 
 #include "wisv_internal.h"

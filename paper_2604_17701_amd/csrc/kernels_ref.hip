@@ -181,7 +181,9 @@ void launch_embed(Ctx *c, const Fwd &f, const void *g, const ActBuf &out, float 
 // SWIGLU: W stacks gate over up; the wave of feature o takes both of its rows and H[r, o] = silu(gate) * up
 // Bound by latency at the small shapes it serves: every row of a pass is requested before the first is used (rows past the last
 // re-read it).  The tiny fp32 target, four rows: 1.5 to 2 us per launch, 1.5 to 2.6 with each row's loads behind a branch, and
-// SwiGLU needs no launch of its own (2 us and a gap); the whole call 178 -> 155 us.
+// SwiGLU needs no launch of its own (2 us and a gap); the whole call 178 -> 155 us.  With SwiGLU a pass takes four rows whatever
+// their count: eight read the weights half as often and leave half as many waves.  fp32, 1024 to 2 x 2816 features, us per launch
+// (event pairs), four / eight: 5 rows 11.4 / 13.1, 8 12.2 / 14.0, 16 16.8 / 19.3, 32 26.2 / 27.1, 128 77 / 82, 512 285 / 299.
 template <typename WT, typename AT, int MT, bool SWIGLU>
 __global__ void k_gemm_ref(const AT *__restrict__ A, const WT *__restrict__ W, float *__restrict__ Y, ActBuf H, int rows, int n, int kd) {
     constexpr int NW = SWIGLU ? 2 : 1;

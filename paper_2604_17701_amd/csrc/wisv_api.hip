@@ -16,9 +16,8 @@ struct wisv_ctx : public wisv::Ctx {};
 
 // Rows of one prefill chunk: a prompt is bound by the weight stream while a chunk is short (a pass costs the same up to
 // a few dozen rows) and by the matrix cores beyond some hundred.  Measured on four layers of the 8B shape, 1999 tokens:
-// chunks of 96 rows with the generic attention kernel 82.6 ms; of 512 rows 6.08 ms, 1024 rows 5.52 ms, 2048 rows
-// 5.25 ms.  512 tokens in chunks of 4 rows 62.3 ms, in one chunk 2.15 ms.  The buffers of 1024 rows hold about 0.35 GB
-// at the 8B shape; doubling them would buy 5 %.
+// chunks of 96 rows 12.2 ms, of 512 rows 5.75, 1024 rows 5.23, 2048 rows 4.88.  512 tokens in chunks of 4 rows 49 ms, in
+// one chunk 2.07.  The buffers of 1024 rows hold about 0.35 GB at the 8B shape; doubling them would buy 7 %.
 constexpr int PREFILL_ROWS = 1024;
 
 // Uploaded hidden states of a host-pointer round up to this size are packed with the other arguments (512 rows of 2048
@@ -1129,7 +1128,7 @@ extern "C" int wisv_prefill(wisv_ctx *ctx, int32_t stream_id, const int32_t *tok
     int32_t len = 0;
     if (int rc = wisv_get_state(ctx, stream_id, &len, nullptr)) return rc;
     if (len + n > g.max_ctx) return fail(c, WISV_ESTATE, "prefill of %d tokens at length %d exceeds max_ctx %d", n, len, g.max_ctx);
-    c->pending_valid = false;   // the forward below overwrites h^T, the greedy tokens and the row map a VERIFY_ONLY call left
+    c->pending_valid = false;   // the forward below overwrites h^T and the greedy tokens a VERIFY_ONLY call left
     const int rc = prefill_chunks(c, &stream_id, tokens, n, len);
     if (rc == WISV_OK) {
         c->h_len_ub[stream_id] = len + n;
@@ -1274,7 +1273,8 @@ extern "C" int wisv_kv_export(wisv_ctx *ctx, int32_t stream_id, int32_t layer, v
 
 // Results to pageable memory, a multiple of 16 bytes: kernels write pieces into pinned memory ahead of the host, which copies each
 // on as it arrives (16 KB of logits of the tiny target: the round and this 159 us with the runtime's own copy, 143 so; 2 MB of the
-// 8B shape's 3463, 3437)
+// 8B shape's 3463, 3437).  No size is sent the other way: 2 / 14 / 49 / 263 MB into memory touched before 116 / 850 / 2860 / 15300 us
+// with the runtime's copy, 90 / 580 / 2480 / 15300 so; into fresh memory 49 / 263 MB 5100 / 25500 and 4100 / 21500.
 static hipError_t read_back(Ctx *c, void *dst, const void *src, size_t bytes) {
     constexpr size_t READ_PIECE = Ctx::READ_PIECE, PIECES = Ctx::READ_PIECES;
     const size_t n = (bytes + READ_PIECE - 1) / READ_PIECE;
