@@ -568,14 +568,20 @@ template <int NQ, int NW> static bool launch_prompt_nq(Ctx *c, const AttnArgs &a
 // A prompt's chunk has more rows than the 64 query rows one workgroup meets: it is cut into blocks of about 48 query rows,
 // each treated as a stream of its own whose cached length is its first row's position (k_kv_append has written the
 // whole chunk's k, v rows before, and a block's causal limit is its own last position).  With 25 to 32 query heads per KV head
-// that is one token, so that keys are read twice as often as by blocks of two (four query tiles): 1000 tokens, 28 / 1 heads
-// 60 us per layer against 52, 64 / 2 heads 117 against 107; but 256 tokens, 28 / 1 heads 18 against 25, half as many workgroups.
+// that is one token, and blocks of two (four query tiles, one workgroup per CU) read the keys half as often: they are taken where
+// they fill seven eighths of their last round of 256 workgroups.  us per layer, event pairs, blocks of one / two, tokens behind
+// nothing and behind 1000: 1000 tokens, 28 / 1 heads (500 workgroups of two) 61.5 / 53.7 and 103.8 / 99.5, 64 / 2 heads (1000)
+// 117.9 / 108.5 and 202 / 195, 112 / 4 heads (2000) 218 / 189 and 387 / 362; 512 tokens, 28 / 1 heads (256) 29.6 / 28.9 and 50.7 /
+// 53.0.  Below that line: 256 tokens, 28 / 1 heads (128) 16.2 / 21.5 and 28.5 / 44.8; 640 tokens (320) 41.1 / 37.6 and 71.5 / 83.5.
 static int attn_block(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;
     const int rep = g.n_heads / g.n_kv_heads;
     if (!c->bf16 || g.head_dim != HD || rep > 64 || f.rows != f.batch * f.k) return 0;
     if (rep * f.k <= 64) return f.k;
-    return f.prefill ? std::max(1, 48 / rep) : 0;   // a round's larger block goes to the generic kernel
+    if (!f.prefill) return 0;   // a round's larger block goes to the generic kernel
+    const int wgs = (f.rows + 1) / 2 * g.n_kv_heads, rounds = (wgs + 255) / 256;
+    if (rep > 24 && rep <= 32 && 8 * wgs >= 7 * 256 * rounds) return 2;
+    return std::max(1, 48 / rep);
 }
 static int attn_splits(const Ctx *c, const Fwd &f) {
     const wisv_config &g = c->cfg;

@@ -627,8 +627,9 @@ def test_mixed_context_lengths_in_one_round(lengths, k):
     (MID128, 1, 4, (15, 16, 17, 31, 33, 64, 65, 130)),       # two bf16 terms; up to 16 tokens are one block
     (MID128, 1, 4, (24, 25, 36, 95)),                        # blocks of 12 tokens: whole ones, a last one of one and of eleven
     (replace(MID128, n_heads=28, n_kv_heads=1), 1, 2, (6, 35)),   # 28 query heads per KV head: blocks of one token
+    (replace(MID128, n_heads=200, n_kv_heads=8), 1, 2, (54, 55, 64)),   # 25 of them: of one, of two (the last one of one), of two
     (replace(MID128, n_heads=56, n_kv_heads=1), 1, 1, (2, 35, 130)),   # 56 of them: four query tiles to a block
-    (replace(MID128, n_layers=1, d_model=2048, n_heads=64, n_kv_heads=1), 1, 1, (3, 33)),   # 64, and more slices of the QKV product
+    (replace(MID128, d_model=2048, n_heads=64, n_kv_heads=1), 1, 1, (3, 33)),   # 64, and more slices of the QKV product
     (MID128, 1, 1, (3, 20)),                                 # more rows in a prompt's chunk than the largest round has
     (MID128, 6, 4, (24, 40, 97, 1061)),                      # rounds beyond 16 rows exist: a leftover of 1, 16, 1, 5 tokens
     (replace(MID128, n_heads=12, n_kv_heads=4), 1, 4, (21, 43, 150)),   # three query heads per KV head: blocks of 21 tokens
