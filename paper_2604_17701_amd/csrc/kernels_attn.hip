@@ -567,7 +567,9 @@ template <int NQ, int NW> static bool launch_prompt_nq(Ctx *c, const AttnArgs &a
 //
 // A prompt's chunk has more rows than the 64 query rows one workgroup meets: it is cut into blocks of about 48 query rows,
 // each treated as a stream of its own whose cached length is its first row's position (k_kv_append has written the
-// whole chunk's k, v rows before, and a block's causal limit is its own last position).  With 25 to 32 query heads per KV head
+// whole chunk's k, v rows before, and a block's causal limit is its own last position).  Blocks of 64 / rep tokens take 1.07 to 1.76
+// times as long with 4 to 20 query heads per KV head, 1 to 8 KV heads, 128 to 1000 tokens behind nothing or 1000; the same with 128 / 8
+// heads over 128 tokens and, being the same two tokens, with 22 to 24 heads per KV head.  With 25 to 32 query heads per KV head
 // that is one token, and blocks of two (four query tiles, one workgroup per CU) read the keys half as often: they are taken where
 // they fill seven eighths of their last round of 256 workgroups.  us per layer, event pairs, blocks of one / two, tokens behind
 // nothing and behind 1000: 1000 tokens, 28 / 1 heads (500 workgroups of two) 61.5 / 53.7 and 103.8 / 99.5, 64 / 2 heads (1000)

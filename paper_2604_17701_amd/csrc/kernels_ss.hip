@@ -66,7 +66,7 @@ __device__ __forceinline__ void ss_load8(const float *__restrict__ row, int i0, 
 }
 
 // One wave per chunk, nothing shared between waves: all its 8 KiB are requested at once, and waves in different phases keep the
-// memory busy (512 rows x 128256 logits: 54.6 us with a workgroup per chunk and its three barriers, 40.5 now; a stream
+// memory busy (512 rows x 128256 logits: 54.6 us with a workgroup per chunk and its three barriers, 41.1 now; a stream
 // of 263 MB takes 42).  The sums are those of 256 threads with eight consecutive logits each, four such groups of 64 per lane.
 __global__ void __launch_bounds__(SS_THREADS)
 k_ss_stats(const float *__restrict__ logits, int V, int C, int n_chunks, bool vec, float *__restrict__ pm, float *__restrict__ pz) {
