@@ -392,8 +392,8 @@ void launch_v_reblock(Ctx *c, void *rows, void *plane, int len, bool to_plane) {
 }
 
 // after a prefill chunk: the slot's length grows by the chunk; after the last one pred_next = the last row's greedy token
-__global__ __launch_bounds__(64) void k_set_pred_next(int32_t *kv_len, int32_t *pred_next, const uint2 *best, int parts, int slot, int row,
-                                                      int new_len) {
+__global__ __launch_bounds__(64) void k_set_pred_next(int32_t *kv_len, int32_t *pred_next, const uint2 *best, int slot, int row, int new_len,
+                                                      int parts) {
     const int token = row >= 0 ? greedy_token(greedy_part(best, parts, row, threadIdx.x)) : 0;
     if (threadIdx.x) return;
     if (row >= 0) pred_next[slot] = token;
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(64) void k_set_pred_next(int32_t *kv_len, int32_t *
 
 void launch_set_pred_next(Ctx *c, int slot, int row, int new_len) {
     const int parts = row >= 0 ? greedy_cut(c->cand).parts : 1;
-    hipLaunchKernelGGL(k_set_pred_next, dim3(1), dim3(64), 0, c->stream, c->d_kv_len, c->d_pred_next, c->best, parts, slot, row, new_len);
+    hipLaunchKernelGGL(k_set_pred_next, dim3(1), dim3(64), 0, c->stream, c->d_kv_len, c->d_pred_next, c->best, slot, row, new_len, parts);
 }
 
 }  // namespace wisv

@@ -116,10 +116,10 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t ld
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].host == f) name = kernels[i].name;
     note(name);
-    if (strstr(name, "k_set_pred_next")) {   /* (kv_len, pred_next, amax, slot, row, new_len) */
-        int32_t *kv_len = *(int32_t **)args[0], *pred_next = *(int32_t **)args[1], *amax = *(int32_t **)args[2];
+    if (strstr(name, "k_set_pred_next")) {   /* (kv_len, pred_next, best, slot, row, new_len, parts) */
+        int32_t *kv_len = *(int32_t **)args[0], *pred_next = *(int32_t **)args[1], *best = *(int32_t **)args[2];
         const int slot = *(int *)args[3], row = *(int *)args[4];
-        if (row >= 0) pred_next[slot] = amax[row];
+        if (row >= 0) pred_next[slot] = best[2 * 16 * row + 1];   /* the token of the row's first (value, token) pair */
         kv_len[slot] = *(int *)args[5];
     }
     return OK;
